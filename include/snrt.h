@@ -217,7 +217,11 @@ typedef struct {
  * moment-form scatter handle in a BF16 / FP16 precision, triangles and nq % 256 == 0 the step
  * runs as one launch: the scattering product's tiles update their cells and ordinates, and
  * S = Psi B never reaches the workspace (the environment variable SNRT_STEP_FUSED=0, read
- * once per process, selects the product-then-step form; both give the same bits). */
+ * once per process, selects the product-then-step form; both give the same bits).
+ * Kernels that are functions of Omega_q . Omega_p on a product rule (one weight and 16 or 32
+ * equally spaced azimuths per polar node, 8 to 32 polar nodes; checked on the entries when the
+ * handle is made) run in every precision mode as FP32 products of the azimuthal modes, in one
+ * launch for triangles and quadrilaterals; their product's error is that of FP32 rounding. */
 snrt_status snrt_step(const snrt_mesh* mesh, const snrt_quad* quad, const snrt_scatter* scatter,
                       const snrt_step_args* args, const float* psi_in, float* psi_out,
                       void* ws, size_t ws_bytes, void* stream);
@@ -228,7 +232,8 @@ snrt_status snrt_step(const snrt_mesh* mesh, const snrt_quad* quad, const snrt_s
  *     dose[i] += coeff * inv_rho[i] * sum_q w_q psi_in[i][q]   (FP64; inv_rho NULL = 1)
  * psi_out is bitwise the output of snrt_step; the dose agrees with snrt_dose_accumulate to
  * FP64 rounding (the sum is formed per row piece of the dense step: 128 ordinates in the
- * one-launch form, 256 in the two-launch form; then the pieces are added in order;
+ * one-launch form, 256 in the two-launch form, whole rows with azimuthal modes; then the
+ * pieces are added in order;
  * deterministic).  ws: at least snrt_workspace_size bytes,
  * 16-byte aligned.  dose must not overlap the states or the workspace (SNRT_E_ALIAS);
  * SNRT_E_NONFINITE for a non-finite coeff. */

@@ -23,7 +23,8 @@ SOURCES = ["sn_pn13.hip", "sn_gemm_mfma.hip", "sn_step_fused.hip", "sn_step_fuse
            "sn_step_fused_adjoint.hip", "snrt_api.hip", "sn_step_f32.hip", "sn_step_f64.hip", "sn_adjoint.hip",
            "sn_reduce.hip", "sn_gemm_simple.hip", "sn_step2.hip", "sn_step_imex.hip",
            "sn_pn.hip", "snrt_pn_api.hip", "snrt_rollout.hip", "snrt_noalloc.hip",
-           "snrt_eig.hip"]
+           "snrt_eig.hip", "snrt_azimuth.hip", "sn_azimuth_step.hip",
+           "sn_azimuth_adjoint.hip"]
 ARCH = os.environ.get("SNRT_OFFLOAD_ARCH", "gfx950")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 

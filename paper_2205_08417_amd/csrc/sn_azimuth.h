@@ -1,0 +1,876 @@
+// Scattering through azimuthal modes (kernel templates; instantiated by sn_azimuth_*.hip).
+//
+// A kernel k(Omega_q . Omega_p) on a product rule (q = k na + l: polar node k, equally spaced
+// azimuth l) couples two ordinates through their polar nodes and the difference of their
+// azimuths only: S[k,l] = sum_{k',l'} a_{kk'}(l - l') psi[k',l'], a even in the difference.  A
+// real Fourier transform over the azimuths makes that one polar matrix per mode m,
+// D_m[k][k'] = sum_d a_{kk'}(d) cos(2 pi f_m d / na), instead of one nq x nq matrix:
+//     X = F psi,   Y_m = D_m X_m,   S = F^T Y,
+// 3 * 2 nq * 16 operations per cell after the two foldings below instead of 2 nq * nq (nq =
+// 1024: 1/21).  What is left fits beside the transport update's memory traffic, so all of it
+// runs in FP32 on the matrix cores (v_mfma_f32_16x16x4_f32): no operand split, and an error
+// below that of the three-product BF16 split (product of a two-decade state: 1.3e-7).
+// Measured against the general products' one-launch steps (BF16x3): 100 352 cells x 1024 ordinates
+// 0.235 against 0.658 ms (a copy of the state: 0.131), FP32 handles 1.8 ms; 299 538 x 512 with its
+// dose 0.348 against 0.690 ms; the transposed step on 74 498 x 512 0.147 against 0.237 ms.  What
+// bounds it now: the vector update (0.10 ms of issue at 1024 ordinates), the matrix instructions
+// (0.065 ms) and the row traffic overlap only across the waves between two barriers.
+//
+// Foldings, so that every contraction is 16 long:
+//   * azimuth (na = 32): x_l +- x_{l+16}; the sums carry the even modes, the differences the odd;
+//   * polar (16 < np <= 32, np even, kernel unchanged by mu -> -mu): x_k +- x_{np-1-k}, k < np/2.
+// A row is then NC = 1, 2 or 4 classes of 16 polar x 16 azimuthal slots (np or np/2 below 16:
+// zero-padded operands, clamped lanes).
+//
+// One wave owns one cell (16 < np, 32 azimuths: one polar half of a cell, two waves per cell).
+// Rows are read, updated and written in memory order, 1 KB per access of a wave; the matrix
+// instructions want lane (kk = lane & 15, l4 = lane >> 4) to hold azimuths 4 l4 .. 4 l4 + 3 of
+// polar slot kk, whose 16-byte pieces of 16 rows cost the address unit four times the accesses
+// (0.35 against 0.24 ms per step at 100 352 x 1024), so rows change order through the wave's own
+// corner of LDS.  The waves of eight cells form a block and exchange through LDS:
+//   1. azimuthal fold (lane-local), X[k][m] = sum_l x[k][l] F[l][m] per class (4 MFMA), to LDS as
+//      [class][polar half][m][cell][k];
+//   2. a wave takes the modes 2j, 2j + 1 of a class: their 2 x 8 cells are the 16 columns of
+//      Y = D X (the cosine and sine of one frequency share D), polar fold around it, in place;
+//   3. S[l][k] = sum_m F[l][m] Y[k][m] per class, azimuthal unfold: S in the layout of the row.
+// The K order of an MFMA is free, so lane groups take k = 4 l4 + s at step s: its four values are
+// one 16-byte LDS access.
+//
+// LDS: a mode's plane is 8 cells x 64 bytes, planes 576 bytes apart, 16-byte granule g of
+// (m, cell) at g ^ swz(m, cell): 16 consecutive lanes of the 16-byte accesses of 1 and 2 and the
+// 4-byte reads of 3 fall on different banks.  Two buffers, tiles alternating: a wave that is a
+// tile ahead writes the buffer that nobody reads any more.
+#pragma once
+
+#include <cstddef>
+
+#include "sn_step_kernels.h"
+
+namespace snrt {
+namespace az {
+
+constexpr int kCells = 8;                    // cells of a block's tile, one wave each
+constexpr int kPlane = 144;                  // floats of a mode's plane (576 bytes)
+constexpr int kClass = 16 * kPlane;          // floats of a class
+
+__device__ __forceinline__ int swz(int m, int cell) {
+    return ((m >> 2) ^ (cell >> 2) ^ ((m & 1) << 1)) & 3;
+}
+
+__device__ __forceinline__ f32x4 mfma4(const f32x4& a, const f32x4& b, f32x4 acc) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s], b[s], acc, 0, 0, 0);
+    return acc;
+}
+
+// How a row is cut: AZ azimuthal classes, MU polar halves, WPC waves per cell, SEG segments per
+// wave, ITEMS mode pairs per wave in stage 2 (each with MU matrices).
+template <int AZ_, int MU_>
+struct Shape {
+    static constexpr int AZ = AZ_, MU = MU_;
+    static constexpr int WPC = AZ * MU == 4 ? 2 : 1;
+    static constexpr int SEG = AZ * MU / WPC;
+    static constexpr int WAVES = kCells * WPC;
+    static constexpr int THREADS = WAVES * kWave;
+    static constexpr int ITEMS = AZ * 8 / WAVES;
+    static constexpr int LDS = AZ * MU * kClass;     // floats of one buffer
+    // class and polar half of segment i
+    static constexpr int az(int i) { return i % AZ; }
+};
+
+// The place of a wave's lane: its cell of the tile; for the row in memory order the byte offset
+// (off) and LDS granule (mem) of its four ordinates per segment and whether they exist (lanes
+// past the end repeat the last ones and store nothing); for the row in matrix order the LDS
+// granule (mat) of each segment and whether the lane's polar slot exists (valid).
+template <typename P>
+struct Lane {
+    int wave, lane, l4, kk, cell, mu0;
+    bool valid, exists[P::SEG];
+    uint32_t off[P::SEG];
+    int mem[P::SEG], mat[P::SEG];
+    __device__ __forceinline__ Lane(int np) {
+        wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        lane = threadIdx.x & (kWave - 1);
+        kk = lane & 15;
+        l4 = lane >> 4;
+        cell = wave & 7;
+        mu0 = P::WPC == 2 ? wave >> 3 : 0;
+        const int h = P::MU == 2 ? np / 2 : np;
+        const int rows = P::WPC == 2 ? h : np, k0 = mu0 * h;      // polar rows of this wave
+        constexpr int na = 16 * P::AZ;
+        valid = kk < h;
+        const int k = valid ? kk : h - 1;
+#pragma unroll
+        for (int i = 0; i < P::SEG; ++i) {
+            int e = i * 256 + 4 * lane;
+            exists[i] = e < rows * na;
+            e = exists[i] ? e : rows * na - 4;
+            off[i] = 4u * (uint32_t)(k0 * na + e);
+            mem[i] = granule(e / na, (e % na) / 4);
+            const int mu = mu0 + i / P::AZ;
+            mat[i] = granule((mu ? np - 1 - k : k) - k0, 4 * P::az(i) + l4);
+        }
+    }
+    // 16-byte granule g of a row of 4 AZ granules: xor-ed so that 16 rows at one g, and 16
+    // granules in memory order, each cover the banks once
+    __device__ __forceinline__ static int granule(int r, int g) {
+        constexpr int G = 4 * P::AZ;
+        return r * G + (g ^ ((r >> (P::AZ == 2 ? 1 : 2)) & (G - 1)));
+    }
+};
+
+// Between the two orders through the wave's LDS corner (LDS accesses of one wave stay in order).
+template <typename P>
+__device__ __forceinline__ void to_matrix_order(f32x4 (&x)[P::SEG], const f32x4 (&p)[P::SEG],
+                                                const Lane<P>& ln, f32x4* corner) {
+#pragma unroll
+    for (int i = 0; i < P::SEG; ++i)
+        if (ln.exists[i]) corner[ln.mem[i]] = p[i];
+#pragma unroll
+    for (int i = 0; i < P::SEG; ++i) x[i] = corner[ln.mat[i]];
+}
+template <typename P>
+__device__ __forceinline__ void to_memory_order(f32x4 (&x)[P::SEG], const Lane<P>& ln,
+                                                f32x4* corner) {
+    if (ln.valid) {
+#pragma unroll
+        for (int i = 0; i < P::SEG; ++i) corner[ln.mat[i]] = x[i];
+    }
+#pragma unroll
+    for (int i = 0; i < P::SEG; ++i) x[i] = corner[ln.mem[i]];
+}
+
+__device__ __forceinline__ f32x4 load4(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
+}
+
+__device__ __forceinline__ void store4(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff,
+                                       const f32x4& v) {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4, v), r, voff, soff,
+                                           kAuxStream);
+}
+
+// Azimuthal fold of a wave's segments and its inverse: the same sums.
+template <typename P>
+__device__ __forceinline__ void fold(f32x4 (&x)[P::SEG]) {
+    if constexpr (P::AZ == 2) {
+#pragma unroll
+        for (int i = 0; i < P::SEG; i += 2) {
+            const f32x4 a = x[i], b = x[i + 1];
+            x[i] = a + b;
+            x[i + 1] = a - b;
+        }
+    }
+}
+
+// The operands a wave keeps: the azimuthal transforms and its mode pairs' polar matrices.
+template <typename P>
+struct Ops {
+    f32x4 f1[P::AZ], f3[P::AZ];
+    f32x4 d[P::ITEMS][P::MU];
+    __device__ __forceinline__ Ops(const AzOperand& op, const float* __restrict__ mats,
+                                   const Lane<P>& ln) {
+#pragma unroll
+        for (int a = 0; a < P::AZ; ++a) {
+            f1[a] = reinterpret_cast<const f32x4*>(op.f1)[a * kWave + ln.lane];
+            f3[a] = reinterpret_cast<const f32x4*>(op.f3)[a * kWave + ln.lane];
+        }
+        load(d, mats, ln);
+    }
+    // mats: [class = mu * AZ + az][pair][which][lane] of float4
+    __device__ __forceinline__ static void load(f32x4 (&d)[P::ITEMS][P::MU],
+                                                const float* __restrict__ mats,
+                                                const Lane<P>& ln) {
+#pragma unroll
+        for (int i = 0; i < P::ITEMS; ++i)
+#pragma unroll
+            for (int mu = 0; mu < P::MU; ++mu)
+                d[i][mu] = reinterpret_cast<const f32x4*>(
+                    mats)[(((mu * P::AZ + az_of(ln, i)) * 8 + (ln.wave & 7)) * 2) * kWave + ln.lane];
+    }
+    __device__ __forceinline__ static int az_of(const Lane<P>& ln, int i) {
+        return P::WPC == 2 ? ln.wave >> 3 : i;
+    }
+};
+
+// Stage 1: the row segments x of this wave into LDS as modes.
+template <typename P>
+__device__ __forceinline__ void to_modes(f32x4 (&x)[P::SEG], const Ops<P>& op, const Lane<P>& ln,
+                                         float* __restrict__ lds) {
+    fold<P>(x);
+    float* at = lds + ln.kk * kPlane + ln.cell * 16 + ((ln.l4 ^ swz(ln.kk, ln.cell)) << 2);
+#pragma unroll
+    for (int i = 0; i < P::SEG; ++i)
+        *reinterpret_cast<f32x4*>(at + (P::az(i) * P::MU + ln.mu0 + i / P::AZ) * kClass) =
+            mfma4(x[i], op.f1[P::az(i)], f32x4{0, 0, 0, 0});
+}
+
+// y = A x for a pair of modes.  The pair of modes 0 and na / 2 (j = 0 of class 0) has a matrix for
+// each: second (LDS) is the other one's, null elsewhere.
+__device__ __forceinline__ f32x4 apply_pair(const f32x4& d, const f32x4* second, const f32x4& x,
+                                            int lane) {
+    const f32x4 zero{0, 0, 0, 0};
+    if (!second) return mfma4(d, x, zero);
+    const bool hi = (lane & 8) != 0;
+    const f32x4 y = mfma4(d, hi ? zero : x, zero);
+    return mfma4(second[lane], hi ? x : zero, y);
+}
+
+// Stage 2: f(item, polar class, column values) on this wave's mode pairs, in place.
+template <typename P, typename F>
+__device__ __forceinline__ void on_modes(const Lane<P>& ln, float* __restrict__ lds, F&& f) {
+    const int cell = ln.lane & 7, m = 2 * (ln.wave & 7) + ((ln.lane >> 3) & 1);
+    float* at = lds + m * kPlane + cell * 16 + ((ln.l4 ^ swz(m, cell)) << 2);
+#pragma unroll
+    for (int i = 0; i < P::ITEMS; ++i) {
+        f32x4* s = reinterpret_cast<f32x4*>(at + Ops<P>::az_of(ln, i) * P::MU * kClass);
+        if constexpr (P::MU == 1) {
+            *s = f(i, 0, *s);
+        } else {
+            f32x4* t = s + kClass / 4;
+            const f32x4 a = *s, b = *t;
+            const f32x4 u = f(i, 0, a + b), v = f(i, 1, a - b);
+            *s = u + v;
+            *t = u - v;
+        }
+    }
+}
+
+// The second matrices of the pair of modes 0 and na / 2 into LDS, one per polar class, and where a
+// wave finds them (null if its item is another pair).  In LDS rather than read from memory at use:
+// loads return in order, so a wait on one in the loop would also wait for the rows in flight.
+template <typename P>
+__device__ __forceinline__ void load_second(const float* __restrict__ mats, f32x4* second) {
+    if (threadIdx.x < kWave * P::MU)
+        second[threadIdx.x] = reinterpret_cast<const f32x4*>(
+            mats)[((threadIdx.x >> 6) * P::AZ * 8 * 2 + 1) * kWave + (threadIdx.x & (kWave - 1))];
+}
+template <typename P>
+__device__ __forceinline__ const f32x4* second_of(const f32x4* second, const Lane<P>& ln, int i,
+                                                  int mu) {
+    return (ln.wave & 7) == 0 && Ops<P>::az_of(ln, i) == 0 ? second + mu * kWave : nullptr;
+}
+
+// Stage 3: the modes of this wave's segments back to azimuths.
+template <typename P>
+__device__ __forceinline__ void from_modes(f32x4 (&s)[P::SEG], const Ops<P>& op, const Lane<P>& ln,
+                                           const float* __restrict__ lds) {
+    const float* at = lds + ln.l4 * kPlane + ln.cell * 16 + (ln.kk & 3);
+    const int g = (ln.kk >> 2) ^ swz(ln.l4, ln.cell);        // mode 4 s + l4: granule g ^ s
+#pragma unroll
+    for (int i = 0; i < P::SEG; ++i) {
+        const int cls = P::az(i) * P::MU + ln.mu0 + i / P::AZ;
+        f32x4 y;
+#pragma unroll
+        for (int st = 0; st < 4; ++st) y[st] = at[cls * kClass + st * 4 * kPlane + ((g ^ st) << 2)];
+        s[i] = mfma4(op.f3[P::az(i)], y, f32x4{0, 0, 0, 0});
+    }
+    fold<P>(s);
+}
+
+// Block barrier for LDS traffic alone: loads in flight stay in flight across it.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// The tiles of a block: XCD x owns a contiguous range of tiles (cells in Hilbert order) and its
+// blocks sweep it together, as in the step kernel.
+struct Tiles {
+    int32_t t, end, stride;
+    __device__ __forceinline__ Tiles(int32_t ntiles) {
+        const int32_t per = (ntiles + kNumXcd - 1) / kNumXcd;
+        const int32_t x = (int32_t)(blockIdx.x % kNumXcd);
+        t = x * per + (int32_t)(blockIdx.x / kNumXcd);
+        end = x * per + per < ntiles ? x * per + per : ntiles;
+        stride = (int32_t)(gridDim.x / kNumXcd);
+    }
+};
+
+// The cell's data besides its rows.  All of it comes through vector loads, one word per lane, and
+// is read back with readlane: the words of the geometry record (rec, two tiles ahead, for the
+// neighbour list), then one tile ahead (mat) in lanes 0..3 sigma_t, sigma_s, source and 1/rho of
+// the cell, in lanes 4.. the neighbours' 1/rho, in lanes 8, 9 the dose to add to.  Scalar loads
+// would share their wait counter with the LDS exchange, which would then wait for memory.
+struct CellWords {
+    const float* base;
+    bool nbr, dose;
+    __device__ __forceinline__ CellWords(int lane, const StepArgs32& a, const float* src_arr,
+                                         const double* dose_) {
+        nbr = lane >= 4 && lane < 8 && a.inv_rho;
+        dose = (lane == 8 || lane == 9) && dose_;
+        base = lane == 1 ? a.sigma_s : lane == 2 ? src_arr : a.sigma_t;
+        if ((lane == 3 && a.inv_rho) || nbr) base = a.inv_rho;
+        if (dose) base = reinterpret_cast<const float*>(dose_) + (lane - 8);
+    }
+    __device__ __forceinline__ static float record(const CellGeom32* __restrict__ geom, int32_t c,
+                                                   int lane) {
+        return reinterpret_cast<const float*>(geom + c)[lane & 15];
+    }
+    template <int MF>
+    __device__ __forceinline__ float material(float rec, int32_t c, int lane) const {
+        int32_t i = c;
+        if (nbr) {
+#pragma unroll
+            for (int f = 0; f < MF; ++f) {
+                const int32_t j = word(rec, f);
+                if (lane == 4 + f && j >= 0) i = j;
+            }
+        }
+        return base[dose ? 2 * (int64_t)i : (int64_t)i];
+    }
+    __device__ __forceinline__ static int32_t word(float r, int l) {
+        return __builtin_amdgcn_readlane(__builtin_bit_cast(int32_t, r), l);
+    }
+    __device__ __forceinline__ static float value(float r, int l) {
+        return __builtin_bit_cast(float, word(r, l));
+    }
+};
+
+// The update's coefficients, formed as fwd_load_stage forms them.
+template <int MF>
+struct CellData {
+    float ghost[MF], nx[MF], ny[MF];
+    float irho, cabs, cflux, cscat, srcv;
+    bool scaled;      // some ghost scale may differ from 1 (densities, boundary faces)
+    template <bool RHO>
+    __device__ __forceinline__ void form(float rec, float mat, const StepArgs32& a,
+                                         const FwdCtx<float>& x) {
+        using W = CellWords;
+        irho = RHO ? W::value(mat, 3) : 1.0f;
+        const float bscale = x.dirichlet ? x.inflow_scale : (x.neumann ? irho : 0.0f);
+        scaled = RHO;
+#pragma unroll
+        for (int f = 0; f < MF; ++f) {
+            scaled |= W::word(rec, f) < 0;
+            ghost[f] = W::word(rec, f) < 0 ? bscale : RHO ? W::value(mat, 4 + f) : 1.0f;
+            nx[f] = W::value(rec, 4 + 2 * f);
+            ny[f] = W::value(rec, 5 + 2 * f);
+        }
+        cabs = a.dt * a.alpha_t * W::value(mat, 0);
+        cflux = a.dt * W::value(rec, 12);
+        cscat = a.dt * a.alpha_s * W::value(mat, 1);
+        srcv = W::value(mat, 2);
+    }
+};
+static_assert(offsetof(CellGeom32, n) == 16 && offsetof(CellGeom32, inv_area) == 48, "record words");
+
+// The ordinate table's two direction rows into LDS (padded to whole segments).
+template <typename P>
+__device__ __forceinline__ void load_table(const float* __restrict__ tab, int nq, f32x4* dst) {
+    constexpr int N = P::AZ * P::MU * kWave;
+    for (int i = threadIdx.x; i < nq / 4; i += P::THREADS) {
+        dst[i] = reinterpret_cast<const f32x4*>(tab)[i];
+        dst[N + i] = reinterpret_cast<const f32x4*>(tab + nq)[i];
+    }
+}
+
+// Sum of a double over the wave, the same in every lane: DPP swaps inside rows of 16, the row
+// sums through scalars (no LDS traffic, which the exchange needs).
+template <int CTRL>
+__device__ __forceinline__ double dpp_partner64(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xF, 0xF, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, false);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double lane64(double v, int l) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    return __builtin_bit_cast(
+        double, ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(b >> 32), l) << 32) |
+                    (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, l));
+}
+__device__ __forceinline__ double wave_sum64(double v) {
+    v += dpp_partner64<0xB1>(v);
+    v += dpp_partner64<0x4E>(v);
+    v += dpp_partner64<0x141>(v);
+    v += dpp_partner64<0x140>(v);
+    return (lane64(v, 0) + lane64(v, 16)) + (lane64(v, 32) + lane64(v, 48));
+}
+
+// The upwind candidate across a face to neighbour j of cell c (the step kernel's branch-free rule).
+__device__ __forceinline__ f32x4 load_face(int32_t j, int32_t c, uint32_t voff,
+                                           const FwdCtx<float>& x) {
+    const bool bnd = j < 0;
+    const int32_t bidx = x.dirichlet ? -1 - j : c;
+    return load4(bnd && x.dirichlet ? x.inflow : x.psi, voff,
+                 (uint32_t)(bnd ? bidx : j) * x.row_bytes);
+}
+
+// The upwind sum over the faces for one segment, in the explicit FMAs of fwd_compute; up: the
+// upwind candidates times their ghost scales.
+template <int MF, bool RHO>
+__device__ __forceinline__ f32x4 flux4(const f32x4& p, float irho, const float (&nx)[MF],
+                                       const float (&ny)[MF], const f32x4 (&up)[MF],
+                                       const f32x4& ox, const f32x4& oy) {
+    f32x4 acc{0, 0, 0, 0};
+#pragma unroll
+    for (int f = 0; f < MF; ++f)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const float u = RHO ? p[v] * irho : p[v];
+            const float s = __builtin_fmaf(nx[f], ox[v], ny[f] * oy[v]);
+            acc[v] = __builtin_fmaf(s, s > 0.0f ? u : up[f][v], acc[v]);
+        }
+    return acc;
+}
+
+__device__ __forceinline__ FwdCtx<float> make_ctx(const StepArgs32& a, const float* psi_in,
+                                                  float* psi_out, int64_t nc, int32_t nq,
+                                                  uint32_t nbf) {
+    FwdCtx<float> cx;
+    cx.row_bytes = (uint32_t)nq * (uint32_t)sizeof(float);
+    const uint32_t state_bytes = (uint32_t)nc * cx.row_bytes;
+    cx.psi = make_rsrc(psi_in, state_bytes);
+    cx.out = make_rsrc(psi_out, state_bytes);
+    cx.inflow = make_rsrc(a.inflow ? a.inflow : psi_in, a.inflow ? nbf * cx.row_bytes : 0u);
+    cx.S = make_rsrc(psi_in, 0u);
+    cx.src_arr = a.source ? a.source : a.sigma_t;
+    cx.src_mul = a.source ? a.dt : 0.0f;
+    cx.inflow_scale = a.inflow_scale;
+    cx.dirichlet = a.inflow != nullptr && !a.neumann;
+    cx.neumann = a.neumann != 0;
+    cx.dpart = nullptr;
+    return cx;
+}
+
+// A wave's cell in tile t, clamped to the mesh (a clamped cell is computed and not stored).
+struct Cell {
+    int32_t c;
+    bool real;
+    __device__ __forceinline__ Cell(int32_t t, int cell, int64_t nc) {
+        const int64_t c0 = (int64_t)t * kCells + cell;
+        real = c0 < nc;
+        c = uniform_cell((int32_t)(real ? c0 : nc - 1));
+    }
+};
+
+// ------------------------------------------------------------------------------ the product
+
+// S = Psi B (or Lambda B^T with the transposed matrices): [nc][nq] -> [nc][nq].
+template <typename P>
+__global__ __launch_bounds__(P::THREADS, 4) void k_az_product(AzOperand opd,
+                                                              const float* __restrict__ mats,
+                                                              const float* __restrict__ in,
+                                                              float* __restrict__ out, int64_t nc)
+{
+    __shared__ __attribute__((aligned(16))) float lds[2][P::LDS];
+    __shared__ f32x4 second[P::MU * kWave];
+    __shared__ f32x4 rows[P::WAVES][P::SEG * kWave];
+    const Lane<P> ln(opd.np);
+    const Ops<P> op(opd, mats, ln);
+    load_second<P>(mats, second);
+    const uint32_t row_bytes = (uint32_t)(opd.np * opd.na) * 4u;
+    const auto rin = make_rsrc(in, (uint32_t)nc * row_bytes);
+    const auto rout = make_rsrc(out, (uint32_t)nc * row_bytes);
+    Tiles tl((int32_t)((nc + kCells - 1) / kCells));
+    if (tl.t >= tl.end) return;
+    f32x4 nx[P::SEG];
+    auto fetch = [&](int32_t t) {
+        const Cell c(t < tl.end ? t : tl.end - 1, ln.cell, nc);
+#pragma unroll
+        for (int i = 0; i < P::SEG; ++i) nx[i] = load4(rin, ln.off[i], (uint32_t)c.c * row_bytes);
+    };
+    fetch(tl.t);
+    for (int b = 0; tl.t < tl.end; tl.t += tl.stride, b ^= 1) {
+        const Cell c(tl.t, ln.cell, nc);
+        f32x4 x[P::SEG];
+        to_matrix_order<P>(x, nx, ln, rows[ln.wave]);
+        fetch(tl.t + tl.stride);
+        to_modes<P>(x, op, ln, lds[b]);
+        lds_barrier();
+        on_modes<P>(ln, lds[b], [&](int i, int mu, const f32x4& v) {
+            return apply_pair(op.d[i][mu], second_of<P>(second, ln, i, mu), v, ln.lane);
+        });
+        lds_barrier();
+        from_modes<P>(x, op, ln, lds[b]);
+        to_memory_order<P>(x, ln, rows[ln.wave]);
+#pragma unroll
+        for (int i = 0; i < P::SEG; ++i)
+            if (c.real && ln.exists[i]) store4(rout, ln.off[i], (uint32_t)c.c * row_bytes, x[i]);
+    }
+}
+
+// ------------------------------------------------------------------------ the explicit step
+
+// The explicit dense step (and its dose) in one pass over the state: the wave's own row feeds the
+// modes and stays in registers for the update.  The next tile's own row is fetched at the start
+// of a tile, its neighbour rows segment by segment into the registers the update has just used
+// (in flight during the next tile's exchange), cell data one tile ahead, neighbour lists two.  The update is fwd_compute's, in the same
+// explicit FMAs: the state equals the product followed by the step kernel bit for bit.  A wave that
+// is in the exchange has priority over one that updates, whose vector work fills the gaps
+// (100 352 x 1024: 0.250 -> 0.231 ms; 299 538 x 512: 0.368 -> 0.350).
+template <typename P, int MF, bool RHO, bool DOSE>
+__global__ __launch_bounds__(P::THREADS, 4) void k_az_step(AzOperand opd, StepEpi se, double coeff,
+                                                           double* __restrict__ dose)
+{
+    constexpr int SEG = P::SEG;
+    __shared__ __attribute__((aligned(16))) float lds[2][P::LDS];
+    __shared__ double dsum[2][DOSE && P::WPC == 2 ? kCells : 1];
+    __shared__ f32x4 second[P::MU * kWave];
+    __shared__ f32x4 dirs[2 * P::AZ * P::MU * kWave];
+    __shared__ f32x4 rows[P::WAVES][SEG * kWave];
+    const Lane<P> ln(opd.np);
+    const Ops<P> op(opd, opd.fwd, ln);
+    load_second<P>(opd.fwd, second);
+    load_table<P>(se.tab, se.nq, dirs);
+    const FwdCtx<float> cx = make_ctx(se.a, se.psi_in, se.psi_out, se.nc, se.nq, se.nbf);
+    const CellWords words(ln.lane, se.a, cx.src_arr, DOSE ? dose : nullptr);
+    double wd[DOSE ? SEG : 1];
+    if constexpr (DOSE) {
+#pragma unroll
+        for (int i = 0; i < SEG; ++i)
+            wd[i] = ln.exists[i] ? se.wq[ln.off[i] / 4] : 0.0;   // one weight per polar node
+    }
+    Tiles tl((int32_t)((se.nc + kCells - 1) / kCells));
+    if (tl.t >= tl.end) return;
+    auto cell_of = [&](int32_t t) { return Cell(t < tl.end ? t : tl.end - 1, ln.cell, se.nc); };
+    auto record = [&](int32_t t) { return CellWords::record(se.geom, cell_of(t).c, ln.lane); };
+    auto own = [&](f32x4 (&p)[SEG], int32_t t) {
+        const uint32_t row = (uint32_t)cell_of(t).c * cx.row_bytes;
+#pragma unroll
+        for (int i = 0; i < SEG; ++i) p[i] = load4(cx.psi, ln.off[i], row);
+    };
+    f32x4 p[SEG], pn[SEG], up[SEG][MF];
+    float rec = record(tl.t), mat = words.template material<MF>(rec, cell_of(tl.t).c, ln.lane);
+    own(p, tl.t);
+#pragma unroll
+    for (int i = 0; i < SEG; ++i)
+#pragma unroll
+        for (int f = 0; f < MF; ++f)
+            up[i][f] = load_face(CellWords::word(rec, f), cell_of(tl.t).c, ln.off[i], cx);
+    float recn = record(tl.t + tl.stride);
+    __syncthreads();                       // second, dirs
+    for (int b = 0;; b ^= 1) {
+        const Cell c = cell_of(tl.t), cn = cell_of(tl.t + tl.stride);
+        float* buf = lds[b];
+        f32x4 x[SEG];
+        __builtin_amdgcn_s_setprio(2);
+        to_matrix_order<P>(x, p, ln, rows[ln.wave]);
+        to_modes<P>(x, op, ln, buf);
+        const float matn = words.template material<MF>(recn, cn.c, ln.lane);
+        own(pn, tl.t + tl.stride);
+        const float recn2 = record(tl.t + 2 * tl.stride);
+        lds_barrier();
+        on_modes<P>(ln, buf, [&](int i, int mu, const f32x4& v) {
+            return apply_pair(op.d[i][mu], second_of<P>(second, ln, i, mu), v, ln.lane);
+        });
+        double sd = 0.0;
+        if constexpr (DOSE) {
+#pragma unroll
+            for (int i = 0; i < SEG; ++i)
+                sd += wd[i] * (((double)p[i][0] + (double)p[i][1]) +
+                               ((double)p[i][2] + (double)p[i][3]));
+            sd = wave_sum64(sd);
+            if (P::WPC == 2 && ln.mu0 == 1 && ln.lane == 0) dsum[b][ln.cell] = sd;
+        }
+        lds_barrier();
+        from_modes<P>(x, op, ln, buf);
+        to_memory_order<P>(x, ln, rows[ln.wave]);
+        __builtin_amdgcn_s_setprio(0);
+        CellData<MF> cd;
+        cd.template form<RHO>(rec, mat, se.a, cx);
+        if constexpr (DOSE) {
+            const uint64_t d0 = ((uint64_t)(uint32_t)CellWords::word(mat, 9) << 32) |
+                                (uint32_t)CellWords::word(mat, 8);
+            if (ln.mu0 == 0 && ln.lane == 0 && c.real) {
+                if (P::WPC == 2) sd += dsum[b][ln.cell];
+                dose[c.c] = __builtin_bit_cast(double, d0) +
+                            coeff * (RHO ? (double)cd.irho : 1.0) * sd;
+            }
+        }
+        const uint32_t row = (uint32_t)c.c * cx.row_bytes;
+#pragma unroll
+        for (int i = 0; i < SEG; ++i) {
+            const f32x4* dir = dirs + ln.off[i] / 16;
+            const f32x4 ox = dir[0], oy = dir[P::AZ * P::MU * kWave];
+            if (cd.scaled) {
+#pragma unroll
+                for (int f = 0; f < MF; ++f) up[i][f] *= cd.ghost[f];
+            }
+            const f32x4 acc = flux4<MF, RHO>(p[i], cd.irho, cd.nx, cd.ny, up[i], ox, oy);
+            f32x4 o;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float e =
+                    __builtin_fmaf(-cd.cflux, acc[v], __builtin_fmaf(-p[i][v], cd.cabs, p[i][v]));
+                o[v] = __builtin_fmaf(cx.src_mul, cd.srcv, __builtin_fmaf(cd.cscat, x[i][v], e));
+            }
+            if (c.real && ln.exists[i]) store4(cx.out, ln.off[i], row, o);
+#pragma unroll
+            for (int f = 0; f < MF; ++f)
+                up[i][f] = load_face(CellWords::word(recn, f), cn.c, ln.off[i], cx);
+        }
+        tl.t += tl.stride;
+        if (tl.t >= tl.end) break;
+#pragma unroll
+        for (int i = 0; i < SEG; ++i) p[i] = pn[i];
+        rec = recn;
+        recn = recn2;
+        mat = matn;
+    }
+}
+
+// ---------------------------------------------------------------------- the transposed step
+
+// The transposed dense step in one pass: G = Lambda B^T through the modes (transposed polar
+// matrices), then adj_compute's update in the same explicit FMAs (lam_n equals the product followed
+// by the transposed-step kernel bit for bit).  A wave holds its whole row (or polar half), so the
+// gradient sums finish here: where two waves share a cell, their sums meet in LDS and are added
+// after the next tile's first barrier.
+struct AzAdjoint {
+    const CellGeom32* geom;
+    const float* tab;
+    StepArgs32 a;
+    const float *psi_n, *lam_np1;
+    float* lam_n;
+    int64_t nc;
+    int32_t nq;
+    DoseAdj da;
+};
+
+// Words of a cell for the transposed step: lanes 0..2 sigma_t, sigma_s, 1/rho; 4..7 the
+// neighbours' 1/A; 8.. the gradients to add to; 14, 15 the dose functional's dJ/dD.
+template <typename GT>
+struct AdjWords {
+    const float* base;
+    int stride;
+    bool nbr;
+    __device__ __forceinline__ AdjWords(int lane, const AzAdjoint& e, const GT* g_t, const GT* g_s,
+                                        const GT* g_r) {
+        constexpr int W = sizeof(GT) / 4;
+        base = lane == 1 ? e.a.sigma_s : lane == 2 && e.a.inv_rho ? e.a.inv_rho : e.a.sigma_t;
+        stride = 1;
+        nbr = lane >= 4 && lane < 8;
+        if (nbr) {
+            base = reinterpret_cast<const float*>(e.geom) + 12;
+            stride = 16;
+        }
+        const int i = (lane - 8) / W, w = (lane - 8) % W;
+        const GT* g = i == 0 ? g_t : i == 1 ? g_s : g_r;
+        if (lane >= 8 && i < 3 && g) {
+            base = reinterpret_cast<const float*>(g) + w;
+            stride = W;
+        }
+        if ((lane == 14 || lane == 15) && e.da.g_dose) {
+            base = reinterpret_cast<const float*>(e.da.g_dose) + (lane - 14);
+            stride = 2;
+        }
+    }
+    template <int MF>
+    __device__ __forceinline__ float load(float rec, int32_t c, int lane) const {
+        int32_t i = c;
+        if (nbr) {
+#pragma unroll
+            for (int f = 0; f < MF; ++f) {
+                const int32_t j = CellWords::word(rec, f);
+                if (lane == 4 + f && j >= 0) i = j;
+            }
+        }
+        return base[(int64_t)i * stride];
+    }
+    __device__ __forceinline__ static GT gradient(float mat, int i) {
+        if constexpr (sizeof(GT) == 8)
+            return __builtin_bit_cast(
+                double, ((uint64_t)(uint32_t)CellWords::word(mat, 9 + 2 * i) << 32) |
+                            (uint32_t)CellWords::word(mat, 8 + 2 * i));
+        else
+            return CellWords::value(mat, 8 + i);
+    }
+};
+
+template <typename P, int MF, typename GT, bool DA>
+__global__ __launch_bounds__(P::THREADS, 4) void k_az_adjoint(AzOperand opd, AzAdjoint e,
+                                                              GT* __restrict__ g_t,
+                                                              GT* __restrict__ g_s,
+                                                              GT* __restrict__ g_r)
+{
+    constexpr int SEG = P::SEG;
+    __shared__ __attribute__((aligned(16))) float lds[2][P::LDS];
+    __shared__ f32x4 second[P::MU * kWave];
+    __shared__ f32x4 dirs[2 * P::AZ * P::MU * kWave];
+    __shared__ f32x4 rows[P::WAVES][SEG * kWave];
+    __shared__ float gsum[2][P::WPC == 2 ? P::WAVES : 1][4];
+    const Lane<P> ln(opd.np);
+    const Ops<P> op(opd, opd.adj, ln);
+    load_second<P>(opd.adj, second);
+    load_table<P>(e.tab, e.nq, dirs);
+    const StepArgs32& a = e.a;
+    const uint32_t row_bytes = (uint32_t)e.nq * 4u, state_bytes = (uint32_t)e.nc * row_bytes;
+    const auto rlam = make_rsrc(e.lam_np1, state_bytes);
+    const auto rpsi = make_rsrc(e.psi_n, state_bytes);
+    const auto rout = make_rsrc(e.lam_n, state_bytes);
+    const AdjWords<GT> words(ln.lane, e, g_t, g_s, g_r);
+    double wd[DA ? SEG : 1];
+    if constexpr (DA) {
+#pragma unroll
+        for (int i = 0; i < SEG; ++i) wd[i] = e.da.w[ln.off[i] / 4];      // one per polar node
+    }
+    Tiles tl((int32_t)((e.nc + kCells - 1) / kCells));
+    if (tl.t >= tl.end) return;
+    auto cell_of = [&](int32_t t) { return Cell(t < tl.end ? t : tl.end - 1, ln.cell, e.nc); };
+    auto record = [&](int32_t t) { return CellWords::record(e.geom, cell_of(t).c, ln.lane); };
+    auto own = [&](f32x4 (&p)[SEG], int32_t t) {
+        const uint32_t row = (uint32_t)cell_of(t).c * row_bytes;
+#pragma unroll
+        for (int i = 0; i < SEG; ++i) p[i] = load4(rlam, ln.off[i], row);
+    };
+    // the rows of segment i that the update alone needs: psi and the neighbours' lambda (a
+    // boundary face reads the cell's own row, with weight 0)
+    f32x4 l[SEG], lnx[SEG], p[SEG], nl[SEG][MF];
+    auto others = [&](int i, float rec, int32_t c) {
+        p[i] = load4(rpsi, ln.off[i], (uint32_t)c * row_bytes);
+#pragma unroll
+        for (int f = 0; f < MF; ++f) {
+            const int32_t j = CellWords::word(rec, f);
+            nl[i][f] = load4(rlam, ln.off[i], (uint32_t)(j >= 0 ? j : c) * row_bytes);
+        }
+    };
+    auto add_gradients = [&](float mat, int32_t c, float pt, float ps, float pr, float irho) {
+        if (g_t) g_t[c] = AdjWords<GT>::gradient(mat, 0) + (GT)(-a.dt * a.alpha_t * pt);
+        if (g_s) g_s[c] = AdjWords<GT>::gradient(mat, 1) + (GT)(a.dt * a.alpha_s * ps);
+        if (g_r) g_r[c] = AdjWords<GT>::gradient(mat, 2) + (GT)(a.dt * irho * irho * pr);
+    };
+    auto shared_gradients = [&](float mat, const Cell& c, int b) {
+        if (ln.mu0 == 0 && c.real) {
+            const float *u = gsum[b][ln.cell], *v = gsum[b][P::WPC == 2 ? ln.cell + 8 : 0];
+            const float irho = a.inv_rho ? CellWords::value(mat, 2) : 1.0f;
+            const float pt = u[0] + v[0], ps = u[1] + v[1], pr = u[2] + v[2];
+            if (ln.lane == 0) add_gradients(mat, c.c, pt, ps, pr, irho);
+        }
+    };
+    float rec = record(tl.t), mat = words.template load<MF>(rec, cell_of(tl.t).c, ln.lane);
+    own(l, tl.t);
+#pragma unroll
+    for (int i = 0; i < SEG; ++i) others(i, rec, cell_of(tl.t).c);
+    float recn = record(tl.t + tl.stride), matp = mat;
+    Cell cp = cell_of(tl.t);
+    bool first = true;
+    __syncthreads();                       // second, dirs
+    int b = 0;
+    for (;; b ^= 1) {
+        const Cell c = cell_of(tl.t), cn = cell_of(tl.t + tl.stride);
+        float* buf = lds[b];
+        f32x4 x[SEG];
+        __builtin_amdgcn_s_setprio(2);
+        to_matrix_order<P>(x, l, ln, rows[ln.wave]);
+        to_modes<P>(x, op, ln, buf);
+        const float matn = words.template load<MF>(recn, cn.c, ln.lane);
+        own(lnx, tl.t + tl.stride);
+        const float recn2 = record(tl.t + 2 * tl.stride);
+        lds_barrier();
+        if (P::WPC == 2 && !first) shared_gradients(matp, cp, b ^ 1);
+        on_modes<P>(ln, buf, [&](int i, int mu, const f32x4& v) {
+            return apply_pair(op.d[i][mu], second_of<P>(second, ln, i, mu), v, ln.lane);
+        });
+        lds_barrier();
+        from_modes<P>(x, op, ln, buf);
+        to_memory_order<P>(x, ln, rows[ln.wave]);
+        __builtin_amdgcn_s_setprio(0);
+        using W = CellWords;
+        const float ia = W::value(rec, 12), irho = a.inv_rho ? W::value(mat, 2) : 1.0f;
+        const float cabs = a.dt * a.alpha_t * W::value(mat, 0);
+        const float cscat = a.dt * a.alpha_s * W::value(mat, 1), cstream = a.dt * irho;
+        float ian[MF], nx[MF], ny[MF];
+        bool all_signs[MF];
+#pragma unroll
+        for (int f = 0; f < MF; ++f) {
+            const bool bnd = W::word(rec, f) < 0;
+            ian[f] = bnd ? 0.0f : W::value(mat, 4 + f);
+            all_signs[f] = bnd && a.neumann;
+            nx[f] = W::value(rec, 4 + 2 * f);
+            ny[f] = W::value(rec, 5 + 2 * f);
+        }
+        double gd = 0.0;
+        if constexpr (DA) {
+            const uint64_t g = ((uint64_t)(uint32_t)W::word(mat, 15) << 32) | (uint32_t)W::word(mat, 14);
+            gd = e.da.coeff * (a.inv_rho ? (double)irho : 1.0) * __builtin_bit_cast(double, g);
+        }
+        float pt = 0.0f, ps = 0.0f, pr = 0.0f;
+#pragma unroll
+        for (int i = 0; i < SEG; ++i) {
+            const f32x4 ox = dirs[ln.off[i] / 16], oy = dirs[ln.off[i] / 16 + P::AZ * P::MU * kWave];
+            f32x4 o;
+            float t0 = 0.0f, s0 = 0.0f, r0 = 0.0f;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                float xs = 0.0f;
+#pragma unroll
+                for (int f = 0; f < MF; ++f) {
+                    const float s = __builtin_fmaf(nx[f], ox[v], ny[f] * oy[v]);
+                    const float dd = __builtin_fmaf(-nl[i][f][v], ian[f], l[i][v] * ia);
+                    xs = (s > 0.0f || all_signs[f]) ? __builtin_fmaf(s, dd, xs) : xs;
+                }
+                const float lv = l[i][v], g = x[i][v];
+                o[v] = __builtin_fmaf(cscat, g,
+                                      __builtin_fmaf(-cstream, xs, __builtin_fmaf(-lv, cabs, lv)));
+                t0 = __builtin_fmaf(lv, p[i][v], t0);
+                s0 = __builtin_fmaf(p[i][v], g, s0);
+                r0 = __builtin_fmaf(p[i][v], xs, r0);
+                if constexpr (DA) o[v] = (float)__builtin_fma(gd, wd[i], (double)o[v]);
+            }
+            if (ln.exists[i]) {
+                pt += t0;
+                ps += s0;
+                pr += r0;
+            }
+            if (c.real && ln.exists[i]) store4(rout, ln.off[i], (uint32_t)c.c * row_bytes, o);
+            others(i, recn, cn.c);
+        }
+        pt = wave_sum_dpp(pt);
+        ps = wave_sum_dpp(ps);
+        pr = wave_sum_dpp(pr);
+        if constexpr (P::WPC == 2) {
+            if (ln.lane == 0) {
+                gsum[b][ln.wave][0] = pt;
+                gsum[b][ln.wave][1] = ps;
+                gsum[b][ln.wave][2] = pr;
+            }
+        } else if (ln.lane == 0 && c.real) {
+            add_gradients(mat, c.c, pt, ps, pr, irho);
+        }
+        matp = mat;
+        cp = c;
+        first = false;
+        tl.t += tl.stride;
+        if (tl.t >= tl.end) break;
+#pragma unroll
+        for (int i = 0; i < SEG; ++i) l[i] = lnx[i];
+        rec = recn;
+        recn = recn2;
+        mat = matn;
+    }
+    if constexpr (P::WPC == 2) {
+        lds_barrier();
+        shared_gradients(matp, cp, b);
+    }
+}
+
+// ------------------------------------------------------------------------------ launch shape
+
+// Blocks of a kernel over the mesh's tiles: what the device holds at once (a multiple of the XCD
+// count), never more than there are tiles.
+inline unsigned az_blocks(const snrt_mesh& m, int resident) {
+    const int64_t tiles = (m.nc + kCells - 1) / kCells;
+    const int64_t cap = (int64_t)m.num_cu * (resident > 0 ? resident : 1);
+    const int64_t b = tiles < cap ? tiles : cap;
+    return (unsigned)((b + kNumXcd - 1) / kNumXcd * kNumXcd);
+}
+
+template <typename K>
+int az_resident(K kernel, int threads) {
+    int n = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, threads, 0) != hipSuccess) n = 0;
+    return n;
+}
+
+// f(shape) for the class shape of an operand.
+template <typename F>
+hipError_t by_shape(const AzOperand& op, F&& f) {
+    if (op.na == 32) return op.np > 16 ? f(Shape<2, 2>{}) : f(Shape<2, 1>{});
+    return op.np > 16 ? f(Shape<1, 2>{}) : f(Shape<1, 1>{});
+}
+
+}  // namespace az
+}  // namespace snrt

@@ -54,6 +54,7 @@ const Tune& tune() {
         if (const char* e = std::getenv("SNRT_GEMM_EPILOGUE")) r.gemm_epilogue = std::atoi(e) != 0;
         if (const char* e = std::getenv("SNRT_PN_MFMA")) r.pn_mfma = std::atoi(e) != 0;
         if (const char* e = std::getenv("SNRT_STEP_FUSED")) r.step_fused = std::atoi(e) != 0;
+        if (const char* e = std::getenv("SNRT_AZIMUTH")) r.azimuth = std::atoi(e) != 0;
         return r;
     }();
     return t;
@@ -416,6 +417,8 @@ void snrt_scatter_destroy(snrt_scatter* sc) {
     dev_free(sc->B.msig64);
     dev_free(sc->B.lam32);
     dev_free(sc->B.lam64);
+    dev_free(sc->B.az.base);
+    dev_free(sc->B.az.imp_base);
     delete sc;
 }
 
@@ -529,7 +532,8 @@ snrt_status snrt_scatter_dense(snrt_scatter** out, const snrt_quad* q, const dou
     B.chain = 1;
     snrt_status s = SNRT_OK;
     if ((s = make_operand(B.fwd[0], b64, nq, nq, precision, "snrt_scatter_dense: upload")) != SNRT_OK ||
-        (s = make_operand(B.adj[0], bt64, nq, nq, precision, "snrt_scatter_dense: upload")) != SNRT_OK) {
+        (s = make_operand(B.adj[0], bt64, nq, nq, precision, "snrt_scatter_dense: upload")) != SNRT_OK ||
+        (s = make_azimuth_dense(B, *q, b64)) != SNRT_OK) {
         snrt_scatter_destroy(sc);
         return s;
     }
@@ -615,7 +619,8 @@ snrt_status snrt_scatter_moments(snrt_scatter** out, const snrt_quad* q, int32_t
         (s = make_operand(B.fwd[0], mt, nq, mid, precision, fn)) != SNRT_OK ||
         (s = make_operand(B.fwd[1], ot, mid, nq, precision, fn)) != SNRT_OK ||
         (s = make_operand(B.adj[0], otT, nq, mid, precision, fn)) != SNRT_OK ||
-        (s = make_operand(B.adj[1], mtT, mid, nq, precision, fn)) != SNRT_OK) {
+        (s = make_operand(B.adj[1], mtT, mid, nq, precision, fn)) != SNRT_OK ||
+        (s = make_azimuth_moments(B, *q, sigma_l)) != SNRT_OK) {
         snrt_scatter_destroy(sc);
         return s;
     }
@@ -833,13 +838,27 @@ int32_t* ws_rexp(const DenseB& B, float* after_S, int64_t M) {
     return reinterpret_cast<int32_t*>(after_S + (B.chain == 2 ? (size_t)M * B.mid : 0));
 }
 
+// Whether the FP32 state's scattering product runs through the azimuthal modes: the handle has
+// them, and half of the matrix kernels' 16 polar slots are not padding.  With 8 polar nodes
+// half are: the step then takes what 16 nodes take, which the FP32 product never undercuts (51 842
+// cells, 8 x 32: 53 against 108 us) and the BF16 / FP16 products do on large meshes only, where
+// their 256-row tiles fill the device (51 842 cells, 8 x 32, BF16x3 / x1: 53 against 48 / 37 us;
+// 3 042 cells: 8 against 41 / 33 us; the two lines cross between 32 000 and 45 000 cells).
+bool azimuth_product(const snrt_mesh& m, const DenseB& B) {
+    return B.az.na != 0 && (size_t)m.nc * B.nq * sizeof(float) < (size_t(1) << 32) &&
+           (B.az.np > 8 || B.precision == SNRT_FP32 || m.nc <= 32768);
+}
+
 // S = Psi B (forward) or G = Lambda B^T (adjoint) into the workspace, FP32 state
 // C = A X0 [X1] (forward) or A X0^T-side chain (adjoint); after_S is the workspace past the
 // [M][nq] product: the moments between the two products of the moment form ([M][mid]), then
 // the FP16 row exponents ([M]).
-hipError_t scatter_product32(const snrt_scatter* sc, const float* A, float* C, int64_t M,
+hipError_t scatter_product32(const snrt_mesh& m, const snrt_scatter* sc, const float* A, float* C,
                              bool transpose, float* after_S, hipStream_t st) {
     const DenseB& B = sc->B;
+    const int64_t M = m.nc;
+    if (azimuth_product(m, B))
+        return launch_az_product(m, B.az, transpose ? B.az.adj : B.az.fwd, A, C, st);
     const GemmOperand* ops = transpose ? B.adj : B.fwd;
     int32_t* rexp = after_S ? ws_rexp(B, after_S, M) : nullptr;
     const float* in = A;
@@ -861,6 +880,12 @@ bool step_fusable(const snrt_mesh& m, const snrt_quad& q, const DenseB& B) {
     return last.N == q.nq && last.Np == q.nq && last.K % 32 == 0 && last.hi != nullptr;
 }
 
+StepEpi step_epi(const snrt_mesh& m, const snrt_quad& q, const StepArgs32& a, const float* psi_in,
+                 float* psi_out, double* dpart = nullptr) {
+    return StepEpi{m.geom32, q.tab32, a, psi_in, psi_out, m.nc, q.nq, (uint32_t)m.nbf,
+                   q.tab64 + 2 * (int64_t)q.nq, dpart};
+}
+
 // The fused dense step: the moment form first writes the moments to after_S (as the
 // two-launch step does); the FP16 mode writes the row exponents of the last product's left
 // operand, then one launch forms S tile by tile and updates psi_out from it.
@@ -880,8 +905,7 @@ hipError_t fused_dense_step(const snrt_mesh& m, const snrt_quad& q, const StepAr
                          : B.precision == SNRT_BF16X2 ? 2 : 1;
     if (e == hipSuccess && products == 0) e = launch_row_exp_f16(A, m.nc, op.K, rexp, st);
     if (e != hipSuccess) return e;
-    const StepEpi se{m.geom32, q.tab32, a, psi_in, psi_out, m.nc, q.nq, (uint32_t)m.nbf,
-                     q.tab64 + 2 * (int64_t)q.nq, dpart};
+    const StepEpi se = step_epi(m, q, a, psi_in, psi_out, dpart);
     return launch_gemm_step(A, op.hi, op.lo, m.nc, op.K, op.Np, products, rexp, op.eb, se, st);
 }
 
@@ -971,6 +995,12 @@ snrt_status step_adjoint32_t(const char* fn, const snrt_mesh* m, const snrt_quad
                  SNRT_E_ALIAS, std::string(fn) + ": workspace aliases psi_n");
     hipStream_t st = static_cast<hipStream_t>(stream);
     const float* G = nullptr;
+    if (sc->dense && tune().step_fused && azimuth_product(*m, sc->B)) {
+        const hipError_t e = launch_az_adjoint(*m, *q, sc->B.az, to32(a), psi_n, lam_np1, lam_n,
+                                               g_t, g_s, g_r, da, st);
+        return e == hipSuccess ? SNRT_OK
+                               : hip_fail(e, (std::string(fn) + ": fused transposed step").c_str());
+    }
     if (sc->dense && adjoint_fusable(*m, *q, sc->B)) {
         float* Gbuf = static_cast<float*>(ws);
         const hipError_t e = fused_dense_adjoint(*m, *q, to32(a), sc->B, psi_n, lam_np1, lam_n,
@@ -981,7 +1011,7 @@ snrt_status step_adjoint32_t(const char* fn, const snrt_mesh* m, const snrt_quad
     }
     if (sc->dense) {
         float* Gbuf = static_cast<float*>(ws);
-        hipError_t e = scatter_product32(sc, lam_np1, Gbuf, m->nc, true,
+        hipError_t e = scatter_product32(*m, sc, lam_np1, Gbuf, true,
                                          Gbuf + (size_t)m->nc * q->nq, st);
         if (e != hipSuccess) return hip_fail(e, (std::string(fn) + ": scattering product").c_str());
         G = Gbuf;
@@ -1020,12 +1050,18 @@ snrt_status snrt_step(const snrt_mesh* m, const snrt_quad* q, const snrt_scatter
     if (sc->dense) {
         float* Sbuf = static_cast<float*>(ws);
         float* after = Sbuf + (size_t)m->nc * q->nq;
+        if (tune().step_fused && azimuth_product(*m, sc->B)) {
+            const hipError_t e =
+                launch_az_step(*m, sc->B.az, step_epi(*m, *q, to32(a), psi_in, psi_out), 0.0,
+                               nullptr, st);
+            return e == hipSuccess ? SNRT_OK : hip_fail(e, "snrt_step: fused dense step");
+        }
         if (step_fusable(*m, *q, sc->B)) {
             const hipError_t e = fused_dense_step(*m, *q, to32(a), sc->B, psi_in, psi_out,
                                                   after, st);
             return e == hipSuccess ? SNRT_OK : hip_fail(e, "snrt_step: fused dense step");
         }
-        hipError_t e = scatter_product32(sc, psi_in, Sbuf, m->nc, false, after, st);
+        hipError_t e = scatter_product32(*m, sc, psi_in, Sbuf, false, after, st);
         if (e != hipSuccess) return hip_fail(e, "snrt_step: scattering product");
         S = Sbuf;
     }
@@ -1058,6 +1094,12 @@ snrt_status snrt_step_dose(const snrt_mesh* m, const snrt_quad* q, const snrt_sc
     if (sc->dense) {
         float* Sbuf = static_cast<float*>(ws);
         float* after = Sbuf + (size_t)m->nc * q->nq;
+        if (tune().step_fused && azimuth_product(*m, sc->B)) {
+            const hipError_t e =
+                launch_az_step(*m, sc->B.az, step_epi(*m, *q, to32(a), psi_in, psi_out), coeff,
+                               dose, st);
+            return e == hipSuccess ? SNRT_OK : hip_fail(e, "snrt_step_dose: fused dense step");
+        }
         if (step_fusable(*m, *q, sc->B)) {
             hipError_t e = fused_dense_step(*m, *q, to32(a), sc->B, psi_in, psi_out, after, st,
                                             part);
@@ -1065,7 +1107,7 @@ snrt_status snrt_step_dose(const snrt_mesh* m, const snrt_quad* q, const snrt_sc
                 e = launch_dose_fold(*m, part, q->nq / 128, a->inv_rho, coeff, dose, st);
             return e == hipSuccess ? SNRT_OK : hip_fail(e, "snrt_step_dose: fused dense step");
         }
-        hipError_t e = scatter_product32(sc, psi_in, Sbuf, m->nc, false, after, st);
+        hipError_t e = scatter_product32(*m, sc, psi_in, Sbuf, false, after, st);
         if (e != hipSuccess) return hip_fail(e, "snrt_step_dose: scattering product");
         S = Sbuf;
     }
@@ -1175,7 +1217,7 @@ snrt_status step2_common(const char* fn, const snrt_mesh* m, const snrt_quad* q,
         if constexpr (sizeof(T) == 4) {
             const StepArgs32 a32 = to32(a);
             e = launch_grad2_32(*m, *q, a32, lim, in[stage], G, st);
-            if (e == hipSuccess && S) e = scatter_product32(sc, in[stage], S, m->nc, false, U, st);
+            if (e == hipSuccess && S) e = scatter_product32(*m, sc, in[stage], S, false, U, st);
             if (e == hipSuccess)
                 e = launch_flux2_32(*m, *q, a32, in[stage], G, S, stage ? psi_in : nullptr,
                                     outp[stage], st);
@@ -1461,7 +1503,7 @@ snrt_status snrt_scatter_apply(const snrt_mesh* m, const snrt_quad* q, const snr
                      SNRT_E_ALIAS, "snrt_scatter_apply: workspace aliases psi or S");
         after = static_cast<float*>(ws);
     }
-    hipError_t e = scatter_product32(sc, psi, S, m->nc, transpose != 0, after,
+    hipError_t e = scatter_product32(*m, sc, psi, S, transpose != 0, after,
                                      static_cast<hipStream_t>(stream));
     return e == hipSuccess ? SNRT_OK : hip_fail(e, "snrt_scatter_apply: launch");
 }

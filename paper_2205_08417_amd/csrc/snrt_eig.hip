@@ -156,6 +156,13 @@ bool tridiagonal_qr(int n, std::vector<double>& d, std::vector<double>& e,
 
 }  // namespace
 
+bool symmetric_eigen(int n, std::vector<double>& S, std::vector<double>& lam,
+                     std::vector<double>& zt) {
+    std::vector<double> e;
+    householder_tridiagonal(n, S, lam, e, zt);
+    return tridiagonal_qr(n, lam, e, zt);
+}
+
 snrt_status implicit_form(int n, const std::vector<double>& A, std::vector<double>& lam,
                           std::vector<double>& x0, std::vector<double>& x1, double* resid,
                           const char* fn) {
@@ -205,9 +212,8 @@ snrt_status implicit_form(int n, const std::vector<double>& A, std::vector<doubl
             const double m = 0.5 * (S[(size_t)q * n + p] + S[(size_t)p * n + q]);
             S[(size_t)q * n + p] = S[(size_t)p * n + q] = m;
         }
-    std::vector<double> e, zt;
-    householder_tridiagonal(n, S, lam, e, zt);
-    if (!tridiagonal_qr(n, lam, e, zt)) {
+    std::vector<double> zt;
+    if (!symmetric_eigen(n, S, lam, zt)) {
         set_error(std::string(fn) + ": the symmetric QR iteration did not converge");
         return SNRT_E_UNSUPPORTED;
     }

@@ -10,6 +10,8 @@
 
 #include "../../include/snrt.h"
 
+struct snrt_quad;
+
 namespace snrt {
 
 constexpr int32_t kUnusedFace = INT32_MIN;
@@ -68,6 +70,20 @@ struct GemmOperand {
     float* t32 = nullptr;     // FP32 in the MFMA kernel's tiled order (FP32 mode, if shaped)
 };
 
+// The scattering operator in azimuthal modes (sn_azimuth.h), for operators that couple two
+// ordinates of a product rule through their polar nodes and azimuth difference only; na == 0:
+// not available.  Device arrays in the kernels' lane order (one allocation, base): the
+// azimuthal transforms f1, f3 [na / 16][64][4]; the polar matrices fwd and adj (transposed)
+// [class][mode pair][first, second][64][4]; for the IMEX solve the modes' eigenvectors e1 =
+// V^-1 and e2 = V diag(lam) in the same order and lam [class][mode pair][first, second][16].
+struct AzOperand {
+    int32_t np = 0, na = 0;
+    const float *f1 = nullptr, *f3 = nullptr, *fwd = nullptr, *adj = nullptr;
+    const float *e1 = nullptr, *e2 = nullptr, *lam = nullptr;
+    float* base = nullptr;
+    float* imp_base = nullptr;
+};
+
 // The scattering product as a chain of right operands, forward (S = Psi X0 [X1]) and adjoint
 // (Lambda B^T):
 //   dense kernel (chain 1):  X0 = B, B[p][q] = w_p K[q][p];  adjoint X0 = B^T;
@@ -95,7 +111,23 @@ struct DenseB {
     float* lam32 = nullptr;
     double* lam64 = nullptr;
     double imp_resid = 0.0;
+    // the same operator in azimuthal modes, where it has that structure, and its coefficients
+    // a_{kk'}(d) = A[(k, l + d)][(k', l)] (host, [np][np][na]) with the polar scaling r [np] that
+    // makes diag(r) A symmetric (empty if none)
+    AzOperand az;
+    std::vector<double> az_a, az_r;
 };
+
+// Azimuthal-mode form of a dense operator X [p][q] = A[q][p] (host, FP64) or of the moment form
+// of the given degree: fills B.az where the structure holds (no error where it does not).
+snrt_status make_azimuth_dense(DenseB& B, const snrt_quad& q, const std::vector<double>& X);
+snrt_status make_azimuth_moments(DenseB& B, const snrt_quad& q, const double* sigma_l);
+// The IMEX solve's operands of B.az (nothing where the modes are not symmetrisable).
+snrt_status make_azimuth_implicit(DenseB& B);
+// Eigenvalues lam [n] and eigenvectors zt [n][n] (rows) of the symmetric S [n][n]; S is
+// overwritten.  false: the QR iteration did not converge.
+bool symmetric_eigen(int n, std::vector<double>& S, std::vector<double>& lam,
+                     std::vector<double>& zt);
 
 // The eigendecomposition behind the implicit form (host, FP64): A [n][n] row-major with
 // A[q][p] = K[q][p] w_p; fills lam [n] and the two product operands x0, x1 [n][n].  Returns
@@ -174,7 +206,7 @@ namespace snrt {
 // the blocks per CU of the three persistent sweeps, SNRT_GEMM_STAGGER=0 turns the staggered
 // chunk order of the product off, SNRT_GEMM_EPILOGUE=0 the IMEX steps in the products'
 // epilogues (separate passes instead), SNRT_PN_MFMA=0 the matrix-core class blocks of the
-// degree-13 P_N step (all read once per process).
+// degree-13 P_N step, SNRT_AZIMUTH=0 the azimuthal-mode scattering (all read once per process).
 struct Tune {
     int step_blocks_per_cu = 3;
     int flux2_blocks_per_cu = 2;   // its larger per-cell footprint favours a narrower sweep
@@ -183,6 +215,7 @@ struct Tune {
     bool gemm_epilogue = true;     // IMEX per-cell steps in the products' epilogues
     bool pn_mfma = true;           // matrix-core class blocks in the degree-13 P_N step
     bool step_fused = true;        // dense step: the update in the product's epilogue
+    bool azimuth = true;           // azimuthal-mode scattering where the kernel has that form
 };
 const Tune& tune();
 
@@ -412,6 +445,22 @@ hipError_t launch_adjoint_fold32(int64_t nc, int32_t npieces, const StepArgs32& 
 hipError_t launch_adjoint_fold64(int64_t nc, int32_t npieces, const StepArgs32& a,
                                  const float* part, double* g_t, double* g_s, double* g_r,
                                  hipStream_t st);
+
+// The products and steps of sn_azimuth.h on an operand with na != 0; states below 4 GiB.
+// launch_az_step: the explicit step, with dose != NULL also dose[c] += coeff (1/rho) sum w psi
+// of its input.
+hipError_t launch_az_product(const snrt_mesh& m, const AzOperand& op, const float* mats,
+                             const float* in, float* out, hipStream_t st);
+hipError_t launch_az_step(const snrt_mesh& m, const AzOperand& op, const StepEpi& se, double coeff,
+                          double* dose, hipStream_t st);
+hipError_t launch_az_adjoint(const snrt_mesh& m, const snrt_quad& q, const AzOperand& op,
+                             const StepArgs32& a, const float* psi_n, const float* lam_np1,
+                             float* lam_n, float* g_t, float* g_s, float* g_r, const DoseAdj& da,
+                             hipStream_t st);
+hipError_t launch_az_adjoint(const snrt_mesh& m, const snrt_quad& q, const AzOperand& op,
+                             const StepArgs32& a, const float* psi_n, const float* lam_np1,
+                             float* lam_n, double* g_t, double* g_s, double* g_r,
+                             const DoseAdj& da, hipStream_t st);
 
 namespace fused {
 template <bool RHO, bool DOSE>
