@@ -24,7 +24,7 @@ SOURCES = ["sn_pn13.hip", "sn_gemm_mfma.hip", "sn_step_fused.hip", "sn_step_fuse
            "sn_reduce.hip", "sn_gemm_simple.hip", "sn_step2.hip", "sn_step_imex.hip",
            "sn_pn.hip", "snrt_pn_api.hip", "snrt_rollout.hip", "snrt_noalloc.hip",
            "snrt_eig.hip", "snrt_azimuth.hip", "sn_azimuth_step.hip",
-           "sn_azimuth_adjoint.hip"]
+           "sn_azimuth_adjoint.hip", "sn_azimuth_imex.hip"]
 ARCH = os.environ.get("SNRT_OFFLOAD_ARCH", "gfx950")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 

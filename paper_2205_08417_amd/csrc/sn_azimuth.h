@@ -12,7 +12,7 @@
 // below that of the three-product BF16 split (product of a two-decade state: 1.3e-7).
 // Measured against the general products' one-launch steps (BF16x3): 100 352 cells x 1024 ordinates
 // 0.235 against 0.658 ms (a copy of the state: 0.131), FP32 handles 1.8 ms; 299 538 x 512 with its
-// dose 0.348 against 0.690 ms; the transposed step on 74 498 x 512 0.147 against 0.237 ms.  What
+// dose 0.348 against 0.690 ms; the transposed step on 74 498 x 512 0.13 against 0.237 ms.  What
 // bounds it now: the vector update (0.10 ms of issue at 1024 ordinates), the matrix instructions
 // (0.065 ms) and the row traffic overlap only across the waves between two barriers.
 //
@@ -163,18 +163,37 @@ __device__ __forceinline__ void fold(f32x4 (&x)[P::SEG]) {
     }
 }
 
-// The operands a wave keeps: the azimuthal transforms and its mode pairs' polar matrices.
+// The azimuthal transforms of stages 1 and 3, in registers or (the kernels whose rows leave no
+// room for them) in LDS, from where each use reads them again: 16 registers that the transposed
+// and the IMEX step would otherwise spill (IMEX, 100 352 x 1024: 0.379 -> 0.304 ms; the 74 498 x
+// 512 gradient 2.55 -> 2.31).
+template <typename P, bool IN_LDS>
+struct Fourier {
+    f32x4 f[IN_LDS ? 1 : 2 * P::AZ];
+    const f32x4* lds;
+    // space: 2 AZ kWave f32x4 of LDS (IN_LDS; a block barrier follows)
+    __device__ __forceinline__ Fourier(const AzOperand& op, const Lane<P>& ln, f32x4* space) {
+        const f32x4* src = reinterpret_cast<const f32x4*>(op.f1);     // f3 follows f1
+        if constexpr (IN_LDS) {
+            for (int i = threadIdx.x; i < 2 * P::AZ * kWave; i += P::THREADS) space[i] = src[i];
+            lds = space + ln.lane;
+        } else {
+#pragma unroll
+            for (int a = 0; a < 2 * P::AZ; ++a) f[a] = src[a * kWave + ln.lane];
+        }
+    }
+    // stage 0 (to modes) or 1 (back), azimuthal class a
+    __device__ __forceinline__ f32x4 at(int stage, int a) const {
+        if constexpr (IN_LDS) return lds[(stage * P::AZ + a) * kWave];
+        else return f[stage * P::AZ + a];
+    }
+};
+
+// The polar matrices of a wave's mode pairs.
 template <typename P>
 struct Ops {
-    f32x4 f1[P::AZ], f3[P::AZ];
     f32x4 d[P::ITEMS][P::MU];
-    __device__ __forceinline__ Ops(const AzOperand& op, const float* __restrict__ mats,
-                                   const Lane<P>& ln) {
-#pragma unroll
-        for (int a = 0; a < P::AZ; ++a) {
-            f1[a] = reinterpret_cast<const f32x4*>(op.f1)[a * kWave + ln.lane];
-            f3[a] = reinterpret_cast<const f32x4*>(op.f3)[a * kWave + ln.lane];
-        }
+    __device__ __forceinline__ Ops(const float* __restrict__ mats, const Lane<P>& ln) {
         load(d, mats, ln);
     }
     // mats: [class = mu * AZ + az][pair][which][lane] of float4
@@ -194,15 +213,15 @@ struct Ops {
 };
 
 // Stage 1: the row segments x of this wave into LDS as modes.
-template <typename P>
-__device__ __forceinline__ void to_modes(f32x4 (&x)[P::SEG], const Ops<P>& op, const Lane<P>& ln,
-                                         float* __restrict__ lds) {
+template <typename P, bool FL>
+__device__ __forceinline__ void to_modes(f32x4 (&x)[P::SEG], const Fourier<P, FL>& fr,
+                                         const Lane<P>& ln, float* __restrict__ lds) {
     fold<P>(x);
     float* at = lds + ln.kk * kPlane + ln.cell * 16 + ((ln.l4 ^ swz(ln.kk, ln.cell)) << 2);
 #pragma unroll
     for (int i = 0; i < P::SEG; ++i)
         *reinterpret_cast<f32x4*>(at + (P::az(i) * P::MU + ln.mu0 + i / P::AZ) * kClass) =
-            mfma4(x[i], op.f1[P::az(i)], f32x4{0, 0, 0, 0});
+            mfma4(x[i], fr.at(0, P::az(i)), f32x4{0, 0, 0, 0});
 }
 
 // y = A x for a pair of modes.  The pair of modes 0 and na / 2 (j = 0 of class 0) has a matrix for
@@ -252,9 +271,9 @@ __device__ __forceinline__ const f32x4* second_of(const f32x4* second, const Lan
 }
 
 // Stage 3: the modes of this wave's segments back to azimuths.
-template <typename P>
-__device__ __forceinline__ void from_modes(f32x4 (&s)[P::SEG], const Ops<P>& op, const Lane<P>& ln,
-                                           const float* __restrict__ lds) {
+template <typename P, bool FL>
+__device__ __forceinline__ void from_modes(f32x4 (&s)[P::SEG], const Fourier<P, FL>& fr,
+                                           const Lane<P>& ln, const float* __restrict__ lds) {
     const float* at = lds + ln.l4 * kPlane + ln.cell * 16 + (ln.kk & 3);
     const int g = (ln.kk >> 2) ^ swz(ln.l4, ln.cell);        // mode 4 s + l4: granule g ^ s
 #pragma unroll
@@ -263,7 +282,7 @@ __device__ __forceinline__ void from_modes(f32x4 (&s)[P::SEG], const Ops<P>& op,
         f32x4 y;
 #pragma unroll
         for (int st = 0; st < 4; ++st) y[st] = at[cls * kClass + st * 4 * kPlane + ((g ^ st) << 2)];
-        s[i] = mfma4(op.f3[P::az(i)], y, f32x4{0, 0, 0, 0});
+        s[i] = mfma4(fr.at(1, P::az(i)), y, f32x4{0, 0, 0, 0});
     }
     fold<P>(s);
 }
@@ -459,7 +478,8 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_product(AzOperand opd,
     __shared__ f32x4 second[P::MU * kWave];
     __shared__ f32x4 rows[P::WAVES][P::SEG * kWave];
     const Lane<P> ln(opd.np);
-    const Ops<P> op(opd, mats, ln);
+    const Ops<P> op(mats, ln);
+    const Fourier<P, false> fr(opd, ln, nullptr);
     load_second<P>(mats, second);
     const uint32_t row_bytes = (uint32_t)(opd.np * opd.na) * 4u;
     const auto rin = make_rsrc(in, (uint32_t)nc * row_bytes);
@@ -478,13 +498,13 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_product(AzOperand opd,
         f32x4 x[P::SEG];
         to_matrix_order<P>(x, nx, ln, rows[ln.wave]);
         fetch(tl.t + tl.stride);
-        to_modes<P>(x, op, ln, lds[b]);
+        to_modes<P>(x, fr, ln, lds[b]);
         lds_barrier();
         on_modes<P>(ln, lds[b], [&](int i, int mu, const f32x4& v) {
             return apply_pair(op.d[i][mu], second_of<P>(second, ln, i, mu), v, ln.lane);
         });
         lds_barrier();
-        from_modes<P>(x, op, ln, lds[b]);
+        from_modes<P>(x, fr, ln, lds[b]);
         to_memory_order<P>(x, ln, rows[ln.wave]);
 #pragma unroll
         for (int i = 0; i < P::SEG; ++i)
@@ -512,7 +532,8 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_step(AzOperand opd, StepEp
     __shared__ f32x4 dirs[2 * P::AZ * P::MU * kWave];
     __shared__ f32x4 rows[P::WAVES][SEG * kWave];
     const Lane<P> ln(opd.np);
-    const Ops<P> op(opd, opd.fwd, ln);
+    const Ops<P> op(opd.fwd, ln);
+    const Fourier<P, false> fr(opd, ln, nullptr);
     load_second<P>(opd.fwd, second);
     load_table<P>(se.tab, se.nq, dirs);
     const FwdCtx<float> cx = make_ctx(se.a, se.psi_in, se.psi_out, se.nc, se.nq, se.nbf);
@@ -548,7 +569,7 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_step(AzOperand opd, StepEp
         f32x4 x[SEG];
         __builtin_amdgcn_s_setprio(2);
         to_matrix_order<P>(x, p, ln, rows[ln.wave]);
-        to_modes<P>(x, op, ln, buf);
+        to_modes<P>(x, fr, ln, buf);
         const float matn = words.template material<MF>(recn, cn.c, ln.lane);
         own(pn, tl.t + tl.stride);
         const float recn2 = record(tl.t + 2 * tl.stride);
@@ -566,7 +587,7 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_step(AzOperand opd, StepEp
             if (P::WPC == 2 && ln.mu0 == 1 && ln.lane == 0) dsum[b][ln.cell] = sd;
         }
         lds_barrier();
-        from_modes<P>(x, op, ln, buf);
+        from_modes<P>(x, fr, ln, buf);
         to_memory_order<P>(x, ln, rows[ln.wave]);
         __builtin_amdgcn_s_setprio(0);
         CellData<MF> cd;
@@ -693,7 +714,9 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_adjoint(AzOperand opd, AzA
     __shared__ f32x4 rows[P::WAVES][SEG * kWave];
     __shared__ float gsum[2][P::WPC == 2 ? P::WAVES : 1][4];
     const Lane<P> ln(opd.np);
-    const Ops<P> op(opd, opd.adj, ln);
+    __shared__ f32x4 ftab[2 * P::AZ * kWave];
+    const Ops<P> op(opd.adj, ln);
+    const Fourier<P, true> fr(opd, ln, ftab);
     load_second<P>(opd.adj, second);
     load_table<P>(e.tab, e.nq, dirs);
     const StepArgs32& a = e.a;
@@ -755,7 +778,7 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_adjoint(AzOperand opd, AzA
         f32x4 x[SEG];
         __builtin_amdgcn_s_setprio(2);
         to_matrix_order<P>(x, l, ln, rows[ln.wave]);
-        to_modes<P>(x, op, ln, buf);
+        to_modes<P>(x, fr, ln, buf);
         const float matn = words.template load<MF>(recn, cn.c, ln.lane);
         own(lnx, tl.t + tl.stride);
         const float recn2 = record(tl.t + 2 * tl.stride);
@@ -765,7 +788,7 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_adjoint(AzOperand opd, AzA
             return apply_pair(op.d[i][mu], second_of<P>(second, ln, i, mu), v, ln.lane);
         });
         lds_barrier();
-        from_modes<P>(x, op, ln, buf);
+        from_modes<P>(x, fr, ln, buf);
         to_memory_order<P>(x, ln, rows[ln.wave]);
         __builtin_amdgcn_s_setprio(0);
         using W = CellWords;
@@ -844,6 +867,130 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_adjoint(AzOperand opd, AzA
     if constexpr (P::WPC == 2) {
         lds_barrier();
         shared_gradients(matp, cp, b);
+    }
+}
+
+// ----------------------------------------------------------------------------- the IMEX step
+
+// The IMEX step with a dense kernel or its moment projection (Sec. 4.2) in one pass: per cell
+// (a I - b A) psi' = r with a = 1 + dt alpha_t sigma_t, b = dt alpha_s sigma_s, A = K W.  The modes
+// decouple, D_m = V diag(lam) V^-1 per mode, so psi' = (r + V D V^-1 r) / a with
+// D = diag(b lam / (a - b lam)).  r is the collision-free step, formed from the wave's rows and
+// kept in registers; in stage 2 the two polar products follow each other without LDS (an MFMA's
+// result rows 4 l4 + s are the next one's K order), the per-cell diagonal between them.  The next
+// tile's rows are fetched as soon as r is formed and fly during the exchange.  100 352 x 1024:
+// 0.304 ms, against 1.47 ms with two nq x nq products (BF16x3) and 0.52 ms with two products
+// through 96 padded moments, each after a collision-free step of its own.
+template <typename P, int MF, bool RHO>
+__global__ __launch_bounds__(P::THREADS, 4) void k_az_imex(AzOperand opd, StepEpi se)
+{
+    constexpr int SEG = P::SEG;
+    __shared__ __attribute__((aligned(16))) float lds[2][P::LDS];
+    __shared__ f32x4 second[2][P::MU * kWave];
+    __shared__ f32x4 dirs[2 * P::AZ * P::MU * kWave];
+    __shared__ f32x4 rows[P::WAVES][SEG * kWave];
+    const Lane<P> ln(opd.np);
+    __shared__ f32x4 ftab[2 * P::AZ * kWave];
+    const Ops<P> op(opd.e1, ln);
+    const Fourier<P, true> fr(opd, ln, ftab);
+    f32x4 e2[P::ITEMS][P::MU], lam[P::ITEMS][P::MU];
+    Ops<P>::load(e2, opd.e2, ln);
+#pragma unroll
+    for (int i = 0; i < P::ITEMS; ++i)
+#pragma unroll
+        for (int mu = 0; mu < P::MU; ++mu) {
+            const int az = Ops<P>::az_of(ln, i), pair = ln.wave & 7;
+            const int which = pair == 0 && az == 0 ? (ln.lane >> 3) & 1 : 0;
+            lam[i][mu] = reinterpret_cast<const f32x4*>(
+                opd.lam)[(((mu * P::AZ + az) * 8 + pair) * 2 + which) * 4 + ln.l4];
+        }
+    load_second<P>(opd.e1, second[0]);
+    load_second<P>(opd.e2, second[1]);
+    load_table<P>(se.tab, se.nq, dirs);
+    const StepArgs32& a = se.a;
+    const FwdCtx<float> cx = make_ctx(a, se.psi_in, se.psi_out, se.nc, se.nq, se.nbf);
+    const CellWords words(ln.lane, a, cx.src_arr, nullptr);
+    Tiles tl((int32_t)((se.nc + kCells - 1) / kCells));
+    if (tl.t >= tl.end) return;
+    auto cell_of = [&](int32_t t) { return Cell(t < tl.end ? t : tl.end - 1, ln.cell, se.nc); };
+    auto record = [&](int32_t t) { return CellWords::record(se.geom, cell_of(t).c, ln.lane); };
+    // the materials of this lane's column in stage 2
+    auto column = [&](const float* __restrict__ v, int32_t t) {
+        const int64_t c = (int64_t)(t < tl.end ? t : tl.end - 1) * kCells + (ln.lane & 7);
+        return v[c < se.nc ? c : se.nc - 1];
+    };
+    f32x4 p[SEG], up[SEG][MF];
+    auto fetch = [&](float rec, int32_t c) {
+#pragma unroll
+        for (int i = 0; i < SEG; ++i) {
+            p[i] = load4(cx.psi, ln.off[i], (uint32_t)c * cx.row_bytes);
+#pragma unroll
+            for (int f = 0; f < MF; ++f)
+                up[i][f] = load_face(CellWords::word(rec, f), c, ln.off[i], cx);
+        }
+    };
+    float rec = record(tl.t), mat = words.template material<MF>(rec, cell_of(tl.t).c, ln.lane);
+    float st = column(a.sigma_t, tl.t), ss = column(a.sigma_s, tl.t);
+    fetch(rec, cell_of(tl.t).c);
+    float recn = record(tl.t + tl.stride);
+    __syncthreads();                       // second, dirs
+    for (int b = 0;; b ^= 1) {
+        const Cell c = cell_of(tl.t), cn = cell_of(tl.t + tl.stride);
+        float* buf = lds[b];
+        CellData<MF> cd;
+        cd.template form<RHO>(rec, mat, a, cx);
+        f32x4 r[SEG], x[SEG];
+#pragma unroll
+        for (int i = 0; i < SEG; ++i) {
+            const f32x4* dir = dirs + ln.off[i] / 16;
+            const f32x4 ox = dir[0], oy = dir[P::AZ * P::MU * kWave];
+            if (cd.scaled) {
+#pragma unroll
+                for (int f = 0; f < MF; ++f) up[i][f] *= cd.ghost[f];
+            }
+            const f32x4 acc = flux4<MF, RHO>(p[i], cd.irho, cd.nx, cd.ny, up[i], ox, oy);
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                r[i][v] = __builtin_fmaf(cx.src_mul, cd.srcv,
+                                         __builtin_fmaf(-cd.cflux, acc[v], p[i][v]));
+        }
+        const float matn = words.template material<MF>(recn, cn.c, ln.lane);
+        const float stn = column(a.sigma_t, tl.t + tl.stride);
+        const float ssn = column(a.sigma_s, tl.t + tl.stride);
+        fetch(recn, cn.c);
+        const float recn2 = record(tl.t + 2 * tl.stride);
+        __builtin_amdgcn_s_setprio(2);
+        to_matrix_order<P>(x, r, ln, rows[ln.wave]);
+        to_modes<P>(x, fr, ln, buf);
+        lds_barrier();
+        const float ca = 1.0f + a.dt * a.alpha_t * st, cb = a.dt * a.alpha_s * ss;
+        on_modes<P>(ln, buf, [&](int i, int mu, const f32x4& v) {
+            f32x4 z = apply_pair(op.d[i][mu], second_of<P>(second[0], ln, i, mu), v, ln.lane);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) z[k] *= cb / (ca - cb * lam[i][mu][k]);
+            return apply_pair(e2[i][mu], second_of<P>(second[1], ln, i, mu), z, ln.lane);
+        });
+        lds_barrier();
+        from_modes<P>(x, fr, ln, buf);
+        to_memory_order<P>(x, ln, rows[ln.wave]);
+        __builtin_amdgcn_s_setprio(0);
+        const float y = cd.cabs / (1.0f + cd.cabs);
+#pragma unroll
+        for (int i = 0; i < SEG; ++i) {
+            const f32x4 s = r[i] + x[i];
+            f32x4 o;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) o[v] = __builtin_fmaf(-s[v], y, s[v]);
+            if (c.real && ln.exists[i])
+                store4(cx.out, ln.off[i], (uint32_t)c.c * cx.row_bytes, o);
+        }
+        tl.t += tl.stride;
+        if (tl.t >= tl.end) break;
+        rec = recn;
+        recn = recn2;
+        mat = matn;
+        st = stn;
+        ss = ssn;
     }
 }
 

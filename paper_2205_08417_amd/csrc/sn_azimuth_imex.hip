@@ -1,0 +1,27 @@
+// The IMEX step with dense or moment-projected scattering through azimuthal modes (sn_azimuth.h).
+#include "sn_azimuth.h"
+
+namespace snrt {
+
+hipError_t launch_az_imex(const snrt_mesh& m, const AzOperand& op, const StepEpi& se,
+                          hipStream_t st) {
+    if (m.nc == 0) return hipSuccess;
+    return az::by_shape(op, [&](auto shape) {
+        using P = decltype(shape);
+        auto go = [&](auto mfc, auto rc) {
+            constexpr int MF = decltype(mfc)::value;
+            constexpr bool R = decltype(rc)::value;
+            static const int occ = az::az_resident(az::k_az_imex<P, MF, R>, P::THREADS);
+            hipLaunchKernelGGL((az::k_az_imex<P, MF, R>), dim3(az::az_blocks(m, occ)),
+                               dim3(P::THREADS), 0, st, op, se);
+            return hipGetLastError();
+        };
+        using I3 = std::integral_constant<int, 3>;
+        using I4 = std::integral_constant<int, 4>;
+        if (m.mf == 4)
+            return se.a.inv_rho ? go(I4{}, std::true_type{}) : go(I4{}, std::false_type{});
+        return se.a.inv_rho ? go(I3{}, std::true_type{}) : go(I3{}, std::false_type{});
+    });
+}
+
+}  // namespace snrt

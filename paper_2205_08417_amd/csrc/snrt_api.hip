@@ -673,7 +673,7 @@ snrt_status snrt_scatter_prepare_implicit(snrt_scatter* sc) {
     }
     B.imp_resid = resid;
     B.implicit = true;
-    return SNRT_OK;
+    return make_azimuth_implicit(B);
 }
 
 }  // extern "C"
@@ -1324,6 +1324,8 @@ hipError_t imex_modes(const snrt_mesh* m, const snrt_quad* q, const DenseB& B,
         StepArgs32 free_flight = a32;
         free_flight.alpha_t = 0.0f;
         free_flight.alpha_s = 0.0f;
+        if (B.az.e1)   // the whole step in one launch through the azimuthal modes
+            return launch_az_imex(*m, B.az, step_epi(*m, *q, a32, psi_in, psi_out), st);
         e = launch_free_step32(*m, *q, free_flight, psi_in, psi_out, st);
         // the per-cell diagonal and the final combine ride on the two products' epilogues
         // where the matrix-core kernels run them (S then stays unused), else separate passes

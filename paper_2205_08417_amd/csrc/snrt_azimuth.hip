@@ -140,27 +140,38 @@ snrt_status make_azimuth_dense(DenseB& B, const snrt_quad& q, const std::vector<
     int np = 0, na = 0;
     if (!tune().azimuth || !product_shape(q, np, na)) return SNRT_OK;
     const int nq = q.nq;
-    auto A = [&](int k, int l, int k2, int l2) {
-        return X[(size_t)(k2 * na + l2) * nq + k * na + l];
-    };
-    // mean over the azimuthal shifts and the mirror image d -> -d, then the largest distance
-    std::vector<double> a((size_t)np * np * na);
-    for (int k = 0; k < np; ++k)
-        for (int k2 = 0; k2 < np; ++k2) {
-            double* m = &a[((size_t)k * np + k2) * na];
-            double top = 0.0;
-            std::vector<double> sum(na, 0.0);
-            for (int l2 = 0; l2 < na; ++l2)
-                for (int d = 0; d < na; ++d) {
-                    const double v = A(k, (l2 + d) % na, k2, l2);
-                    sum[d] += v;
-                    top = std::max(top, std::fabs(v));
+    // mean over the azimuthal shifts and the mirror image d -> -d (rows of X in order), then the
+    // largest distance from it
+    const size_t n = (size_t)np * np * na;
+    std::vector<double> a(n, 0.0), top((size_t)np * np, 0.0);
+    for (int k2 = 0; k2 < np; ++k2)
+        for (int l2 = 0; l2 < na; ++l2) {
+            const double* x = &X[(size_t)(k2 * na + l2) * nq];
+            for (int k = 0; k < np; ++k, x += na) {
+                double* m = &a[((size_t)k * np + k2) * na];
+                double t = top[(size_t)k * np + k2];
+                for (int l = 0; l < na; ++l) {
+                    m[(l - l2) & (na - 1)] += x[l];
+                    t = std::max(t, std::fabs(x[l]));
                 }
-            for (int d = 0; d < na; ++d) m[d] = 0.5 * (sum[d] + sum[(na - d) % na]) / na;
-            for (int l2 = 0; l2 < na; ++l2)
-                for (int d = 0; d < na; ++d)
-                    if (!(std::fabs(A(k, (l2 + d) % na, k2, l2) - m[d]) <= kInvariant * top))
-                        return SNRT_OK;
+                top[(size_t)k * np + k2] = t;
+            }
+        }
+    for (size_t i = 0; i < n; i += na) {
+        a[i] /= na;
+        a[i + na / 2] /= na;
+        for (int d = 1; d < na / 2; ++d)
+            a[i + d] = a[i + na - d] = 0.5 * (a[i + d] + a[i + na - d]) / na;
+    }
+    for (int k2 = 0; k2 < np; ++k2)
+        for (int l2 = 0; l2 < na; ++l2) {
+            const double* x = &X[(size_t)(k2 * na + l2) * nq];
+            for (int k = 0; k < np; ++k, x += na) {
+                const double* m = &a[((size_t)k * np + k2) * na];
+                double far = 0.0;
+                for (int l = 0; l < na; ++l) far = std::max(far, std::fabs(x[l] - m[(l - l2) & (na - 1)]));
+                if (!(far <= kInvariant * top[(size_t)k * np + k2])) return SNRT_OK;
+            }
         }
     if (np > 16) {
         for (int k = 0; k < np; ++k)
@@ -224,7 +235,64 @@ snrt_status make_azimuth_moments(DenseB& B, const snrt_quad& q, const double* si
             }
     }
     B.az_r = std::move(r);
-    return upload_operand(B, np, na, std::move(a));
+    const snrt_status s = upload_operand(B, np, na, std::move(a));
+    return s == SNRT_OK ? make_azimuth_implicit(B) : s;
+}
+
+snrt_status make_azimuth_implicit(DenseB& B) {
+    AzOperand& op = B.az;
+    if (op.na == 0 || op.imp_base || B.az_r.empty()) return SNRT_OK;
+    const int np = op.np, na = op.na, AZ = na / 16, MU = np > 16 ? 2 : 1, h = np / MU;
+    // A is symmetric after the scaling r of the polar nodes; under the polar fold r has to be
+    // the same on both halves
+    std::vector<double> sr(h);
+    for (int k = 0; k < h; ++k) {
+        if (MU == 2 && std::fabs(B.az_r[k] - B.az_r[np - 1 - k]) > 1e-10 * B.az_r[k]) return SNRT_OK;
+        sr[k] = std::sqrt(B.az_r[k]);
+    }
+    const std::vector<double> M = polar_matrices(B.az_a, np, na, false);
+    const size_t nb = (size_t)AZ * MU * 16;                    // matrices
+    double top = 0.0;
+    for (double v : M) top = std::max(top, std::fabs(v));
+    std::vector<double> E1(nb * 256, 0.0), E2(nb * 256, 0.0), L(nb * 16, 0.0);
+    std::vector<double> S((size_t)h * h), lam, zt;
+    for (size_t b = 0; b < nb; ++b) {
+        const double* D = &M[b * 256];
+        for (int i = 0; i < h; ++i)
+            for (int j = 0; j < h; ++j) S[(size_t)i * h + j] = sr[i] * D[i * 16 + j] / sr[j];
+        for (int i = 0; i < h; ++i)
+            for (int j = i + 1; j < h; ++j) {
+                double &u = S[(size_t)i * h + j], &v = S[(size_t)j * h + i];
+                if (!(std::fabs(u - v) <= 1e-10 * top)) return SNRT_OK;
+                u = v = 0.5 * (u + v);
+            }
+        if (!symmetric_eigen(h, S, lam, zt)) return SNRT_OK;
+        for (int j = 0; j < h; ++j) {
+            L[b * 16 + j] = lam[j];
+            for (int k = 0; k < h; ++k) {
+                const double z = zt[(size_t)j * h + k];
+                E1[b * 256 + j * 16 + k] = z * sr[k];
+                E2[b * 256 + k * 16 + j] = lam[j] * z / sr[k] / MU;
+            }
+        }
+    }
+    const size_t nm = nb * 256;
+    std::vector<float> host(2 * nm + L.size());
+    pack(E1.data(), nb, false, host.data());
+    pack(E2.data(), nb, false, &host[nm]);
+    for (size_t i = 0; i < L.size(); ++i) host[2 * nm + i] = (float)L[i];
+    float* base = nullptr;
+    snrt_status s = dev_alloc(&base, host.size(), "azimuthal modes (implicit)");
+    if (s == SNRT_OK) s = upload(base, host.data(), host.size(), "azimuthal modes: upload");
+    if (s != SNRT_OK) {
+        dev_free(base);
+        return s;
+    }
+    op.imp_base = base;
+    op.e1 = base;
+    op.e2 = base + nm;
+    op.lam = base + 2 * nm;
+    return SNRT_OK;
 }
 
 }  // namespace snrt

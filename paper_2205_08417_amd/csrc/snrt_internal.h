@@ -453,6 +453,9 @@ hipError_t launch_az_product(const snrt_mesh& m, const AzOperand& op, const floa
                              const float* in, float* out, hipStream_t st);
 hipError_t launch_az_step(const snrt_mesh& m, const AzOperand& op, const StepEpi& se, double coeff,
                           double* dose, hipStream_t st);
+// the IMEX step on an operand with e1 != NULL (dense kernel or moment form)
+hipError_t launch_az_imex(const snrt_mesh& m, const AzOperand& op, const StepEpi& se,
+                          hipStream_t st);
 hipError_t launch_az_adjoint(const snrt_mesh& m, const snrt_quad& q, const AzOperand& op,
                              const StepArgs32& a, const float* psi_n, const float* lam_np1,
                              float* lam_n, float* g_t, float* g_s, float* g_r, const DoseAdj& da,

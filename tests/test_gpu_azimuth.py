@@ -156,3 +156,28 @@ def test_operators_without_the_structure_keep_the_general_products(make, precisi
     assert rel_l2(S.to_user(out).cpu().numpy(),
                   o.adjoint_step(op, P.psi0, lam, P.dt, 1.0, 1.0, ref[0], ref[1], None)) <= tol
     S.close()
+
+
+# stiff: dt sigma of the order of ten.  The solve applies the modes' eigenvectors (condition
+# number the root of the weights' ratio, below 4 here) around the diagonal: twice the product's
+# roundings, each once more through the weights, 4 * TOL.
+@pytest.mark.parametrize("npol,naz", [(8, 32), (13, 32), (18, 32), (9, 16), (16, 16), (20, 16)])
+@pytest.mark.parametrize("kind", [3, 4, "quads"])
+@pytest.mark.parametrize("moments", [False, True])
+def test_imex_step_vs_oracle(npol, naz, kind, moments):
+    from oracle import moments as mo
+    from oracle import oracle as o
+    from paper_2205_08417_amd.solver import Solver
+    P = _problem(npol, naz, _mesh(kind), rho=kind != 3, seed=77)
+    st = P.sigma_t * 10.0 / P.dt
+    P = dataclasses.replace(P, sigma_t=st, sigma_s=0.9 * st)
+    sig = I.hg_legendre_moments(0.8, 3) if moments else None
+    K = mo.moment_kernel(P.omega, P.w, sig) if moments else P.K
+    op = o.OracleProblem.from_problem(P, K=K)
+    S = Solver(P, precision="fp32", moments=sig)
+    out = torch.empty_like(S.initial_state())
+    S.step_imex(S.initial_state(), out, S.args(alpha_t=1.1, alpha_s=0.9, inflow_scale=0.6))
+    err = rel_l2(S.to_user(out).cpu().numpy(), o.step_imex(op, P.psi0, P.dt, 1.1, 0.9, 0.6))
+    print(f"imex {npol}x{naz} {kind} moments={moments}: {err:.2e}")
+    S.close()
+    assert err <= 4 * TOL
