@@ -4,8 +4,8 @@
 //   mass         M = sum_i A_i phi_i                              (solver log, Sec. 5.1)
 //   dose         D_i += coeff * (1/rho_i) * phi_i                 (Sec. 2, pseudo-time form)
 //
-// Persistent wavefronts stride over the cells; lane l owns the V contiguous ordinates
-// [l*V, l*V+V) of a row (16-byte loads) and keeps their FP64 weights in registers, sums its
+// Persistent wavefronts stride over the cells; a lane owns V ordinates of a row (load_slice: V
+// contiguous ones, or every 64th) and keeps their FP64 weights in registers, sums its
 // slice in FP64 and the wave adds the 64 partial sums with a butterfly.  The next row is
 // loaded while the current one is reduced.  The mass is a deterministic two-pass tree: one
 // partial per wave (a fixed set of cells in a fixed order), then one block folds them.
@@ -29,9 +29,12 @@ struct RowPhi {
     int q0;
     int32_t nq;
     __device__ __forceinline__ RowPhi(const double* __restrict__ w, int32_t nq_, int lane)
-        : q0(lane * V), nq(nq_) {
+        : q0(lane_q0<V, EXACT>(lane)), nq(nq_) {
 #pragma unroll
-        for (int k = 0; k < V; ++k) wv[k] = (q0 + k < nq) ? w[q0 + k] : 0.0;
+        for (int k = 0; k < V; ++k) {
+            const int q = q0 + lane_step<EXACT>(k);
+            wv[k] = (EXACT || q < nq) ? w[q] : 0.0;
+        }
     }
     __device__ __forceinline__ void load(const float* __restrict__ psi, int64_t c, float (&r)[V]) const {
         load_slice<V, EXACT>(psi + c * (int64_t)nq, q0, nq, r);
@@ -163,10 +166,9 @@ __global__ __launch_bounds__(kStepBlock) void k_dose_adjoint(const double* __res
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t nw = (int64_t)gridDim.x * (blockDim.x / kWave);
     const int64_t gw = (int64_t)blockIdx.x * (blockDim.x / kWave) + (threadIdx.x / kWave);
-    const int q0 = lane * V;
+    const int q0 = lane_q0<V, EXACT>(lane);
     double wv[V];
-#pragma unroll
-    for (int k = 0; k < V; ++k) wv[k] = (q0 + k < nq) ? w[q0 + k] : 0.0;
+    load_slice<V, EXACT>(w, q0, nq, wv);
     for (int64_t c = gw; c < nc; c += nw) {
         const double g = coeff * (inv_rho ? (double)inv_rho[c] : 1.0) * g_dose[c];
         float* row = lam + c * (int64_t)nq;

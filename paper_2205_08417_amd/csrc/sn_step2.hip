@@ -61,7 +61,7 @@ __global__ __launch_bounds__(kStepBlock) void k_grad2(
     const int64_t item = lb * kCellsPerBlock + wave;
     if (item >= (nc << shift)) return;
     const int64_t c = item >> shift;
-    const int q0 = (int)(item & ((1 << shift) - 1)) * kWave * V + lane * V;
+    const int q0 = (int)(item & ((1 << shift) - 1)) * kWave * V + lane_q0<V, EXACT>(lane);
     const auto& g = geom[c];
     const auto& rc = recon[c];
 
@@ -145,7 +145,7 @@ __global__ __launch_bounds__(kStepBlock) void k_flux2(
     const int64_t item = lb * kCellsPerBlock + wave;
     if (item >= (nc << shift)) return;
     const int64_t c = item >> shift;
-    const int q0 = (int)(item & ((1 << shift) - 1)) * kWave * V + lane * V;
+    const int q0 = (int)(item & ((1 << shift) - 1)) * kWave * V + lane_q0<V, EXACT>(lane);
     const auto& g = geom[c];
     const auto& rc = recon[c];
 
@@ -348,7 +348,7 @@ __global__ __launch_bounds__(kStepBlock) void k_flux2p(
     const int32_t xend = (int32_t)(xb + items_per_xcd < ni ? xb + items_per_xcd : ni);
     int32_t c = (int32_t)xb + kx * kCellsPerBlock + wave;
     if (c >= xend) return;
-    const int q0 = lane * V;
+    const int q0 = lane_q0<V, EXACT>(lane);
     const int32_t sh = shift;
     const int chunk = c & ((1 << sh) - 1);
     const uint32_t cb = (uint32_t)chunk * (uint32_t)(kWave * V * sizeof(T));

@@ -1,9 +1,15 @@
 // Explicit S_N step and its adjoint on gfx950 (kernel templates; instantiated by
 // sn_step_f32.hip, sn_step_f64.hip and sn_adjoint.hip).
 //
-// One wavefront owns one cell; lane l owns the V contiguous ordinates [l*V, l*V+V) of that
-// cell (psi is [cell][ordinate], ordinates fastest), so the own row and every neighbour row
-// are read with fully coalesced 16-byte loads.  The cell's geometry record is wave-uniform
+// One wavefront owns one cell; where the row is 64, 128, 256, 512 or 1024 ordinates long (EXACT),
+// lane l owns the V contiguous ordinates [l*V, l*V+V) of that cell (psi is [cell][ordinate],
+// ordinates fastest), so the own row and every neighbour row are read with fully coalesced
+// 16-byte loads.  Rows of any other length are striped: lane l owns ordinates l, l + 64, ..., V =
+// ceil(nq / 64) of them, so that every access covers 64 consecutive ordinates and all but the
+// last fill the wave, whatever the length.  Lanes of V contiguous ordinates, V the next power of
+// two, took V strided 4-byte accesses to each row and left lanes idle: 79 202 cells, 182 / 252 /
+// 480 ordinates, step 97 / 126 / 468 -> 26 / 32 / 60 us, second-order step 523 / 695 / 2534 ->
+// 231 / 316 / 568 us, transposed step 109 / 140 / 538 -> 36 / 48 / 100 us.  The cell's geometry record is wave-uniform
 // and arrives through scalar loads.  Isotropic scattering is a wavefront reduction of the
 // cell's own row; dense scattering reads the GEMM result S = Psi B.
 //
@@ -41,6 +47,21 @@ template <> struct ArgsOf<double> { using type = StepArgs64; };
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
+// First ordinate of a lane, and the place of its k-th one relative to that.
+template <int V, bool EXACT>
+__device__ __forceinline__ int lane_q0(int lane) {
+    return EXACT ? lane * V : lane;
+}
+template <bool EXACT>
+__device__ __forceinline__ constexpr int lane_step(int k) {
+    return EXACT ? k : k * kWave;
+}
+// Striped rows: the first k whose ordinates may lie past the row's end (dispatch_v).
+template <int V, typename T>
+__device__ __forceinline__ constexpr int first_ragged() {
+    return V <= 2 || (sizeof(T) == 4 && V <= 8) ? V - 1 : V / 2;
+}
+
 template <int V, bool EXACT, typename T>
 __device__ __forceinline__ void load_slice(const T* __restrict__ row, int q0, int nq, T (&r)[V]) {
     if constexpr (EXACT) {
@@ -60,7 +81,10 @@ __device__ __forceinline__ void load_slice(const T* __restrict__ row, int q0, in
         }
     } else {
 #pragma unroll
-        for (int j = 0; j < V; ++j) r[j] = (q0 + j < nq) ? row[q0 + j] : T(0);
+        for (int j = 0; j < V; ++j) {
+            const int q = q0 + lane_step<false>(j);
+            r[j] = (j < first_ragged<V, T>() || q < nq) ? row[q] : T(0);
+        }
     }
 }
 
@@ -96,8 +120,10 @@ __device__ __forceinline__ void store_slice(T* __restrict__ row, int q0, int nq,
         }
     } else {
 #pragma unroll
-        for (int j = 0; j < V; ++j)
-            if (q0 + j < nq) row[q0 + j] = r[j];
+        for (int j = 0; j < V; ++j) {
+            const int q = q0 + lane_step<false>(j);
+            if (j < first_ragged<V, T>() || q < nq) row[q] = r[j];
+        }
     }
 }
 
@@ -144,7 +170,9 @@ __device__ __forceinline__ void buf_load_row(__amdgpu_buffer_rsrc_t r, uint32_t 
     } else {
 #pragma unroll
         for (int k = 0; k < V; ++k) {
-            const int q = q0 + k < nq ? q0 + k : nq - 1;           // clamp, then zero
+            const bool sure = k < first_ragged<V, T>();
+            const int qk = q0 + lane_step<false>(k);
+            const int q = sure || qk < nq ? qk : nq - 1;           // clamp, then zero
             T v;
             if constexpr (sizeof(T) == 4) {
                 int32_t b = __builtin_amdgcn_raw_buffer_load_b32(r, (uint32_t)q * 4u, soff, AUX);
@@ -153,7 +181,7 @@ __device__ __forceinline__ void buf_load_row(__amdgpu_buffer_rsrc_t r, uint32_t 
                 i32x2 b = __builtin_amdgcn_raw_buffer_load_b64(r, (uint32_t)q * 8u, soff, AUX);
                 __builtin_memcpy(&v, &b, 8);
             }
-            out[k] = q0 + k < nq ? v : T(0);
+            out[k] = sure || qk < nq ? v : T(0);
         }
     }
 }
@@ -183,15 +211,16 @@ __device__ __forceinline__ void buf_store_row(__amdgpu_buffer_rsrc_t r, uint32_t
     } else {
 #pragma unroll
         for (int k = 0; k < V; ++k) {
-            if (q0 + k >= nq) continue;
+            const int q = q0 + lane_step<false>(k);
+            if (k >= first_ragged<V, T>() && q >= nq) continue;
             if constexpr (sizeof(T) == 4) {
                 int32_t b;
                 __builtin_memcpy(&b, &in[k], 4);
-                __builtin_amdgcn_raw_buffer_store_b32(b, r, (uint32_t)(q0 + k) * 4u, soff, AUX);
+                __builtin_amdgcn_raw_buffer_store_b32(b, r, (uint32_t)q * 4u, soff, AUX);
             } else {
                 i32x2 b;
                 __builtin_memcpy(&b, &in[k], 8);
-                __builtin_amdgcn_raw_buffer_store_b64(b, r, (uint32_t)(q0 + k) * 8u, soff, AUX);
+                __builtin_amdgcn_raw_buffer_store_b64(b, r, (uint32_t)q * 8u, soff, AUX);
             }
         }
     }
@@ -491,7 +520,7 @@ __device__ __forceinline__ void step_sweep(
     const int32_t xend = (int32_t)(xb + items_per_xcd < ni ? xb + items_per_xcd : ni);
     int32_t c = (int32_t)xb + kx * kCellsPerBlock + wave;
     if (c >= xend) return;
-    const int q0 = lane * V;
+    const int q0 = lane_q0<V, EXACT>(lane);
     const int32_t sh = DENSE ? shift : 0;
     const int chunk = DENSE ? (c & ((1 << sh) - 1)) : 0;
     const uint32_t cb = (uint32_t)chunk * (uint32_t)(kWave * V * sizeof(T));
@@ -531,7 +560,10 @@ __device__ __forceinline__ void step_sweep(
     double wd[DOSE ? V : 1];                    // FP64 weights w_q of the fused dose
     if constexpr (DOSE) {
 #pragma unroll
-        for (int k = 0; k < V; ++k) wd[k] = (EXACT || tq + k < nq) ? wq[tq + k] : 0.0;
+        for (int k = 0; k < V; ++k) {
+            const int q = tq + lane_step<EXACT>(k);
+            wd[k] = (EXACT || q < nq) ? wq[q] : 0.0;
+        }
     }
 
     NbrList<MF> n0, n1, n2;
@@ -628,7 +660,7 @@ __global__ __launch_bounds__(kStepBlock) void k_adjoint(
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t c = lb * kCellsPerBlock + wave;
     if (c >= nc) return;
-    const int q0 = lane * V;
+    const int q0 = lane_q0<V, EXACT>(lane);
 
     T ox[V], oy[V], wi[V];
     load_slice<V, EXACT>(tab, q0, nq, ox);
@@ -912,7 +944,7 @@ __global__ __launch_bounds__(kStepBlock) void k_adjoint_p(
     const int32_t xend = (int32_t)(xb + items_per_xcd < nc ? xb + items_per_xcd : nc);
     int32_t c = (int32_t)xb + kx * kCellsPerBlock + wave;
     if (c >= xend) return;
-    const int q0 = lane * V;
+    const int q0 = lane_q0<V, EXACT>(lane);
 
     AdjCtx<T, GT> cx;
     cx.row_bytes = (uint32_t)nq * sizeof(T);
@@ -975,6 +1007,15 @@ hipError_t dispatch_v(int32_t nq, F&& f) {
     }
     if (v <= 1) return f(std::integral_constant<int, 1>{}, std::false_type{});
     if (v <= 2) return f(std::integral_constant<int, 2>{}, std::false_type{});
+    if constexpr (sizeof(T) == 4) {      // as many as the row needs: no idle accesses
+        switch (v) {
+            case 3: return f(std::integral_constant<int, 3>{}, std::false_type{});
+            case 5: return f(std::integral_constant<int, 5>{}, std::false_type{});
+            case 6: return f(std::integral_constant<int, 6>{}, std::false_type{});
+            case 7: return f(std::integral_constant<int, 7>{}, std::false_type{});
+            default: break;
+        }
+    }
     if (v <= 4) return f(std::integral_constant<int, 4>{}, std::false_type{});
     if (v <= 8) return f(std::integral_constant<int, 8>{}, std::false_type{});
     return f(std::integral_constant<int, 16>{}, std::false_type{});
