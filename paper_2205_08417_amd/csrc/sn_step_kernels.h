@@ -1028,6 +1028,16 @@ struct StepShape {
     int64_t cells_per_xcd;
 };
 
+// Rows of at most 512 bytes put little load on a CU's memory path, and a sweep over them waits for
+// latency: the widths that suit 1 KB rows are then multiplied (79 202 / 178 802 cells x 64 FP32
+// ordinates, step at 3 and 6 blocks per CU: 17.1 / 45.6 and 14.4 / 33.5 us, 100 ordinates 20.1 /
+// 41.8 and 18.1 / 36.6; the second-order update at 2 and 6: its whole step 122 / 253 and 100 / 206
+// us; 182 and 256 ordinates are as fast at 3, respectively 2).
+template <typename T>
+bool small_rows(int32_t nq) {
+    return nq * (int)sizeof(T) <= 512;
+}
+
 inline StepShape step_shape(const snrt_mesh& m, int64_t items, int cpw,
                             int resident_blocks_per_cu, int blocks_per_cu = 0) {
     int bpc = blocks_per_cu > 0 ? blocks_per_cu : tune().step_blocks_per_cu;
@@ -1058,10 +1068,12 @@ hipError_t launch_fwd(const typename GeomOf<T>::type* geom, const snrt_mesh& m, 
                       T* psi_out, const T* S, int shift, hipStream_t st,
                       const double* wq = nullptr, double* dpart = nullptr)
 {
+    const int bpc = tune().step_blocks_per_cu * (small_rows<T>(nq) ? 2 : 1);
     if (dpart) {
         if constexpr (!IMEX) {
             static const int occ = resident_blocks(k_step_dose<V, E, MF, RHO, DENSE, T>);
-            const StepShape sh = step_shape(m, m.nc << shift, shift ? kCellsPerBlock : 1, occ);
+            const StepShape sh =
+                step_shape(m, m.nc << shift, shift ? kCellsPerBlock : 1, occ, bpc);
             hipLaunchKernelGGL((k_step_dose<V, E, MF, RHO, DENSE, T>), dim3(sh.blocks),
                                dim3(kStepBlock), 0, st, geom, m.nc, nq, tab, a, psi_in, psi_out,
                                S, sh.cells_per_xcd, (uint32_t)m.nbf, (int32_t)shift, wq, dpart);
@@ -1070,7 +1082,7 @@ hipError_t launch_fwd(const typename GeomOf<T>::type* geom, const snrt_mesh& m, 
         return hipErrorNotSupported;
     }
     static const int occ = resident_blocks(k_step<V, E, MF, RHO, DENSE, T, IMEX>);
-    const StepShape sh = step_shape(m, m.nc << shift, shift ? kCellsPerBlock : 1, occ);
+    const StepShape sh = step_shape(m, m.nc << shift, shift ? kCellsPerBlock : 1, occ, bpc);
     hipLaunchKernelGGL((k_step<V, E, MF, RHO, DENSE, T, IMEX>), dim3(sh.blocks), dim3(kStepBlock),
                        0, st, geom, m.nc, nq, tab, a, psi_in, psi_out, S, sh.cells_per_xcd,
                        (uint32_t)m.nbf, (int32_t)shift);
