@@ -218,10 +218,11 @@ typedef struct {
  * runs as one launch: the scattering product's tiles update their cells and ordinates, and
  * S = Psi B never reaches the workspace (the environment variable SNRT_STEP_FUSED=0, read
  * once per process, selects the product-then-step form; both give the same bits).
- * Kernels that are functions of Omega_q . Omega_p on a product rule (one weight and 16 or 32
- * equally spaced azimuths per polar node, 8 to 32 polar nodes; checked on the entries when the
- * handle is made) run in every precision mode as FP32 products of the azimuthal modes, in one
- * launch for triangles and quadrilaterals; their product's error is that of FP32 rounding. */
+ * Kernels that are functions of Omega_q . Omega_p on a product rule (one weight per polar node, up
+ * to 16 equally spaced azimuths or an even count up to 32, up to 16 polar nodes or an even count
+ * up to 32; checked on the entries when the handle is made) run in every precision mode as FP32
+ * products of the azimuthal modes where that is faster, in one launch for triangles and
+ * quadrilaterals; their product's error is that of FP32 rounding. */
 snrt_status snrt_step(const snrt_mesh* mesh, const snrt_quad* quad, const snrt_scatter* scatter,
                       const snrt_step_args* args, const float* psi_in, float* psi_out,
                       void* ws, size_t ws_bytes, void* stream);

@@ -16,11 +16,12 @@
 // bounds it now: the vector update (0.10 ms of issue at 1024 ordinates), the matrix instructions
 // (0.065 ms) and the row traffic overlap only across the waves between two barriers.
 //
-// Foldings, so that every contraction is 16 long:
-//   * azimuth (na = 32): x_l +- x_{l+16}; the sums carry the even modes, the differences the odd;
+// Foldings, so that every contraction is at most 16 long (shorter ones are padded with zeros in
+// the operands, empty azimuthal slots hold zeros):
+//   * azimuth (16 < na <= 32, even): x_l +- x_{l+na/2}; the sums carry the even modes, the
+//     differences the odd;
 //   * polar (16 < np <= 32, np even, kernel unchanged by mu -> -mu): x_k +- x_{np-1-k}, k < np/2.
-// A row is then NC = 1, 2 or 4 classes of 16 polar x 16 azimuthal slots (np or np/2 below 16:
-// zero-padded operands, clamped lanes).
+// A row is then 1, 2 or 4 classes of 16 polar x 16 azimuthal slots.
 //
 // One wave owns one cell (16 < np, 32 azimuths: one polar half of a cell, two waves per cell).
 // Rows are read, updated and written in memory order, 1 KB per access of a wave; the matrix
@@ -65,48 +66,71 @@ __device__ __forceinline__ f32x4 mfma4(const f32x4& a, const f32x4& b, f32x4 acc
 
 // How a row is cut: AZ azimuthal classes, MU polar halves, WPC waves per cell, SEG segments per
 // wave, ITEMS mode pairs per wave in stage 2 (each with MU matrices).
-template <int AZ_, int MU_>
+// RV = 0: 16 AZ azimuths, rows in whole 16-byte pieces; else the azimuths do not fill their slots
+// and a lane owns RV (even) ordinates of a wave's piece of the row, 64 apart (as in the step
+// kernel's striped rows), the last RAGGED of which may lie past its end.
+template <int AZ_, int MU_, int RV_ = 0>
 struct Shape {
-    static constexpr int AZ = AZ_, MU = MU_;
+    static constexpr int AZ = AZ_, MU = MU_, RV = RV_;
     static constexpr int WPC = AZ * MU == 4 ? 2 : 1;
     static constexpr int SEG = AZ * MU / WPC;
     static constexpr int WAVES = kCells * WPC;
     static constexpr int THREADS = WAVES * kWave;
     static constexpr int ITEMS = AZ * 8 / WAVES;
     static constexpr int LDS = AZ * MU * kClass;     // floats of one buffer
-    // class and polar half of segment i
+    static constexpr int RAGGED = 2;
+    // class of segment i; whether a lane has ordinate v of segment i at all
     static constexpr int az(int i) { return i % AZ; }
+    static constexpr bool has(int i, int v) { return RV == 0 || 4 * i + v < RV; }
 };
 
 // The place of a wave's lane: its cell of the tile; for the row in memory order the byte offset
-// (off) and LDS granule (mem) of its four ordinates per segment and whether they exist (lanes
-// past the end repeat the last ones and store nothing); for the row in matrix order the LDS
-// granule (mat) of each segment and whether the lane's polar slot exists (valid).
+// (off) and LDS place (mem) of its ordinates and which exist (those past the end repeat the last
+// one and are not stored); for the row in matrix order the LDS granule (mat) of each segment and
+// whether the lane's polar slot exists (valid).
 template <typename P>
 struct Lane {
-    int wave, lane, l4, kk, cell, mu0;
-    bool valid, exists[P::SEG];
-    uint32_t off[P::SEG];
-    int mem[P::SEG], mat[P::SEG];
-    __device__ __forceinline__ Lane(int np) {
+    static constexpr bool RAG = P::RV != 0;
+    static constexpr int N = RAG ? P::RV : P::SEG;               // pieces in memory order
+    int wave, lane, l4, kk, cell, mu0, half;
+    bool valid, exists_[RAG ? P::RAGGED : P::SEG];
+    uint32_t off[RAG ? 1 + P::RAGGED : P::SEG];
+    int mem[N], mat[P::SEG];
+    __device__ __forceinline__ Lane(const AzOperand& op) {
         wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         lane = threadIdx.x & (kWave - 1);
         kk = lane & 15;
         l4 = lane >> 4;
         cell = wave & 7;
         mu0 = P::WPC == 2 ? wave >> 3 : 0;
+        const int np = op.np, na = RAG ? op.na : 16 * P::AZ;
+        half = na / P::AZ;
         const int h = P::MU == 2 ? np / 2 : np;
         const int rows = P::WPC == 2 ? h : np, k0 = mu0 * h;      // polar rows of this wave
-        constexpr int na = 16 * P::AZ;
         valid = kk < h;
         const int k = valid ? kk : h - 1;
+        off[0] = 4u * (uint32_t)(k0 * na + lane);
+#pragma unroll
+        for (int n = 0; n < N; ++n) {
+            int e = RAG ? n * kWave + lane : n * 256 + 4 * lane;
+            const bool in = e < rows * na;
+            e = in ? e : rows * na - (RAG ? 1 : 4);
+            const int r = e / na, l = e % na;
+            if constexpr (RAG) {
+                if (n >= P::RV - P::RAGGED) {
+                    exists_[n - (P::RV - P::RAGGED)] = in;
+                    off[1 + n - (P::RV - P::RAGGED)] = 4u * (uint32_t)(k0 * na + e);
+                }
+                const int s = l < half ? l : 16 + l - half;       // azimuthal slot
+                mem[n] = 4 * granule(r, s >> 2) + (s & 3);
+            } else {
+                exists_[n] = in;
+                off[n] = 4u * (uint32_t)(k0 * na + e);
+                mem[n] = granule(r, l >> 2);
+            }
+        }
 #pragma unroll
         for (int i = 0; i < P::SEG; ++i) {
-            int e = i * 256 + 4 * lane;
-            exists[i] = e < rows * na;
-            e = exists[i] ? e : rows * na - 4;
-            off[i] = 4u * (uint32_t)(k0 * na + e);
-            mem[i] = granule(e / na, (e % na) / 4);
             const int mu = mu0 + i / P::AZ;
             mat[i] = granule((mu ? np - 1 - k : k) - k0, 4 * P::az(i) + l4);
         }
@@ -117,28 +141,16 @@ struct Lane {
         constexpr int G = 4 * P::AZ;
         return r * G + (g ^ ((r >> (P::AZ == 2 ? 1 : 2)) & (G - 1)));
     }
-};
-
-// Between the two orders through the wave's LDS corner (LDS accesses of one wave stay in order).
-template <typename P>
-__device__ __forceinline__ void to_matrix_order(f32x4 (&x)[P::SEG], const f32x4 (&p)[P::SEG],
-                                                const Lane<P>& ln, f32x4* corner) {
-#pragma unroll
-    for (int i = 0; i < P::SEG; ++i)
-        if (ln.exists[i]) corner[ln.mem[i]] = p[i];
-#pragma unroll
-    for (int i = 0; i < P::SEG; ++i) x[i] = corner[ln.mat[i]];
-}
-template <typename P>
-__device__ __forceinline__ void to_memory_order(f32x4 (&x)[P::SEG], const Lane<P>& ln,
-                                                f32x4* corner) {
-    if (ln.valid) {
-#pragma unroll
-        for (int i = 0; i < P::SEG; ++i) corner[ln.mat[i]] = x[i];
+    // ordinate v of segment i: whether the lane has it, and its byte offset in a row (striped)
+    __device__ __forceinline__ bool exists(int i, int v) const {
+        if constexpr (!RAG) return exists_[i];
+        const int n = 4 * i + v;
+        return P::has(i, v) && (n < P::RV - P::RAGGED || exists_[n - (P::RV - P::RAGGED)]);
     }
-#pragma unroll
-    for (int i = 0; i < P::SEG; ++i) x[i] = corner[ln.mem[i]];
-}
+    __device__ __forceinline__ uint32_t at(int n) const {
+        return n < P::RV - P::RAGGED ? off[0] + 256u * n : off[1 + n - (P::RV - P::RAGGED)];
+    }
+};
 
 __device__ __forceinline__ f32x4 load4(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
     return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
@@ -148,6 +160,100 @@ __device__ __forceinline__ void store4(__amdgpu_buffer_rsrc_t r, uint32_t voff, 
                                        const f32x4& v) {
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4, v), r, voff, soff,
                                            kAuxStream);
+}
+
+// Segment i of a row in memory order.
+template <typename P>
+__device__ __forceinline__ f32x4 load_piece(__amdgpu_buffer_rsrc_t r, const Lane<P>& ln, int i,
+                                            uint32_t row) {
+    if constexpr (P::RV == 0) {
+        return load4(r, ln.off[i], row);
+    } else {
+        f32x4 x{0, 0, 0, 0};
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (P::has(i, v))
+                x[v] = __builtin_bit_cast(
+                    float, __builtin_amdgcn_raw_buffer_load_b32(r, ln.at(4 * i + v), row, 0));
+        return x;
+    }
+}
+template <typename P>
+__device__ __forceinline__ void store_piece(__amdgpu_buffer_rsrc_t r, const Lane<P>& ln, int i,
+                                            uint32_t row, const f32x4& x) {
+    if constexpr (P::RV == 0) {
+        if (ln.exists(i, 0)) store4(r, ln.off[i], row, x);
+    } else {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const float xv = x[v];
+            if (ln.exists(i, v))
+                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int32_t, xv), r,
+                                                      ln.at(4 * i + v), row, kAuxStream);
+        }
+    }
+}
+// The same segment of a per-ordinate table in LDS (padded by a wave's width).
+template <typename P, typename T>
+__device__ __forceinline__ void table_piece(const T* tab, const Lane<P>& ln, int i, T (&x)[4]) {
+    if constexpr (P::RV == 0) {
+        __builtin_memcpy(x, __builtin_assume_aligned(tab + ln.off[i] / 4, 16), sizeof(x));
+    } else {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            x[v] = P::has(i, v) ? tab[ln.off[0] / 4 + kWave * (4 * i + v)] : T(0);
+    }
+}
+
+// Between the two orders through the wave's LDS corner (LDS accesses of one wave stay in order).
+// Azimuthal slots that no ordinate fills hold zeros: cleared at the start, and written as zeros
+// even where a cell's modes are not finite.
+template <typename P>
+__device__ __forceinline__ void clear_corner(const Lane<P>& ln, f32x4* corner) {
+    if constexpr (P::RV != 0) {
+#pragma unroll
+        for (int i = 0; i < P::SEG; ++i) corner[i * kWave + ln.lane] = f32x4{0, 0, 0, 0};
+    }
+}
+template <typename P>
+__device__ __forceinline__ void to_matrix_order(f32x4 (&x)[P::SEG], const f32x4 (&p)[P::SEG],
+                                                const Lane<P>& ln, f32x4* corner) {
+#pragma unroll
+    for (int i = 0; i < P::SEG; ++i) {
+        if constexpr (P::RV == 0) {
+            if (ln.exists(i, 0)) corner[ln.mem[i]] = p[i];
+        } else {
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                if (ln.exists(i, v)) reinterpret_cast<float*>(corner)[ln.mem[4 * i + v]] = p[i][v];
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < P::SEG; ++i) x[i] = corner[ln.mat[i]];
+}
+template <typename P>
+__device__ __forceinline__ void to_memory_order(f32x4 (&x)[P::SEG], const Lane<P>& ln,
+                                                f32x4* corner) {
+    if constexpr (P::RV != 0) {
+#pragma unroll
+        for (int i = 0; i < P::SEG; ++i)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) x[i][v] = 4 * ln.l4 + v < ln.half ? x[i][v] : 0.0f;
+    }
+    if (ln.valid) {
+#pragma unroll
+        for (int i = 0; i < P::SEG; ++i) corner[ln.mat[i]] = x[i];
+    }
+#pragma unroll
+    for (int i = 0; i < P::SEG; ++i) {
+        if constexpr (P::RV == 0) {
+            x[i] = corner[ln.mem[i]];
+        } else {
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                x[i][v] = P::has(i, v) ? reinterpret_cast<float*>(corner)[ln.mem[4 * i + v]] : 0.0f;
+        }
+    }
 }
 
 // Azimuthal fold of a wave's segments and its inverse: the same sums.
@@ -375,14 +481,38 @@ struct CellData {
 };
 static_assert(offsetof(CellGeom32, n) == 16 && offsetof(CellGeom32, inv_area) == 48, "record words");
 
-// The ordinate table's two direction rows into LDS (padded to whole segments).
+// Per-ordinate tables in LDS, padded by a wave's width: the two direction rows, and for striped
+// rows with a dose the FP64 weights (whole pieces have one weight per segment, in registers).
 template <typename P>
-__device__ __forceinline__ void load_table(const float* __restrict__ tab, int nq, f32x4* dst) {
-    constexpr int N = P::AZ * P::MU * kWave;
-    for (int i = threadIdx.x; i < nq / 4; i += P::THREADS) {
-        dst[i] = reinterpret_cast<const f32x4*>(tab)[i];
-        dst[N + i] = reinterpret_cast<const f32x4*>(tab + nq)[i];
+constexpr int kTable = P::AZ * P::MU * 256 + (P::RV ? kWave : 0);
+template <typename P, typename T>
+__device__ __forceinline__ void load_table(const T* __restrict__ tab, int nq, T* dst) {
+    for (int i = threadIdx.x; i < nq; i += P::THREADS) dst[i] = tab[i];
+}
+template <typename P>
+__device__ __forceinline__ void load_dirs(const float* __restrict__ tab, int nq, float* dst) {
+    load_table<P>(tab, nq, dst);
+    load_table<P>(tab + nq, nq, dst + kTable<P>);
+}
+// sum over a lane's ordinates of w p, FP64
+template <typename P>
+__device__ __forceinline__ double weighted(const f32x4 (&p)[P::SEG], const double* wd,
+                                           const Lane<P>& ln) {
+    double sd = 0.0;
+#pragma unroll
+    for (int i = 0; i < P::SEG; ++i) {
+        if constexpr (P::RV == 0) {
+            sd += wd[i] *
+                  (((double)p[i][0] + (double)p[i][1]) + ((double)p[i][2] + (double)p[i][3]));
+        } else {
+            double w[4];
+            table_piece<P>(wd, ln, i, w);
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                if (ln.exists(i, v)) sd += w[v] * (double)p[i][v];
+        }
     }
+    return sd;
 }
 
 // Sum of a double over the wave, the same in every lane: DPP swaps inside rows of 16, the row
@@ -409,25 +539,27 @@ __device__ __forceinline__ double wave_sum64(double v) {
 }
 
 // The upwind candidate across a face to neighbour j of cell c (the step kernel's branch-free rule).
-__device__ __forceinline__ f32x4 load_face(int32_t j, int32_t c, uint32_t voff,
+template <typename P>
+__device__ __forceinline__ f32x4 load_face(int32_t j, int32_t c, const Lane<P>& ln, int i,
                                            const FwdCtx<float>& x) {
     const bool bnd = j < 0;
     const int32_t bidx = x.dirichlet ? -1 - j : c;
-    return load4(bnd && x.dirichlet ? x.inflow : x.psi, voff,
-                 (uint32_t)(bnd ? bidx : j) * x.row_bytes);
+    return load_piece<P>(bnd && x.dirichlet ? x.inflow : x.psi, ln, i,
+                         (uint32_t)(bnd ? bidx : j) * x.row_bytes);
 }
 
 // The upwind sum over the faces for one segment, in the explicit FMAs of fwd_compute; up: the
 // upwind candidates times their ghost scales.
-template <int MF, bool RHO>
-__device__ __forceinline__ f32x4 flux4(const f32x4& p, float irho, const float (&nx)[MF],
+template <typename P, int MF, bool RHO>
+__device__ __forceinline__ f32x4 flux4(int i, const f32x4& p, float irho, const float (&nx)[MF],
                                        const float (&ny)[MF], const f32x4 (&up)[MF],
-                                       const f32x4& ox, const f32x4& oy) {
+                                       const float (&ox)[4], const float (&oy)[4]) {
     f32x4 acc{0, 0, 0, 0};
 #pragma unroll
     for (int f = 0; f < MF; ++f)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
+            if (!P::has(i, v)) continue;
             const float u = RHO ? p[v] * irho : p[v];
             const float s = __builtin_fmaf(nx[f], ox[v], ny[f] * oy[v]);
             acc[v] = __builtin_fmaf(s, s > 0.0f ? u : up[f][v], acc[v]);
@@ -477,10 +609,11 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_product(AzOperand opd,
     __shared__ __attribute__((aligned(16))) float lds[2][P::LDS];
     __shared__ f32x4 second[P::MU * kWave];
     __shared__ f32x4 rows[P::WAVES][P::SEG * kWave];
-    const Lane<P> ln(opd.np);
+    const Lane<P> ln(opd);
     const Ops<P> op(mats, ln);
     const Fourier<P, false> fr(opd, ln, nullptr);
     load_second<P>(mats, second);
+    clear_corner<P>(ln, rows[ln.wave]);
     const uint32_t row_bytes = (uint32_t)(opd.np * opd.na) * 4u;
     const auto rin = make_rsrc(in, (uint32_t)nc * row_bytes);
     const auto rout = make_rsrc(out, (uint32_t)nc * row_bytes);
@@ -490,7 +623,8 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_product(AzOperand opd,
     auto fetch = [&](int32_t t) {
         const Cell c(t < tl.end ? t : tl.end - 1, ln.cell, nc);
 #pragma unroll
-        for (int i = 0; i < P::SEG; ++i) nx[i] = load4(rin, ln.off[i], (uint32_t)c.c * row_bytes);
+        for (int i = 0; i < P::SEG; ++i)
+            nx[i] = load_piece<P>(rin, ln, i, (uint32_t)c.c * row_bytes);
     };
     fetch(tl.t);
     for (int b = 0; tl.t < tl.end; tl.t += tl.stride, b ^= 1) {
@@ -508,7 +642,7 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_product(AzOperand opd,
         to_memory_order<P>(x, ln, rows[ln.wave]);
 #pragma unroll
         for (int i = 0; i < P::SEG; ++i)
-            if (c.real && ln.exists[i]) store4(rout, ln.off[i], (uint32_t)c.c * row_bytes, x[i]);
+            if (c.real) store_piece<P>(rout, ln, i, (uint32_t)c.c * row_bytes, x[i]);
     }
 }
 
@@ -529,20 +663,23 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_step(AzOperand opd, StepEp
     __shared__ __attribute__((aligned(16))) float lds[2][P::LDS];
     __shared__ double dsum[2][DOSE && P::WPC == 2 ? kCells : 1];
     __shared__ f32x4 second[P::MU * kWave];
-    __shared__ f32x4 dirs[2 * P::AZ * P::MU * kWave];
+    __shared__ __attribute__((aligned(16))) float dirs[2 * kTable<P>];
     __shared__ f32x4 rows[P::WAVES][SEG * kWave];
-    const Lane<P> ln(opd.np);
+    const Lane<P> ln(opd);
     const Ops<P> op(opd.fwd, ln);
     const Fourier<P, false> fr(opd, ln, nullptr);
     load_second<P>(opd.fwd, second);
-    load_table<P>(se.tab, se.nq, dirs);
+    load_dirs<P>(se.tab, se.nq, dirs);
+    clear_corner<P>(ln, rows[ln.wave]);
     const FwdCtx<float> cx = make_ctx(se.a, se.psi_in, se.psi_out, se.nc, se.nq, se.nbf);
     const CellWords words(ln.lane, se.a, cx.src_arr, DOSE ? dose : nullptr);
-    double wd[DOSE ? SEG : 1];
-    if constexpr (DOSE) {
+    __shared__ double wtab[DOSE && P::RV ? kTable<P> : 1];
+    double wd[DOSE ? SEG : 1];                                   // one weight per polar node
+    if constexpr (DOSE && P::RV != 0) {
+        load_table<P>(se.wq, se.nq, wtab);
+    } else if constexpr (DOSE) {
 #pragma unroll
-        for (int i = 0; i < SEG; ++i)
-            wd[i] = ln.exists[i] ? se.wq[ln.off[i] / 4] : 0.0;   // one weight per polar node
+        for (int i = 0; i < SEG; ++i) wd[i] = ln.exists(i, 0) ? se.wq[ln.off[i] / 4] : 0.0;
     }
     Tiles tl((int32_t)((se.nc + kCells - 1) / kCells));
     if (tl.t >= tl.end) return;
@@ -551,7 +688,7 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_step(AzOperand opd, StepEp
     auto own = [&](f32x4 (&p)[SEG], int32_t t) {
         const uint32_t row = (uint32_t)cell_of(t).c * cx.row_bytes;
 #pragma unroll
-        for (int i = 0; i < SEG; ++i) p[i] = load4(cx.psi, ln.off[i], row);
+        for (int i = 0; i < SEG; ++i) p[i] = load_piece<P>(cx.psi, ln, i, row);
     };
     f32x4 p[SEG], pn[SEG], up[SEG][MF];
     float rec = record(tl.t), mat = words.template material<MF>(rec, cell_of(tl.t).c, ln.lane);
@@ -560,7 +697,7 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_step(AzOperand opd, StepEp
     for (int i = 0; i < SEG; ++i)
 #pragma unroll
         for (int f = 0; f < MF; ++f)
-            up[i][f] = load_face(CellWords::word(rec, f), cell_of(tl.t).c, ln.off[i], cx);
+            up[i][f] = load_face<P>(CellWords::word(rec, f), cell_of(tl.t).c, ln, i, cx);
     float recn = record(tl.t + tl.stride);
     __syncthreads();                       // second, dirs
     for (int b = 0;; b ^= 1) {
@@ -579,10 +716,7 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_step(AzOperand opd, StepEp
         });
         double sd = 0.0;
         if constexpr (DOSE) {
-#pragma unroll
-            for (int i = 0; i < SEG; ++i)
-                sd += wd[i] * (((double)p[i][0] + (double)p[i][1]) +
-                               ((double)p[i][2] + (double)p[i][3]));
+            sd = weighted<P>(p, P::RV ? wtab : wd, ln);
             sd = wave_sum64(sd);
             if (P::WPC == 2 && ln.mu0 == 1 && ln.lane == 0) dsum[b][ln.cell] = sd;
         }
@@ -604,24 +738,26 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_step(AzOperand opd, StepEp
         const uint32_t row = (uint32_t)c.c * cx.row_bytes;
 #pragma unroll
         for (int i = 0; i < SEG; ++i) {
-            const f32x4* dir = dirs + ln.off[i] / 16;
-            const f32x4 ox = dir[0], oy = dir[P::AZ * P::MU * kWave];
+            float ox[4], oy[4];
+            table_piece<P>(dirs, ln, i, ox);
+            table_piece<P>(dirs + kTable<P>, ln, i, oy);
             if (cd.scaled) {
 #pragma unroll
                 for (int f = 0; f < MF; ++f) up[i][f] *= cd.ghost[f];
             }
-            const f32x4 acc = flux4<MF, RHO>(p[i], cd.irho, cd.nx, cd.ny, up[i], ox, oy);
+            const f32x4 acc = flux4<P, MF, RHO>(i, p[i], cd.irho, cd.nx, cd.ny, up[i], ox, oy);
             f32x4 o;
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
+                if (!P::has(i, v)) continue;
                 const float e =
                     __builtin_fmaf(-cd.cflux, acc[v], __builtin_fmaf(-p[i][v], cd.cabs, p[i][v]));
                 o[v] = __builtin_fmaf(cx.src_mul, cd.srcv, __builtin_fmaf(cd.cscat, x[i][v], e));
             }
-            if (c.real && ln.exists[i]) store4(cx.out, ln.off[i], row, o);
+            if (c.real) store_piece<P>(cx.out, ln, i, row, o);
 #pragma unroll
             for (int f = 0; f < MF; ++f)
-                up[i][f] = load_face(CellWords::word(recn, f), cn.c, ln.off[i], cx);
+                up[i][f] = load_face<P>(CellWords::word(recn, f), cn.c, ln, i, cx);
         }
         tl.t += tl.stride;
         if (tl.t >= tl.end) break;
@@ -710,25 +846,29 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_adjoint(AzOperand opd, AzA
     constexpr int SEG = P::SEG;
     __shared__ __attribute__((aligned(16))) float lds[2][P::LDS];
     __shared__ f32x4 second[P::MU * kWave];
-    __shared__ f32x4 dirs[2 * P::AZ * P::MU * kWave];
+    __shared__ __attribute__((aligned(16))) float dirs[2 * kTable<P>];
     __shared__ f32x4 rows[P::WAVES][SEG * kWave];
     __shared__ float gsum[2][P::WPC == 2 ? P::WAVES : 1][4];
-    const Lane<P> ln(opd.np);
+    const Lane<P> ln(opd);
     __shared__ f32x4 ftab[2 * P::AZ * kWave];
     const Ops<P> op(opd.adj, ln);
     const Fourier<P, true> fr(opd, ln, ftab);
     load_second<P>(opd.adj, second);
-    load_table<P>(e.tab, e.nq, dirs);
+    load_dirs<P>(e.tab, e.nq, dirs);
+    clear_corner<P>(ln, rows[ln.wave]);
     const StepArgs32& a = e.a;
     const uint32_t row_bytes = (uint32_t)e.nq * 4u, state_bytes = (uint32_t)e.nc * row_bytes;
     const auto rlam = make_rsrc(e.lam_np1, state_bytes);
     const auto rpsi = make_rsrc(e.psi_n, state_bytes);
     const auto rout = make_rsrc(e.lam_n, state_bytes);
     const AdjWords<GT> words(ln.lane, e, g_t, g_s, g_r);
-    double wd[DA ? SEG : 1];
-    if constexpr (DA) {
+    __shared__ double wtab[DA && P::RV ? kTable<P> : 1];
+    double wd[DA ? SEG : 1];                                     // one weight per polar node
+    if constexpr (DA && P::RV != 0) {
+        load_table<P>(e.da.w, e.nq, wtab);
+    } else if constexpr (DA) {
 #pragma unroll
-        for (int i = 0; i < SEG; ++i) wd[i] = e.da.w[ln.off[i] / 4];      // one per polar node
+        for (int i = 0; i < SEG; ++i) wd[i] = e.da.w[ln.off[i] / 4];
     }
     Tiles tl((int32_t)((e.nc + kCells - 1) / kCells));
     if (tl.t >= tl.end) return;
@@ -737,17 +877,17 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_adjoint(AzOperand opd, AzA
     auto own = [&](f32x4 (&p)[SEG], int32_t t) {
         const uint32_t row = (uint32_t)cell_of(t).c * row_bytes;
 #pragma unroll
-        for (int i = 0; i < SEG; ++i) p[i] = load4(rlam, ln.off[i], row);
+        for (int i = 0; i < SEG; ++i) p[i] = load_piece<P>(rlam, ln, i, row);
     };
     // the rows of segment i that the update alone needs: psi and the neighbours' lambda (a
     // boundary face reads the cell's own row, with weight 0)
     f32x4 l[SEG], lnx[SEG], p[SEG], nl[SEG][MF];
     auto others = [&](int i, float rec, int32_t c) {
-        p[i] = load4(rpsi, ln.off[i], (uint32_t)c * row_bytes);
+        p[i] = load_piece<P>(rpsi, ln, i, (uint32_t)c * row_bytes);
 #pragma unroll
         for (int f = 0; f < MF; ++f) {
             const int32_t j = CellWords::word(rec, f);
-            nl[i][f] = load4(rlam, ln.off[i], (uint32_t)(j >= 0 ? j : c) * row_bytes);
+            nl[i][f] = load_piece<P>(rlam, ln, i, (uint32_t)(j >= 0 ? j : c) * row_bytes);
         }
     };
     auto add_gradients = [&](float mat, int32_t c, float pt, float ps, float pr, float irho) {
@@ -813,11 +953,16 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_adjoint(AzOperand opd, AzA
         float pt = 0.0f, ps = 0.0f, pr = 0.0f;
 #pragma unroll
         for (int i = 0; i < SEG; ++i) {
-            const f32x4 ox = dirs[ln.off[i] / 16], oy = dirs[ln.off[i] / 16 + P::AZ * P::MU * kWave];
+            float ox[4], oy[4];
+            double w[4];
+            table_piece<P>(dirs, ln, i, ox);
+            table_piece<P>(dirs + kTable<P>, ln, i, oy);
+            if constexpr (DA && P::RV != 0) table_piece<P>(wtab, ln, i, w);
             f32x4 o;
             float t0 = 0.0f, s0 = 0.0f, r0 = 0.0f;
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
+                if (!P::has(i, v)) continue;
                 float xs = 0.0f;
 #pragma unroll
                 for (int f = 0; f < MF; ++f) {
@@ -828,17 +973,20 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_adjoint(AzOperand opd, AzA
                 const float lv = l[i][v], g = x[i][v];
                 o[v] = __builtin_fmaf(cscat, g,
                                       __builtin_fmaf(-cstream, xs, __builtin_fmaf(-lv, cabs, lv)));
-                t0 = __builtin_fmaf(lv, p[i][v], t0);
-                s0 = __builtin_fmaf(p[i][v], g, s0);
-                r0 = __builtin_fmaf(p[i][v], xs, r0);
-                if constexpr (DA) o[v] = (float)__builtin_fma(gd, wd[i], (double)o[v]);
+                if (P::RV == 0 || ln.exists(i, v)) {
+                    t0 = __builtin_fmaf(lv, p[i][v], t0);
+                    s0 = __builtin_fmaf(p[i][v], g, s0);
+                    r0 = __builtin_fmaf(p[i][v], xs, r0);
+                }
+                if constexpr (DA)
+                    o[v] = (float)__builtin_fma(gd, P::RV ? w[v] : wd[i], (double)o[v]);
             }
-            if (ln.exists[i]) {
+            if (P::RV != 0 || ln.exists(i, 0)) {
                 pt += t0;
                 ps += s0;
                 pr += r0;
             }
-            if (c.real && ln.exists[i]) store4(rout, ln.off[i], (uint32_t)c.c * row_bytes, o);
+            if (c.real) store_piece<P>(rout, ln, i, (uint32_t)c.c * row_bytes, o);
             others(i, recn, cn.c);
         }
         pt = wave_sum_dpp(pt);
@@ -887,9 +1035,9 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_imex(AzOperand opd, StepEp
     constexpr int SEG = P::SEG;
     __shared__ __attribute__((aligned(16))) float lds[2][P::LDS];
     __shared__ f32x4 second[2][P::MU * kWave];
-    __shared__ f32x4 dirs[2 * P::AZ * P::MU * kWave];
+    __shared__ __attribute__((aligned(16))) float dirs[2 * kTable<P>];
     __shared__ f32x4 rows[P::WAVES][SEG * kWave];
-    const Lane<P> ln(opd.np);
+    const Lane<P> ln(opd);
     __shared__ f32x4 ftab[2 * P::AZ * kWave];
     const Ops<P> op(opd.e1, ln);
     const Fourier<P, true> fr(opd, ln, ftab);
@@ -906,7 +1054,8 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_imex(AzOperand opd, StepEp
         }
     load_second<P>(opd.e1, second[0]);
     load_second<P>(opd.e2, second[1]);
-    load_table<P>(se.tab, se.nq, dirs);
+    load_dirs<P>(se.tab, se.nq, dirs);
+    clear_corner<P>(ln, rows[ln.wave]);
     const StepArgs32& a = se.a;
     const FwdCtx<float> cx = make_ctx(a, se.psi_in, se.psi_out, se.nc, se.nq, se.nbf);
     const CellWords words(ln.lane, a, cx.src_arr, nullptr);
@@ -923,10 +1072,10 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_imex(AzOperand opd, StepEp
     auto fetch = [&](float rec, int32_t c) {
 #pragma unroll
         for (int i = 0; i < SEG; ++i) {
-            p[i] = load4(cx.psi, ln.off[i], (uint32_t)c * cx.row_bytes);
+            p[i] = load_piece<P>(cx.psi, ln, i, (uint32_t)c * cx.row_bytes);
 #pragma unroll
             for (int f = 0; f < MF; ++f)
-                up[i][f] = load_face(CellWords::word(rec, f), c, ln.off[i], cx);
+                up[i][f] = load_face<P>(CellWords::word(rec, f), c, ln, i, cx);
         }
     };
     float rec = record(tl.t), mat = words.template material<MF>(rec, cell_of(tl.t).c, ln.lane);
@@ -942,17 +1091,20 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_imex(AzOperand opd, StepEp
         f32x4 r[SEG], x[SEG];
 #pragma unroll
         for (int i = 0; i < SEG; ++i) {
-            const f32x4* dir = dirs + ln.off[i] / 16;
-            const f32x4 ox = dir[0], oy = dir[P::AZ * P::MU * kWave];
+            float ox[4], oy[4];
+            table_piece<P>(dirs, ln, i, ox);
+            table_piece<P>(dirs + kTable<P>, ln, i, oy);
             if (cd.scaled) {
 #pragma unroll
                 for (int f = 0; f < MF; ++f) up[i][f] *= cd.ghost[f];
             }
-            const f32x4 acc = flux4<MF, RHO>(p[i], cd.irho, cd.nx, cd.ny, up[i], ox, oy);
+            const f32x4 acc = flux4<P, MF, RHO>(i, p[i], cd.irho, cd.nx, cd.ny, up[i], ox, oy);
 #pragma unroll
             for (int v = 0; v < 4; ++v)
-                r[i][v] = __builtin_fmaf(cx.src_mul, cd.srcv,
-                                         __builtin_fmaf(-cd.cflux, acc[v], p[i][v]));
+                r[i][v] = P::has(i, v)
+                              ? __builtin_fmaf(cx.src_mul, cd.srcv,
+                                               __builtin_fmaf(-cd.cflux, acc[v], p[i][v]))
+                              : 0.0f;
         }
         const float matn = words.template material<MF>(recn, cn.c, ln.lane);
         const float stn = column(a.sigma_t, tl.t + tl.stride);
@@ -981,8 +1133,7 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_imex(AzOperand opd, StepEp
             f32x4 o;
 #pragma unroll
             for (int v = 0; v < 4; ++v) o[v] = __builtin_fmaf(-s[v], y, s[v]);
-            if (c.real && ln.exists[i])
-                store4(cx.out, ln.off[i], (uint32_t)c.c * cx.row_bytes, o);
+            if (c.real) store_piece<P>(cx.out, ln, i, (uint32_t)c.c * cx.row_bytes, o);
         }
         tl.t += tl.stride;
         if (tl.t >= tl.end) break;
@@ -1015,8 +1166,24 @@ int az_resident(K kernel, int threads) {
 // f(shape) for the class shape of an operand.
 template <typename F>
 hipError_t by_shape(const AzOperand& op, F&& f) {
-    if (op.na == 32) return op.np > 16 ? f(Shape<2, 2>{}) : f(Shape<2, 1>{});
-    return op.np > 16 ? f(Shape<1, 2>{}) : f(Shape<1, 1>{});
+    const bool two = op.na > 16, fold = op.np > 16;
+    if (op.na == (two ? 32 : 16)) {
+        if (two) return fold ? f(Shape<2, 2>{}) : f(Shape<2, 1>{});
+        return fold ? f(Shape<1, 2>{}) : f(Shape<1, 1>{});
+    }
+    // ordinates of a wave's piece of the row per lane
+    const int rv = ((two && fold ? op.np / 2 : op.np) * op.na + kWave - 1) / kWave;
+    auto wide = [&](auto az, auto mu) {
+        constexpr int AZ = decltype(az)::value, MU = decltype(mu)::value;
+        if (rv <= 2) return f(Shape<AZ, MU, 2>{});
+        if (rv <= 4) return f(Shape<AZ, MU, 4>{});
+        return rv <= 6 ? f(Shape<AZ, MU, 6>{}) : f(Shape<AZ, MU, 8>{});
+    };
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    if (two) return fold ? wide(I2{}, I2{}) : wide(I2{}, I1{});
+    if (fold) return wide(I1{}, I2{});
+    return rv <= 2 ? f(Shape<1, 1, 2>{}) : f(Shape<1, 1, 4>{});
 }
 
 }  // namespace az

@@ -838,15 +838,24 @@ int32_t* ws_rexp(const DenseB& B, float* after_S, int64_t M) {
     return reinterpret_cast<int32_t*>(after_S + (B.chain == 2 ? (size_t)M * B.mid : 0));
 }
 
-// Whether the FP32 state's scattering product runs through the azimuthal modes: the handle has
-// them, and half of the matrix kernels' 16 polar slots are not padding.  With 8 polar nodes
-// half are: the step then takes what 16 nodes take, which the FP32 product never undercuts (51 842
-// cells, 8 x 32: 53 against 108 us) and the BF16 / FP16 products do on large meshes only, where
-// their 256-row tiles fill the device (51 842 cells, 8 x 32, BF16x3 / x1: 53 against 48 / 37 us;
-// 3 042 cells: 8 against 41 / 33 us; the two lines cross between 32 000 and 45 000 cells).
+// Whether the FP32 state's scattering product runs through the azimuthal modes, where the handle
+// has them.  Their kernels work on 16 or 32 azimuthal times 16 or 32 polar slots, padded, so the
+// line is how much of the slots the ordinates fill.  us per step, modes against general products:
+//   3 042 cells (short launches decide): every shape and precision measured, from 4 x 5 (8.0 :
+//     11.0 FP32) over 4 x 32 (8.2 : 24.7 FP32, 12.1 BF16x1) to 32 x 32 (13.7 : 258 FP32, 54 BF16x1);
+//   51 842 cells, FP32: 4 x 5 (8 % filled) 28.1 : 23.7, 6 x 8 (19 %) 28.4 : 32.3 but its product
+//     alone 18.6 : 15.4, 5 x 20 (20 %) 44.6 : 67.1, 8 x 8 (25 %) 28.8 : 35.8, 10 x 10 30.2 : 66.8;
+//     a width the matrix-core FP32 product takes, 4 x 32 (25 %) 49.3 : 44.5;
+//   51 842 cells, BF16x3: 8 x 20 (31 %) 50.4 : 44.2, 6 x 32 (38 %) 50.6 : 51.4, 8 x 32 (50 %) 53.3 :
+//     48.5, 8 x 16 (50 %) 33.0 : 33.9, 16 x 20 (63 %) 60.6 : 111.6, 12 x 16 (75 %) 34.1 : 94.8
+//     (BF16x1: 16 x 20 83.5, 12 x 16 83.9, 16 x 16 34.4 : 37.4).
 bool azimuth_product(const snrt_mesh& m, const DenseB& B) {
-    return B.az.na != 0 && (size_t)m.nc * B.nq * sizeof(float) < (size_t(1) << 32) &&
-           (B.az.np > 8 || B.precision == SNRT_FP32 || m.nc <= 32768);
+    if (B.az.na == 0 || (size_t)m.nc * B.nq * sizeof(float) >= (size_t(1) << 32)) return false;
+    if (m.nc <= 16384) return true;
+    const int32_t slots = (B.az.na > 16 ? 32 : 16) * (B.az.np > 16 ? 32 : 16);
+    if (B.precision == SNRT_FP32)
+        return 5 * B.nq >= slots && (B.nq % 128 != 0 || 4 * B.nq > slots);
+    return 2 * B.nq > slots;
 }
 
 // S = Psi B (forward) or G = Lambda B^T (adjoint) into the workspace, FP32 state
@@ -995,7 +1004,9 @@ snrt_status step_adjoint32_t(const char* fn, const snrt_mesh* m, const snrt_quad
                  SNRT_E_ALIAS, std::string(fn) + ": workspace aliases psi_n");
     hipStream_t st = static_cast<hipStream_t>(stream);
     const float* G = nullptr;
-    if (sc->dense && tune().step_fused && azimuth_product(*m, sc->B)) {
+    // up to 64 ordinates the transposed-step kernel holds a row in one register per lane, and the
+    // gradients' row sums keep its order, whether or not the dose term rides along
+    if (sc->dense && tune().step_fused && q->nq > kWave && azimuth_product(*m, sc->B)) {
         const hipError_t e = launch_az_adjoint(*m, *q, sc->B.az, to32(a), psi_n, lam_np1, lam_n,
                                                g_t, g_s, g_r, da, st);
         return e == hipSuccess ? SNRT_OK

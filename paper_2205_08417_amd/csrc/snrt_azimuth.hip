@@ -18,16 +18,16 @@ constexpr double kPi = 3.14159265358979323846;
 constexpr double kInvariant = 1e-11;
 
 // Product-rule shape: na consecutive ordinates share each polar node, with one weight.  The
-// kernels take 16 or 32 azimuths, and 8 to 16 polar nodes or an even count up to 32 (folded); with
-// fewer than 8 nodes more than half of the 16 polar slots would be padding.
+// kernels take up to 16 azimuths or an even count up to 32 (folded), and up to 16 polar nodes or an
+// even count up to 32 (folded).
 bool product_shape(const snrt_quad& q, int& np, int& na) {
     const int nq = q.nq;
     auto z = [&](int i) { return q.omega_host[(size_t)i * 3 + 2]; };
     na = 1;
     while (na < nq && std::fabs(z(na) - z(0)) <= 1e-12) ++na;
-    if ((na != 16 && na != 32) || nq % na != 0) return false;
+    if (na < 2 || nq % na != 0) return false;
     np = nq / na;
-    if (np < 8 || np > 32 || (np > 16 && np % 2 != 0)) return false;
+    if (na > 32 || (na > 16 && na % 2 != 0) || np > 32 || (np > 16 && np % 2 != 0)) return false;
     for (int k = 0; k < np; ++k)
         for (int l = 1; l < na; ++l)
             if (q.w_host[(size_t)k * na + l] != q.w_host[(size_t)k * na] ||
@@ -36,30 +36,39 @@ bool product_shape(const snrt_quad& q, int& np, int& na) {
     return true;
 }
 
-// Frequency and phase of mode slot m (0..15) of azimuthal class c: pairs (2j, 2j + 1) are the
-// cosine and sine of one frequency, except modes 0 and na / 2, which share the first pair.
+int classes(int na) { return na > 16 ? 2 : 1; }
+
+// Frequency and phase of mode slot m (0..15) of azimuthal class c (two classes: the even and the
+// odd frequencies): pairs (2j, 2j + 1) are the cosine and sine of one frequency, except modes 0
+// and na / 2 of class 0, which share its first pair.  f < 0: no mode in the slot.
 struct Mode {
     int f;
     bool sine;
 };
 Mode mode_of(int na, int c, int m) {
-    const int j = m / 2, s = m & 1;
-    const int f = na == 16 ? j : 2 * j + c;
-    if (f == 0) return {s ? na / 2 : 0, false};
-    return {f, s == 1};
+    const int j = m / 2, s = m & 1, AZ = classes(na);
+    const int f = AZ == 1 ? j : 2 * j + c;
+    if (f == 0) {
+        if (!s) return {0, false};
+        return {na % 2 == 0 && (AZ == 1 || na / 2 % 2 == 0) ? na / 2 : -1, false};
+    }
+    if (2 * f < na) return {f, s == 1};
+    // the odd class holds na / 2 where that is odd, as an ordinary pair without a sine
+    return {2 * f == na && AZ == 2 && c == 1 && !s ? f : -1, false};
 }
 
 // Element l of the orthonormal real Fourier basis over na azimuths.
 double basis(int na, const Mode& md, int l) {
+    if (md.f < 0) return 0.0;
     const double x = 2.0 * kPi * (double)((md.f * l) % na) / na;
-    if (md.f == 0 || md.f == na / 2) return std::cos(x) / std::sqrt((double)na);
+    if (md.f == 0 || 2 * md.f == na) return std::cos(x) / std::sqrt((double)na);
     return std::sqrt(2.0 / na) * (md.sine ? std::sin(x) : std::cos(x));
 }
 
 // The polar matrices M[class][pair][which] (h x h in a 16 x 16 frame, row-major) of the
 // coefficients a; half: the polar fold's factor 1/2 included.
 std::vector<double> polar_matrices(const std::vector<double>& a, int np, int na, bool half) {
-    const int AZ = na / 16, MU = np > 16 ? 2 : 1, NC = AZ * MU, h = np / MU;
+    const int AZ = classes(na), MU = np > 16 ? 2 : 1, NC = AZ * MU, h = np / MU;
     std::vector<double> M((size_t)NC * 16 * 256, 0.0);
     std::vector<double> c(na);
     for (int f = 0; f <= na / 2; ++f) {
@@ -102,7 +111,7 @@ void pack(const double* M, size_t n, bool transpose, float* out) {
 }
 
 snrt_status upload_operand(DenseB& B, int np, int na, std::vector<double> a) {
-    const int AZ = na / 16, MU = np > 16 ? 2 : 1, NC = AZ * MU;
+    const int AZ = classes(na), MU = np > 16 ? 2 : 1, NC = AZ * MU, half = na / AZ;
     const std::vector<double> M = polar_matrices(a, np, na, true);
     const size_t nf = (size_t)AZ * 256, nm = (size_t)NC * 16 * 256;
     std::vector<float> host(2 * nf + 2 * nm);
@@ -111,8 +120,8 @@ snrt_status upload_operand(DenseB& B, int np, int na, std::vector<double> a) {
             for (int s = 0; s < 4; ++s) {
                 const int lo = lane & 15, hi = lane >> 4;
                 const size_t at = (size_t)(c * 64 + lane) * 4 + s;
-                host[at] = (float)basis(na, mode_of(na, c, lo), 4 * hi + s);
-                host[nf + at] = (float)basis(na, mode_of(na, c, 4 * s + hi), lo);
+                if (4 * hi + s < half) host[at] = (float)basis(na, mode_of(na, c, lo), 4 * hi + s);
+                if (lo < half) host[nf + at] = (float)basis(na, mode_of(na, c, 4 * s + hi), lo);
             }
     pack(M.data(), (size_t)NC * 16, false, &host[2 * nf]);
     pack(M.data(), (size_t)NC * 16, true, &host[2 * nf + nm]);
@@ -151,7 +160,7 @@ snrt_status make_azimuth_dense(DenseB& B, const snrt_quad& q, const std::vector<
                 double* m = &a[((size_t)k * np + k2) * na];
                 double t = top[(size_t)k * np + k2];
                 for (int l = 0; l < na; ++l) {
-                    m[(l - l2) & (na - 1)] += x[l];
+                    m[l - l2 + (l < l2 ? na : 0)] += x[l];
                     t = std::max(t, std::fabs(x[l]));
                 }
                 top[(size_t)k * np + k2] = t;
@@ -159,8 +168,7 @@ snrt_status make_azimuth_dense(DenseB& B, const snrt_quad& q, const std::vector<
         }
     for (size_t i = 0; i < n; i += na) {
         a[i] /= na;
-        a[i + na / 2] /= na;
-        for (int d = 1; d < na / 2; ++d)
+        for (int d = 1; 2 * d <= na; ++d)
             a[i + d] = a[i + na - d] = 0.5 * (a[i + d] + a[i + na - d]) / na;
     }
     for (int k2 = 0; k2 < np; ++k2)
@@ -169,7 +177,7 @@ snrt_status make_azimuth_dense(DenseB& B, const snrt_quad& q, const std::vector<
             for (int k = 0; k < np; ++k, x += na) {
                 const double* m = &a[((size_t)k * np + k2) * na];
                 double far = 0.0;
-                for (int l = 0; l < na; ++l) far = std::max(far, std::fabs(x[l] - m[(l - l2) & (na - 1)]));
+                for (int l = 0; l < na; ++l) far = std::max(far, std::fabs(x[l] - m[l - l2 + (l < l2 ? na : 0)]));
                 if (!(far <= kInvariant * top[(size_t)k * np + k2])) return SNRT_OK;
             }
         }
@@ -242,7 +250,7 @@ snrt_status make_azimuth_moments(DenseB& B, const snrt_quad& q, const double* si
 snrt_status make_azimuth_implicit(DenseB& B) {
     AzOperand& op = B.az;
     if (op.na == 0 || op.imp_base || B.az_r.empty()) return SNRT_OK;
-    const int np = op.np, na = op.na, AZ = na / 16, MU = np > 16 ? 2 : 1, h = np / MU;
+    const int np = op.np, na = op.na, AZ = classes(na), MU = np > 16 ? 2 : 1, h = np / MU;
     // A is symmetric after the scaling r of the polar nodes; under the polar fold r has to be
     // the same on both halves
     std::vector<double> sr(h);

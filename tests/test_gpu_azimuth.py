@@ -19,8 +19,12 @@ torch = pytest.importorskip("torch")
 from paper_2205_08417_amd import inputs as I  # noqa: E402
 
 TOL = 1e-6
-# polar x azimuthal: every fold, full and partly filled polar slots, an odd count
-SHAPES = [(8, 32), (13, 32), (16, 32), (18, 32), (32, 32), (9, 16), (16, 16), (20, 16), (32, 16)]
+# polar x azimuthal: every fold, full and partly filled polar slots, an odd count; then azimuths
+# that leave slots empty (odd, even, folded with an even and an odd half), at the edges of the
+# striped rows' lane counts (128 | 192 | 256 | 320 | 384 | 512 ordinates per wave)
+SHAPES = [(8, 32), (13, 32), (16, 32), (18, 32), (32, 32), (9, 16), (16, 16), (20, 16), (32, 16),
+          (12, 10), (13, 11), (16, 15), (20, 9), (26, 13), (32, 15), (13, 18), (16, 20), (16, 24),
+          (15, 26), (16, 30), (18, 22), (28, 26), (32, 30)]
 
 
 @pytest.fixture(scope="module", autouse=True)
@@ -126,10 +130,10 @@ def _uneven_weights():
 
 
 @pytest.mark.parametrize("make", [_one_entry, _no_mirror, _odd_in_difference, _uneven_weights,
-                                  lambda: _kernel(12, 24), lambda: _kernel(17, 32),
-                                  lambda: _kernel(4, 32)],
+                                  lambda: _kernel(16, 34), lambda: _kernel(17, 32),
+                                  lambda: _kernel(32, 19), lambda: _kernel(4, 32)],
                          ids=["one-entry", "no-mirror", "odd-in-difference", "uneven-weights",
-                              "24-azimuths", "17-polar", "4-polar"])
+                              "34-azimuths", "17-polar", "19-azimuths", "4-polar"])
 @pytest.mark.parametrize("precision,tol", [("fp32", TOL), ("bf16x3", 2e-5)])
 def test_operators_without_the_structure_keep_the_general_products(make, precision, tol):
     """Kernels, weights and shapes outside the structure: their product, step and transposed step
@@ -161,7 +165,8 @@ def test_operators_without_the_structure_keep_the_general_products(make, precisi
 # stiff: dt sigma of the order of ten.  The solve applies the modes' eigenvectors (condition
 # number the root of the weights' ratio, below 4 here) around the diagonal: twice the product's
 # roundings, each once more through the weights, 4 * TOL.
-@pytest.mark.parametrize("npol,naz", [(8, 32), (13, 32), (18, 32), (9, 16), (16, 16), (20, 16)])
+@pytest.mark.parametrize("npol,naz", [(8, 32), (13, 32), (18, 32), (9, 16), (16, 16), (20, 16),
+                                      (12, 10), (20, 9), (13, 18), (16, 24), (18, 22)])
 @pytest.mark.parametrize("kind", [3, 4, "quads"])
 @pytest.mark.parametrize("moments", [False, True])
 def test_imex_step_vs_oracle(npol, naz, kind, moments):
