@@ -570,8 +570,8 @@ snrt_status snrt_pn_operators(int32_t degree, double* ax, double* ay, double* ax
 
 /* P_N system of the given degree (0..30) on the current device.  sigma_l: host [degree+1]
  * Legendre moments of the scattering kernel (2 pi int P_l(mu) k(mu) dmu; sigma_0 = 1
- * conserves particles), NULL = isotropic (1, 0, 0, ...).  Degrees up to 9 run a fully
- * unrolled kernel; larger degrees a chunked one. */
+ * conserves particles), NULL = isotropic (1, 0, 0, ...).  FP32 degrees up to 9
+ * run a fully unrolled kernel, 10 to 13 the matrix cores; larger degrees a chunked kernel. */
 snrt_status snrt_pn_create(snrt_pn** out, int32_t degree, const double* sigma_l);
 void snrt_pn_destroy(snrt_pn* pn);
 snrt_status snrt_pn_info(const snrt_pn* pn, int32_t* degree, int32_t* nmoments);

@@ -18,7 +18,8 @@ BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libsnrt.so")
 # the longest compiles (the unrolled P_N kernel of degree 13, the products) first, so the
 # pool starts them early
-SOURCES = ["sn_pn13.hip", "sn_gemm_mfma.hip", "sn_step_fused.hip", "sn_step_fused_rho.hip",
+SOURCES = ["sn_pn13.hip", "sn_pn12.hip", "sn_pn11.hip", "sn_pn10.hip",
+           "sn_gemm_mfma.hip", "sn_step_fused.hip", "sn_step_fused_rho.hip",
            "sn_step_fused_dose.hip", "sn_step_fused_rho_dose.hip", "sn_step_fused_combine.hip",
            "sn_step_fused_adjoint.hip", "snrt_api.hip", "sn_step_f32.hip", "sn_step_f64.hip", "sn_adjoint.hip",
            "sn_reduce.hip", "sn_gemm_simple.hip", "sn_step2.hip", "sn_step_imex.hip",

@@ -26,6 +26,9 @@ constexpr int kMaxFusedDegree = 9;    // degrees 0..9 have a fully unrolled FP32
 constexpr int kFusedHighDegree = 13;  // and degree 13 (the CSD degree of Sec. 7) as well
 constexpr int kMaxFusedDegree64 = 2;  // the same for FP64 (its accumulators take twice the
                                       // registers; larger degrees use the chunked kernel)
+// Degrees above the contiguous range whose step runs on the matrix cores (k_pn_mfma): up to 32
+// moments per reflection class.
+constexpr bool has_mfma_kernel(int N) { return N > kMaxFusedDegree && N <= kFusedHighDegree; }
 template <typename T>
 constexpr int max_fused_degree() { return sizeof(T) == 4 ? kMaxFusedDegree : kMaxFusedDegree64; }
 template <typename T>

@@ -185,7 +185,7 @@ struct snrt_pn {
     double* w64 = nullptr;
     float* sig32 = nullptr;
     double* sig64 = nullptr;
-    // the matrix-core step of degree pn::kFusedHighDegree: the A_x, A_y coefficients
+    // the matrix-core step (pn::has_mfma_kernel): the A_x, A_y coefficients
     // (pn::SparseOps order), the class blocks' FP16 hi/lo operands [z parity][class][K step]
     // [hi, lo][lane][8] and their exponents [z parity][class]
     float* wsp32 = nullptr;
@@ -206,14 +206,14 @@ namespace snrt {
 // the blocks per CU of the three persistent sweeps, SNRT_GEMM_STAGGER=0 turns the staggered
 // chunk order of the product off, SNRT_GEMM_EPILOGUE=0 the IMEX steps in the products'
 // epilogues (separate passes instead), SNRT_PN_MFMA=0 the matrix-core class blocks of the
-// degree-13 P_N step, SNRT_AZIMUTH=0 the azimuthal-mode scattering (all read once per process).
+// P_N steps of degrees 10 to 13, SNRT_AZIMUTH=0 the azimuthal-mode scattering (all read once per process).
 struct Tune {
     int step_blocks_per_cu = 3;
     int flux2_blocks_per_cu = 2;   // its larger per-cell footprint favours a narrower sweep
     int adjoint_blocks_per_cu = 7; // the adjoint's smaller workloads favour a wide grid
     bool gemm_stagger = true;      // staggered split/product phases in the BF16 product
     bool gemm_epilogue = true;     // IMEX per-cell steps in the products' epilogues
-    bool pn_mfma = true;           // matrix-core class blocks in the degree-13 P_N step
+    bool pn_mfma = true;           // matrix-core class blocks in the P_N steps of degrees 10..13
     bool step_fused = true;        // dense step: the update in the product's epilogue
     bool azimuth = true;           // azimuthal-mode scattering where the kernel has that form
 };
@@ -559,6 +559,13 @@ hipError_t launch_dose_density_grad64(const snrt_mesh& m, const double* dose,
 
 // P_N step (sn_pn.hip): u_out = step(u_in) in the tiled moment layout; layout conversion
 // between the user's [ncells][nm] rows and the tiled internal layout.
+// the matrix-core FP32 kernels of degrees 10..12 (sn_pn10.hip, ...)
+hipError_t launch_pn_mfma32_10(const snrt_mesh& m, const snrt_pn& p, const StepArgs32& a,
+                               const float* u, float* out, hipStream_t st);
+hipError_t launch_pn_mfma32_11(const snrt_mesh& m, const snrt_pn& p, const StepArgs32& a,
+                               const float* u, float* out, hipStream_t st);
+hipError_t launch_pn_mfma32_12(const snrt_mesh& m, const snrt_pn& p, const StepArgs32& a,
+                               const float* u, float* out, hipStream_t st);
 // the unrolled FP32 kernel of degree pn::kFusedHighDegree (sn_pn13.hip)
 hipError_t launch_pn_fused_high32(const snrt_mesh& m, const snrt_pn& p, const StepArgs32& a,
                                   const float* u, float* out, hipStream_t st);
