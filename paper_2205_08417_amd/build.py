@@ -22,7 +22,7 @@ SOURCES = ["sn_pn13.hip", "sn_pn12.hip", "sn_pn11.hip", "sn_pn10.hip",
            "sn_gemm_mfma.hip", "sn_step_fused.hip", "sn_step_fused_rho.hip",
            "sn_step_fused_dose.hip", "sn_step_fused_rho_dose.hip", "sn_step_fused_combine.hip",
            "sn_step_fused_adjoint.hip", "snrt_api.hip", "sn_step_f32.hip", "sn_step_f64.hip", "sn_adjoint.hip",
-           "sn_reduce.hip", "sn_gemm_simple.hip", "sn_step2.hip", "sn_step_imex.hip",
+           "sn_reduce.hip", "sn_gemm_simple.hip", "sn_step2.hip", "sn_step2_tile.hip", "sn_step_imex.hip",
            "sn_pn.hip", "snrt_pn_api.hip", "snrt_rollout.hip", "snrt_noalloc.hip",
            "snrt_eig.hip", "snrt_azimuth.hip", "sn_azimuth_step.hip",
            "sn_azimuth_adjoint.hip", "sn_azimuth_imex.hip"]

@@ -393,13 +393,6 @@ __device__ __forceinline__ void from_modes(f32x4 (&s)[P::SEG], const Fourier<P, 
     fold<P>(s);
 }
 
-// Block barrier for LDS traffic alone: loads in flight stay in flight across it.
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // The tiles of a block: XCD x owns a contiguous range of tiles (cells in Hilbert order) and its
 // blocks sweep it together, as in the step kernel.
 struct Tiles {

@@ -3,6 +3,8 @@
 // linear reconstructions of u on both sides of every face.  The host runs two stages and
 // averages (Heun).
 //
+// FP32 stages of most sizes run in one launch instead (sn_step2_tile.hip: stage2_tiled).
+//
 // k_grad2 (one wavefront per cell or per 256-ordinate chunk of a cell, lane = V ordinates):
 //   grad u_i = 1/A_i sum_f (u_i + u_f)/2 n_if          (u_f: neighbour value or ghost value)
 //   Psi_i    = min_f phi(d1_f, d_f), d_f = grad u_i . r_if, d1_f = u_max - u_i if d_f > 0,
@@ -20,13 +22,9 @@
 // neighbour row scaled by its 1/rho, Dirichlet faces the inflow row scaled by inflow_scale,
 // Neumann faces the own row scaled by 1/rho, vacuum faces the own row scaled by 0; an unused
 // slot is the cell itself with zero normal and zero reconstruction vectors.
-#include "sn_step_kernels.h"
+#include "sn_slope.h"
 
 namespace snrt {
-
-template <typename T> struct ReconOf;
-template <> struct ReconOf<float> { using type = CellRecon32; };
-template <> struct ReconOf<double> { using type = CellRecon64; };
 
 namespace {
 
@@ -87,46 +85,16 @@ __global__ __launch_bounds__(kStepBlock) void k_grad2(
             const T avg = T(0.5) * (u[k] + uf[k]);
             gx[k] += avg * nx;
             gy[k] += avg * ny;
-            umax[k] = uf[k] > umax[k] ? uf[k] : umax[k];
-            umin[k] = uf[k] < umin[k] ? uf[k] : umin[k];
+            umax[k] = larger(umax[k], uf[k]);
+            umin[k] = smaller(umin[k], uf[k]);
         }
     }
-    T lim[V];
 #pragma unroll
     for (int k = 0; k < V; ++k) {
         gx[k] *= g.inv_area;
         gy[k] *= g.inv_area;
-        lim[k] = T(1);
     }
-    T eps2 = T(0);
-    if constexpr (LIM == SNRT_LIMITER_VENKATAKRISHNAN) {
-        const T h = vk_k * sqrt(T(1) / g.inv_area);
-        eps2 = h * h * h;
-    }
-#pragma unroll
-    for (int f = 0; f < MF; ++f) {
-        const T rx = rc.r_own[f][0], ry = rc.r_own[f][1];
-#pragma unroll
-        for (int k = 0; k < V; ++k) {
-            const T d2 = gx[k] * rx + gy[k] * ry;
-            const T d1 = d2 > T(0) ? umax[k] - u[k] : umin[k] - u[k];
-            T t = T(1);
-            if constexpr (LIM == SNRT_LIMITER_VENKATAKRISHNAN) {
-                // d1 d2 >= 0, so the denominator is at least 2 d2^2 > 0 whenever d2 != 0
-                const T d11 = d1 * d1 + eps2;
-                if (d2 != T(0)) t = (d11 + T(2) * d2 * d1) / (d11 + T(2) * d2 * d2 + d1 * d2);
-            } else {
-                if (d2 != T(0)) t = d1 / d2;
-                t = t < T(1) ? t : T(1);
-            }
-            lim[k] = t < lim[k] ? t : lim[k];
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < V; ++k) {
-        gx[k] *= lim[k];
-        gy[k] *= lim[k];
-    }
+    limit_slope<V, MF, LIM>(gx, gy, u, umax, umin, rc.r_own, limiter_eps2<LIM>(vk_k, g.inv_area));
     store_slice<V, EXACT>(G + (2 * c) * nq, q0, nq, gx, false);
     store_slice<V, EXACT>(G + (2 * c + 1) * nq, q0, nq, gy, false);
 }

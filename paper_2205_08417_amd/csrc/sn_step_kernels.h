@@ -226,6 +226,13 @@ __device__ __forceinline__ void buf_store_row(__amdgpu_buffer_rsrc_t r, uint32_t
     }
 }
 
+// Block barrier for LDS traffic alone: loads in flight stay in flight across it.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // Element i of a per-cell array through a scalar load with a 32-bit byte offset.
 template <typename T>
 __device__ __forceinline__ T cell_val(const T* __restrict__ a, int32_t i) {

@@ -36,6 +36,42 @@ uint64_t hilbert_index(uint32_t x, uint32_t y) {
     return d;
 }
 
+void drop_stage_tiles(snrt_mesh* m) {
+    dev_free(m->tiles.tile);
+    dev_free(m->tiles.rows);
+    dev_free(m->tiles.geom);
+    m->tiles = StageTiles();
+}
+
+bool finite_centroids(const double* centroid, int64_t nc) {
+    for (int64_t i = 0; i < 2 * nc; ++i)
+        if (!is_finite(centroid[i])) return false;
+    return true;
+}
+
+// The cells of order, at least one, along a Hilbert curve through the bounding box of their
+// finite centroids.
+void hilbert_sort(std::vector<int64_t>& order, const double* centroid) {
+    const int64_t nc = (int64_t)order.size();
+    double x0 = centroid[0], x1 = centroid[0], y0 = centroid[1], y1 = centroid[1];
+    for (int64_t i = 0; i < nc; ++i) {
+        x0 = std::min(x0, centroid[2 * i]);
+        x1 = std::max(x1, centroid[2 * i]);
+        y0 = std::min(y0, centroid[2 * i + 1]);
+        y1 = std::max(y1, centroid[2 * i + 1]);
+    }
+    const double span = std::max(std::max(x1 - x0, y1 - y0), 1e-300);
+    std::vector<uint64_t> key(nc);
+    for (int64_t i = 0; i < nc; ++i) {
+        const double fx = (centroid[2 * i] - x0) / span, fy = (centroid[2 * i + 1] - y0) / span;
+        const uint32_t ix = (uint32_t)std::min(65535.0, std::floor(fx * 65536.0));
+        const uint32_t iy = (uint32_t)std::min(65535.0, std::floor(fy * 65536.0));
+        key[i] = hilbert_index(ix, iy);
+    }
+    std::stable_sort(order.begin(), order.end(),
+                     [&](int64_t a, int64_t b) { return key[a] < key[b]; });
+}
+
 }  // namespace
 
 void set_error(const std::string& msg) { g_last_error = msg; }
@@ -132,6 +168,7 @@ void snrt_mesh_destroy(snrt_mesh* m) {
     dev_free(m->geom64);
     dev_free(m->d_to_user);
     dev_free(m->d_partial);
+    drop_stage_tiles(m);
     dev_free(m->recon32);
     dev_free(m->recon64);
     delete m;
@@ -188,25 +225,9 @@ snrt_status snrt_mesh_create(snrt_mesh** out, int64_t nc, int32_t mf, const int3
     std::vector<int64_t> to_user(nc);
     std::iota(to_user.begin(), to_user.end(), 0);
     if (reorder && nc > 1) {
-        double x0 = centroid[0], x1 = centroid[0], y0 = centroid[1], y1 = centroid[1];
-        for (int64_t i = 0; i < nc; ++i) {
-            SNRT_REQUIRE(is_finite(centroid[2 * i]) && is_finite(centroid[2 * i + 1]), SNRT_E_ARG,
-                         "snrt_mesh_create: non-finite centroid");
-            x0 = std::min(x0, centroid[2 * i]);
-            x1 = std::max(x1, centroid[2 * i]);
-            y0 = std::min(y0, centroid[2 * i + 1]);
-            y1 = std::max(y1, centroid[2 * i + 1]);
-        }
-        const double span = std::max(std::max(x1 - x0, y1 - y0), 1e-300);
-        std::vector<uint64_t> key(nc);
-        for (int64_t i = 0; i < nc; ++i) {
-            const double fx = (centroid[2 * i] - x0) / span, fy = (centroid[2 * i + 1] - y0) / span;
-            const uint32_t ix = (uint32_t)std::min(65535.0, std::floor(fx * 65536.0));
-            const uint32_t iy = (uint32_t)std::min(65535.0, std::floor(fy * 65536.0));
-            key[i] = hilbert_index(ix, iy);
-        }
-        std::stable_sort(to_user.begin(), to_user.end(),
-                         [&](int64_t a, int64_t b) { return key[a] < key[b]; });
+        SNRT_REQUIRE(finite_centroids(centroid, nc), SNRT_E_ARG,
+                     "snrt_mesh_create: non-finite centroid");
+        hilbert_sort(to_user, centroid);
     }
     std::vector<int64_t> to_int(nc);
     for (int64_t k = 0; k < nc; ++k) to_int[to_user[k]] = k;
@@ -254,6 +275,7 @@ snrt_status snrt_mesh_create(snrt_mesh** out, int64_t nc, int32_t mf, const int3
     m->nbf = nbf;
     m->mf = mf;
     m->to_user = std::move(to_user);
+    m->on_curve = reorder;
     m->face_nbr_user.assign(face_nbr, face_nbr + nc * mf);
     if (centroid) m->centroid_user.assign(centroid, centroid + nc * 2);
     m->n_partial = std::max<int64_t>((nc + kCellsPerBlock - 1) / kCellsPerBlock, 16);
@@ -268,9 +290,143 @@ snrt_status snrt_mesh_create(snrt_mesh** out, int64_t nc, int32_t mf, const int3
         snrt_mesh_destroy(m);
         return s;
     }
+    m->geom_host = std::move(g32);
     *out = m;
     return SNRT_OK;
 }
+
+}  // extern "C"
+
+namespace {
+
+// The tiles of the second-order stage kernel: cells along a Hilbert curve, whatever their
+// numbering, as long as the faces fit a block's rows.  The two sides of a face decide from their own normals which of them is
+// upwind; that they agree takes normals that are exact negatives in FP32 and one face at most
+// between two cells, else there are no tiles.
+snrt_status make_stage_tiles(snrt_mesh* m) {
+    const int64_t nc = m->nc;
+    const int32_t mf = m->mf;
+    if (nc == 0) return SNRT_OK;
+    const std::vector<CellGeom32>& geom = m->geom_host;
+    // an unused slot holds the cell itself
+    const auto used = [&](int64_t k, int f) { return geom[k].nbr[f] != (int32_t)k; };
+    const auto back = [&](int64_t j, int64_t k) {      // the slot of cell k in cell j
+        int g = 0;
+        while (g < mf && geom[j].nbr[g] != (int32_t)k) ++g;
+        return g;
+    };
+    for (int64_t k = 0; k < nc; ++k)
+        for (int f = 0; f < mf; ++f) {
+            const int64_t j = geom[k].nbr[f];
+            if (j < 0 || !used(k, f)) continue;
+            const float* n = geom[k].n[f];
+            const float* nj = geom[j].n[back(j, k)];
+            if (n[0] != -nj[0] || n[1] != -nj[1] || back(k, j) != f) return SNRT_OK;
+        }
+    if (!finite_centroids(m->centroid_user.data(), nc)) return SNRT_OK;
+    std::vector<int32_t> order(nc), place(nc);          // cells along the curve
+    std::iota(order.begin(), order.end(), 0);
+    if (!m->on_curve) {
+        std::vector<int64_t> curve(nc), to_int(nc);
+        std::iota(curve.begin(), curve.end(), 0);
+        hilbert_sort(curve, m->centroid_user.data());
+        for (int64_t k = 0; k < nc; ++k) to_int[m->to_user[k]] = k;
+        for (int64_t i = 0; i < nc; ++i) order[i] = (int32_t)to_int[curve[i]];
+    }
+    for (int64_t i = 0; i < nc; ++i) place[order[i]] = (int32_t)i;
+    const int64_t cap = std::clamp<int64_t>(nc / m->num_cu, 16, kStageCells);
+    std::vector<StageTile> tiles;
+    std::vector<StageRow> rows;
+    rows.reserve(nc * 2);
+    std::vector<int32_t> face_row(nc * 4, -1);         // of the tile in hand
+    std::vector<char> halo(nc, 0);
+    std::vector<int32_t> cells;
+    for (int64_t first = 0; first < nc;) {
+        int64_t end = first;
+        const auto inside = [&](int64_t j) { return place[j] >= first && place[j] < end; };
+        for (int32_t faces = 0; end < nc && end - first < cap; ++end) {
+            const int64_t k = order[end];
+            int32_t add = 0;
+            for (int f = 0; f < mf; ++f) {
+                const int64_t j = geom[k].nbr[f];
+                add += used(k, f) && !(j >= 0 && inside(j));
+            }
+            if (end > first && faces + add > kStageFaces) break;
+            faces += add;
+        }
+        cells.assign(order.begin() + first, order.begin() + end);
+        StageTile t = {(int32_t)rows.size(), (int32_t)cells.size(), 0, 0};
+        for (int32_t i = 0; i < t.cells; ++i)
+            for (int f = 0; f < mf; ++f) {
+                const int64_t j = geom[cells[i]].nbr[f];
+                if (j < 0 || inside(j) || halo[j]) continue;
+                halo[j] = 1;
+                cells.push_back((int32_t)j);
+            }
+        t.halo = (int32_t)cells.size() - t.cells;
+        int32_t next = 0;
+        for (int32_t i = 0; i < t.cells; ++i)
+            for (int f = 0; f < mf; ++f) {
+                const int64_t k = cells[i], j = geom[k].nbr[f];
+                if (!used(k, f) || face_row[k * 4 + f] >= 0) continue;
+                face_row[k * 4 + f] = next;
+                if (j >= 0) face_row[j * 4 + back(j, k)] = next;
+                ++next;
+            }
+        for (const int32_t k : cells) {
+            StageRow r = {k, {0, 0}, 0.5f * geom[k].inv_area, {}};
+            bool interior = true;
+            int32_t any = 0;
+            for (int f = 0; f < mf; ++f) {
+                interior &= !(used(k, f) && geom[k].nbr[f] < 0);
+                any = std::max(any, face_row[(int64_t)k * 4 + f]);
+            }
+            for (int f = 0; f < 4; ++f) {
+                const int32_t row = face_row[(int64_t)k * 4 + f], j = geom[k].nbr[f];
+                const uint32_t e = row < 0 ? any | kFaceSkip
+                                           : row | (j < 0 ? kFaceBoundary : 0) |
+                                                 (j < 0 || k < j ? kFaceLower : 0);
+                r.faces[f / 2] |= (e | (f == 0 && interior ? kFaceInterior : 0)) << (16 * (f % 2));
+                r.nbr[f] = j;
+            }
+            rows.push_back(r);
+        }
+        for (const int32_t k : cells) {
+            halo[k] = 0;
+            for (int f = 0; f < 4; ++f) face_row[(int64_t)k * 4 + f] = -1;
+        }
+        tiles.push_back(t);
+        first = end;
+    }
+    StageTiles d;
+    const char* what = "snrt_mesh_set_face_midpoints: upload";
+    snrt_status s = SNRT_OK;
+    if ((s = dev_alloc(&d.tile, (int64_t)tiles.size(), "stage tiles")) != SNRT_OK ||
+        (s = dev_alloc(&d.rows, (int64_t)rows.size(), "stage tiles")) != SNRT_OK ||
+        (s = dev_alloc(&d.geom, (int64_t)rows.size(), "stage tiles")) != SNRT_OK ||
+        (s = upload(d.tile, tiles.data(), (int64_t)tiles.size(), what)) != SNRT_OK ||
+        (s = upload(d.rows, rows.data(), (int64_t)rows.size(), what)) != SNRT_OK) {
+        dev_free(d.tile);
+        dev_free(d.rows);
+        dev_free(d.geom);
+        return s;
+    }
+    hipError_t e = launch_stage_geom(*m, d.rows, d.geom, (int64_t)rows.size(), nullptr);
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+    if (e != hipSuccess) {
+        dev_free(d.tile);
+        dev_free(d.rows);
+        dev_free(d.geom);
+        return hip_fail(e, what);
+    }
+    d.count = (int32_t)tiles.size();
+    m->tiles = d;
+    return SNRT_OK;
+}
+
+}  // namespace
+
+extern "C" {
 
 snrt_status snrt_mesh_set_face_midpoints(snrt_mesh* m, const double* face_mid) {
     g_last_error.clear();
@@ -331,7 +487,8 @@ snrt_status snrt_mesh_set_face_midpoints(snrt_mesh* m, const double* face_mid) {
     if ((s = upload(m->recon32, r32.data(), nc, "snrt_mesh_set_face_midpoints: upload")) != SNRT_OK ||
         (s = upload(m->recon64, r64.data(), nc, "snrt_mesh_set_face_midpoints: upload")) != SNRT_OK)
         return s;
-    return SNRT_OK;
+    drop_stage_tiles(m);
+    return make_stage_tiles(m);
 }
 
 snrt_status snrt_mesh_permutation(const snrt_mesh* m, int64_t* internal_to_user) {
@@ -1227,6 +1384,13 @@ snrt_status step2_common(const char* fn, const snrt_mesh* m, const snrt_quad* q,
     for (int stage = 0; stage < 2 && e == hipSuccess; ++stage) {
         if constexpr (sizeof(T) == 4) {
             const StepArgs32 a32 = to32(a);
+            if (stage2_tiled(*m, *q)) {
+                if (S) e = scatter_product32(*m, sc, in[stage], S, false, U, st);
+                if (e == hipSuccess)
+                    e = launch_stage2_32(*m, *q, a32, lim, in[stage], S,
+                                         stage ? psi_in : nullptr, outp[stage], st);
+                continue;
+            }
             e = launch_grad2_32(*m, *q, a32, lim, in[stage], G, st);
             if (e == hipSuccess && S) e = scatter_product32(*m, sc, in[stage], S, false, U, st);
             if (e == hipSuccess)

@@ -55,6 +55,39 @@ struct alignas(64) CellRecon64 {
 };
 static_assert(sizeof(CellRecon64) == 128, "two cache lines per cell");
 
+// Tiles of the second-order stage kernel (sn_step2_tile.hip): neighbouring cells, and the cells
+// outside the tile that share a face with one inside (its halo), so that a block can hold the
+// upwind value of every face of the tile in LDS, one row per face.
+constexpr int kStageFaces = 158;       // face rows of a block, 64 lanes x 2 x 4 bytes each
+constexpr int kStageCells = 96;        // cells of a tile at most
+struct StageTile {
+    int32_t rows;                      // first of its StageRows: its cells, then its halo
+    int32_t cells, halo;
+    int32_t pad;
+};
+// A cell of a tile or of its halo, in whole words for two scalar loads.
+struct alignas(32) StageRow {
+    int32_t cell;
+    uint32_t faces[2];                 // face(f): the LDS row of the face, and who writes it
+    float half_inv_area;
+    int32_t nbr[4];
+    __host__ __device__ uint32_t face(int f) const { return faces[f / 2] >> (16 * (f % 2)) & 0xffffu; }
+};
+constexpr uint32_t kFaceRow = 0x1ff;        // the LDS row (an unused slot's: a used face's)
+constexpr uint32_t kFaceInterior = 0x1000;  // on face 0: no face of the cell is a boundary's
+constexpr uint32_t kFaceLower = 0x2000;     // the lower of the face's two cells, or the only one
+constexpr uint32_t kFaceBoundary = 0x4000;  // this side writes the ghost value as well
+constexpr uint32_t kFaceSkip = 0x8000;      // not a face of the tile, or an unused slot
+struct alignas(64) StageGeom {
+    float n[4][2], r[4][2];            // CellGeom32::n, CellRecon32::r_own
+};
+struct StageTiles {
+    StageTile* tile = nullptr;         // [count]
+    StageRow* rows = nullptr;
+    StageGeom* geom = nullptr;         // of the same row
+    int32_t count = 0;                 // 0: no tiles, the two-kernel stage
+};
+
 // Right operand X [K][N] of a scattering product C = A X on the device, in every precision
 // the products use: FP32 and FP64 row-major, and the BF16 or FP16 hi/lo parts for the MFMA
 // kernel, with the columns zero-padded to Np (a multiple of 128) and tiled by K chunks of 32
@@ -154,8 +187,11 @@ struct snrt_mesh {
     // host copies kept for the second-order set-up (user order)
     std::vector<int32_t> face_nbr_user;    // [nc*mf]
     std::vector<double> centroid_user;     // [nc*2], empty if none was given
+    std::vector<snrt::CellGeom32> geom_host;   // geom32
+    bool on_curve = false;                 // the internal order is the Hilbert curve's
     snrt::CellRecon32* recon32 = nullptr;  // second-order reconstruction vectors (internal
     snrt::CellRecon64* recon64 = nullptr;  // order); NULL until face midpoints are set
+    snrt::StageTiles tiles;                // and the tiles of its FP32 stage kernel
 };
 
 struct snrt_quad {
@@ -534,6 +570,14 @@ hipError_t launch_grad2_32(const snrt_mesh& m, const snrt_quad& q, const StepArg
                            const Limiter& lim, const float* psi, float* G, hipStream_t st);
 hipError_t launch_grad2_64(const snrt_mesh& m, const snrt_quad& q, const StepArgs64& a,
                            const Limiter& lim, const double* psi, double* G, hipStream_t st);
+// Both in one launch (sn_step2_tile.hip), for meshes with tiles; S NULL: isotropic scattering.
+bool stage2_tiled(const snrt_mesh& m, const snrt_quad& q);
+// StageTiles::geom of n rows from the mesh's records
+hipError_t launch_stage_geom(const snrt_mesh& m, const StageRow* rows, StageGeom* geom, int64_t n,
+                             hipStream_t st);
+hipError_t launch_stage2_32(const snrt_mesh& m, const snrt_quad& q, const StepArgs32& a,
+                            const Limiter& lim, const float* psi, const float* S,
+                            const float* psi_n, float* out, hipStream_t st);
 hipError_t launch_flux2_32(const snrt_mesh& m, const snrt_quad& q, const StepArgs32& a,
                            const float* psi, const float* G, const float* S,
                            const float* psi_n, float* out, hipStream_t st);
