@@ -1,6 +1,7 @@
 // C ABI of libsnrt: argument validation, handle lifetime, mesh renumbering and launches.
 // Declarations and the meaning of every argument are in include/snrt.h.
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -308,23 +309,21 @@ snrt_status make_stage_tiles(snrt_mesh* m) {
     const int32_t mf = m->mf;
     if (nc == 0) return SNRT_OK;
     const std::vector<CellGeom32>& geom = m->geom_host;
-    // an unused slot holds the cell itself
-    const auto used = [&](int64_t k, int f) { return geom[k].nbr[f] != (int32_t)k; };
-    const auto back = [&](int64_t j, int64_t k) {      // the slot of cell k in cell j
+    const auto back = [&](int32_t j, int32_t k) {      // the slot of cell k in cell j
         int g = 0;
-        while (g < mf && geom[j].nbr[g] != (int32_t)k) ++g;
+        while (g < mf && geom[j].nbr[g] != k) ++g;
         return g;
     };
-    for (int64_t k = 0; k < nc; ++k)
+    for (int32_t k = 0; k < nc; ++k)
         for (int f = 0; f < mf; ++f) {
-            const int64_t j = geom[k].nbr[f];
-            if (j < 0 || !used(k, f)) continue;
+            const int32_t j = geom[k].nbr[f];
+            if (j < 0 || j == k) continue;              // an unused slot holds the cell itself
             const float* n = geom[k].n[f];
             const float* nj = geom[j].n[back(j, k)];
             if (n[0] != -nj[0] || n[1] != -nj[1] || back(k, j) != f) return SNRT_OK;
         }
     if (!finite_centroids(m->centroid_user.data(), nc)) return SNRT_OK;
-    std::vector<int32_t> order(nc), place(nc);          // cells along the curve
+    std::vector<int32_t> order(nc);                     // cells along the curve
     std::iota(order.begin(), order.end(), 0);
     if (!m->on_curve) {
         std::vector<int64_t> curve(nc), to_int(nc);
@@ -333,70 +332,65 @@ snrt_status make_stage_tiles(snrt_mesh* m) {
         for (int64_t k = 0; k < nc; ++k) to_int[m->to_user[k]] = k;
         for (int64_t i = 0; i < nc; ++i) order[i] = (int32_t)to_int[curve[i]];
     }
-    for (int64_t i = 0; i < nc; ++i) place[order[i]] = (int32_t)i;
     const int64_t cap = std::clamp<int64_t>(nc / m->num_cu, 16, kStageCells);
     std::vector<StageTile> tiles;
     std::vector<StageRow> rows;
-    rows.reserve(nc * 2);
-    std::vector<int32_t> face_row(nc * 4, -1);         // of the tile in hand
-    std::vector<char> halo(nc, 0);
-    std::vector<int32_t> cells;
-    for (int64_t first = 0; first < nc;) {
-        int64_t end = first;
-        const auto inside = [&](int64_t j) { return place[j] >= first && place[j] < end; };
-        for (int32_t faces = 0; end < nc && end - first < cap; ++end) {
-            const int64_t k = order[end];
+    rows.reserve(nc + nc / 2);
+    std::vector<int32_t> local(nc, -1), cells;         // a cell's place among the tile's rows
+    std::vector<std::array<int32_t, 4>> face_row;      // of those rows
+    for (int64_t first = 0, end; first < nc; first = end) {
+        cells.clear();
+        int32_t faces = 0;
+        for (end = first; end < nc && end - first < cap; ++end) {
+            const int32_t k = order[end];
             int32_t add = 0;
             for (int f = 0; f < mf; ++f) {
-                const int64_t j = geom[k].nbr[f];
-                add += used(k, f) && !(j >= 0 && inside(j));
+                const int32_t j = geom[k].nbr[f];
+                add += j != k && (j < 0 || local[j] < 0);
             }
             if (end > first && faces + add > kStageFaces) break;
             faces += add;
+            local[k] = (int32_t)cells.size();
+            cells.push_back(k);
         }
-        cells.assign(order.begin() + first, order.begin() + end);
         StageTile t = {(int32_t)rows.size(), (int32_t)cells.size(), 0, 0};
-        for (int32_t i = 0; i < t.cells; ++i)
-            for (int f = 0; f < mf; ++f) {
-                const int64_t j = geom[cells[i]].nbr[f];
-                if (j < 0 || inside(j) || halo[j]) continue;
-                halo[j] = 1;
-                cells.push_back((int32_t)j);
-            }
-        t.halo = (int32_t)cells.size() - t.cells;
+        face_row.assign(cells.size(), {-1, -1, -1, -1});
         int32_t next = 0;
         for (int32_t i = 0; i < t.cells; ++i)
             for (int f = 0; f < mf; ++f) {
-                const int64_t k = cells[i], j = geom[k].nbr[f];
-                if (!used(k, f) || face_row[k * 4 + f] >= 0) continue;
-                face_row[k * 4 + f] = next;
-                if (j >= 0) face_row[j * 4 + back(j, k)] = next;
+                const int32_t k = cells[i], j = geom[k].nbr[f];
+                if (j == k || face_row[i][f] >= 0) continue;
+                face_row[i][f] = next;
+                if (j >= 0) {
+                    if (local[j] < 0) {
+                        local[j] = (int32_t)cells.size();
+                        cells.push_back(j);
+                        face_row.push_back({-1, -1, -1, -1});
+                    }
+                    face_row[local[j]][back(j, k)] = next;
+                }
                 ++next;
             }
-        for (const int32_t k : cells) {
+        t.halo = (int32_t)cells.size() - t.cells;
+        for (size_t i = 0; i < cells.size(); ++i) {
+            const int32_t k = cells[i];
+            local[k] = -1;
             StageRow r = {k, {0, 0}, 0.5f * geom[k].inv_area, {}};
             bool interior = true;
-            int32_t any = 0;
-            for (int f = 0; f < mf; ++f) {
-                interior &= !(used(k, f) && geom[k].nbr[f] < 0);
-                any = std::max(any, face_row[(int64_t)k * 4 + f]);
-            }
+            const int32_t any = *std::max_element(face_row[i].begin(), face_row[i].end());
             for (int f = 0; f < 4; ++f) {
-                const int32_t row = face_row[(int64_t)k * 4 + f], j = geom[k].nbr[f];
+                const int32_t row = face_row[i][f], j = geom[k].nbr[f];
                 const uint32_t e = row < 0 ? any | kFaceSkip
                                            : row | (j < 0 ? kFaceBoundary : 0) |
                                                  (j < 0 || k < j ? kFaceLower : 0);
-                r.faces[f / 2] |= (e | (f == 0 && interior ? kFaceInterior : 0)) << (16 * (f % 2));
+                interior &= j >= 0;
+                r.faces[f / 2] |= e << (16 * (f % 2));
                 r.nbr[f] = j;
             }
+            r.faces[0] |= interior ? kFaceInterior : 0;
             rows.push_back(r);
         }
-        for (const int32_t k : cells) {
-            halo[k] = 0;
-            for (int f = 0; f < 4; ++f) face_row[(int64_t)k * 4 + f] = -1;
-        }
         tiles.push_back(t);
-        first = end;
     }
     StageTiles d;
     const char* what = "snrt_mesh_set_face_midpoints: upload";
