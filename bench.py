@@ -152,8 +152,11 @@ def timed(fn, n, stream):
 
 def product_rate(S, psi, reps: int = 10, passes: int = 3, kernel: str = "k_gemm_bf16",
                  peak: float = None):
-    """Executed TFLOP/s of the scattering product on state psi: the BF16 hi+lo product
-    (three passes, against the BF16 MFMA peak) or the FP32 one (one pass, FP32 MFMA peak)."""
+    """Rate of the scattering product on state psi.  The kernels here are invariant under the
+    azimuth of their product rules and run through azimuthal modes (k_az_product: bound by
+    memory, one read and one write of the state).  With SNRT_AZIMUTH=0 the dense product runs:
+    executed TFLOP/s of the BF16 hi+lo product (three passes, against the BF16 MFMA peak) or the
+    FP32 one (one pass, FP32 MFMA peak)."""
     import torch
     from paper_2205_08417_amd import snrt
     peak = BF16_PEAK_TFLOPS if peak is None else peak
@@ -164,13 +167,25 @@ def product_rate(S, psi, reps: int = 10, passes: int = 3, kernel: str = "k_gemm_
     apply()
     torch.cuda.synchronize()
     ms = timed(apply, reps, stream)
+    if modes_on():
+        gbs = 2.0 * psi.element_size() * S.nc * S.nq / (ms * 1e-3) / 1e9
+        return {"kernel": "k_az_product", "ms": ms, "gbs": gbs, "hbm_frac": gbs / HBM_PEAK_GBS}
     tflops = passes * 2.0 * S.nc * S.nq * S.nq / (ms * 1e-3) / 1e12
     return {"kernel": kernel, "ms": ms, "executed_tflops": tflops,
             "peak_tflops": peak, "mfma_utilization": tflops / peak}
 
 
+def modes_on() -> bool:
+    """Whether azimuth-invariant kernels run through azimuthal modes (read once per process)."""
+    return os.environ.get("SNRT_AZIMUTH", "1") != "0"
+
+
 def step_form() -> str:
-    """How the library runs an explicit dense step (SNRT_STEP_FUSED, read once per process)."""
+    """How the library runs an explicit dense step (SNRT_AZIMUTH, SNRT_STEP_FUSED, read once per
+    process)."""
+    if modes_on():
+        return ("one launch: k_az_step, the scattering product through azimuthal modes and the "
+                "update of the same cells (product rules, kernels of the angle)")
     if os.environ.get("SNRT_STEP_FUSED", "1") == "0":
         return "two launches: scattering product into the workspace, then k_step"
     return ("one launch: k_gemm_step, the scattering product whose tiles run the update of "
@@ -178,7 +193,10 @@ def step_form() -> str:
 
 
 def transposed_step_form() -> str:
-    """How the library runs a dense transposed step (the same switch as the forward)."""
+    """How the library runs a dense transposed step (the same switches as the forward)."""
+    if modes_on():
+        return ("one launch: k_az_adjoint, the transposed product through azimuthal modes, the "
+                "update (with the dose functional's term) and the gradient sums")
     if os.environ.get("SNRT_STEP_FUSED", "1") == "0":
         return ("two launches: transposed product into the workspace, then k_adjoint_p with "
                 "the dose functional's term")
@@ -582,12 +600,10 @@ def bench_moments(steps, warmup: int, degree: int = 8):
 
 def bench_second_order(steps: int, warmup: int):
     """Second-order scheme on the headline checkerboard (198 450 cells x 256 ordinates,
-    isotropic, FP32): one Heun step = two stages of limited-gradient + reconstructed-flux
-    kernels.  Algorithmic bytes per step: per stage the gradient kernel reads psi and writes
-    the two-component gradient (12 B per update) and the update kernel reads psi and the
-    gradient and writes the stage result (16 B), the final stage also reads psi^n (4 B):
-    60 B per update, plus 2 x 64 B of geometry and 2 x 64 B of reconstruction vectors per
-    cell and stage."""
+    isotropic, FP32): one Heun step = two stages, each one launch that keeps the limited
+    gradients in LDS.  Algorithmic bytes per step: a stage reads psi and writes its result
+    (8 B per update), the final one also reads psi^n (4 B): 20 B per update, plus 96 B of
+    geometry per cell and stage."""
     import torch
     from paper_2205_08417_amd import inputs as I
     from paper_2205_08417_amd.solver import Solver
@@ -611,7 +627,7 @@ def bench_second_order(steps: int, warmup: int):
 
     ms = run("barth-jespersen")
     ms_vk = run("venkatakrishnan")
-    alg = P.ncells * (60 * P.nq + 2 * 2 * (64 + 64))
+    alg = P.ncells * (20 * P.nq + 2 * 96)
     from oracle import oracle as o
     op = o.OracleProblem.from_problem(P)
     # the oracle's Heun step is taken over the whole state (it has no cell selection)
