@@ -317,10 +317,12 @@ snrt_status make_stage_tiles(snrt_mesh* m) {
     for (int32_t k = 0; k < nc; ++k)
         for (int f = 0; f < mf; ++f) {
             const int32_t j = geom[k].nbr[f];
-            if (j < 0 || j == k) continue;              // an unused slot holds the cell itself
+            if (j <= k) continue;      // a boundary, an unused slot (the cell itself), or seen from j
             const float* n = geom[k].n[f];
             const float* nj = geom[j].n[back(j, k)];
-            if (n[0] != -nj[0] || n[1] != -nj[1] || back(k, j) != f) return SNRT_OK;
+            if (n[0] != -nj[0] || n[1] != -nj[1]) return SNRT_OK;
+            for (int g = 0; g < f; ++g)
+                if (geom[k].nbr[g] == j) return SNRT_OK;
         }
     if (!finite_centroids(m->centroid_user.data(), nc)) return SNRT_OK;
     std::vector<int32_t> order(nc);                     // cells along the curve
