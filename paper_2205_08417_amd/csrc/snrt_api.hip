@@ -1,7 +1,6 @@
 // C ABI of libsnrt: argument validation, handle lifetime, mesh renumbering and launches.
 // Declarations and the meaning of every argument are in include/snrt.h.
 #include <algorithm>
-#include <array>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -300,100 +299,25 @@ snrt_status snrt_mesh_create(snrt_mesh** out, int64_t nc, int32_t mf, const int3
 
 namespace {
 
-// The tiles of the second-order stage kernel: cells along a Hilbert curve, whatever their
-// numbering, as long as the faces fit a block's rows.  The two sides of a face decide from their own normals which of them is
-// upwind; that they agree takes normals that are exact negatives in FP32 and one face at most
-// between two cells, else there are no tiles.
+// The tiles of the second-order stage kernel: cells along a Hilbert curve, whatever their numbering.
 snrt_status make_stage_tiles(snrt_mesh* m) {
     const int64_t nc = m->nc;
-    const int32_t mf = m->mf;
-    if (nc == 0) return SNRT_OK;
-    const std::vector<CellGeom32>& geom = m->geom_host;
-    const auto back = [&](int32_t j, int32_t k) {      // the slot of cell k in cell j
-        int g = 0;
-        while (g < mf && geom[j].nbr[g] != k) ++g;
-        return g;
-    };
-    for (int32_t k = 0; k < nc; ++k)
-        for (int f = 0; f < mf; ++f) {
-            const int32_t j = geom[k].nbr[f];
-            if (j <= k) continue;      // a boundary, an unused slot (the cell itself), or seen from j
-            const float* n = geom[k].n[f];
-            const float* nj = geom[j].n[back(j, k)];
-            if (n[0] != -nj[0] || n[1] != -nj[1]) return SNRT_OK;
-            for (int g = 0; g < f; ++g)
-                if (geom[k].nbr[g] == j) return SNRT_OK;
-        }
-    if (!finite_centroids(m->centroid_user.data(), nc)) return SNRT_OK;
-    std::vector<int32_t> order(nc);                     // cells along the curve
-    std::iota(order.begin(), order.end(), 0);
+    if (nc == 0 || !finite_centroids(m->centroid_user.data(), nc)) return SNRT_OK;
+    std::vector<int32_t> order;                         // cells along the curve
     if (!m->on_curve) {
+        order.resize(nc);
         std::vector<int64_t> curve(nc), to_int(nc);
         std::iota(curve.begin(), curve.end(), 0);
         hilbert_sort(curve, m->centroid_user.data());
         for (int64_t k = 0; k < nc; ++k) to_int[m->to_user[k]] = k;
         for (int64_t i = 0; i < nc; ++i) order[i] = (int32_t)to_int[curve[i]];
     }
-    const int64_t cap = std::clamp<int64_t>(nc / m->num_cu, 16, kStageCells);
-    std::vector<StageTile> tiles;
-    std::vector<StageRow> rows;
-    rows.reserve(nc + nc / 2);
-    std::vector<int32_t> local(nc, -1), cells;         // a cell's place among the tile's rows
-    std::vector<std::array<int32_t, 4>> face_row;      // of those rows
-    for (int64_t first = 0, end; first < nc; first = end) {
-        cells.clear();
-        int32_t faces = 0;
-        for (end = first; end < nc && end - first < cap; ++end) {
-            const int32_t k = order[end];
-            int32_t add = 0;
-            for (int f = 0; f < mf; ++f) {
-                const int32_t j = geom[k].nbr[f];
-                add += j != k && (j < 0 || local[j] < 0);
-            }
-            if (end > first && faces + add > kStageFaces) break;
-            faces += add;
-            local[k] = (int32_t)cells.size();
-            cells.push_back(k);
-        }
-        StageTile t = {(int32_t)rows.size(), (int32_t)cells.size(), 0, 0};
-        face_row.assign(cells.size(), {-1, -1, -1, -1});
-        int32_t next = 0;
-        for (int32_t i = 0; i < t.cells; ++i)
-            for (int f = 0; f < mf; ++f) {
-                const int32_t k = cells[i], j = geom[k].nbr[f];
-                if (j == k || face_row[i][f] >= 0) continue;
-                face_row[i][f] = next;
-                if (j >= 0) {
-                    if (local[j] < 0) {
-                        local[j] = (int32_t)cells.size();
-                        cells.push_back(j);
-                        face_row.push_back({-1, -1, -1, -1});
-                    }
-                    face_row[local[j]][back(j, k)] = next;
-                }
-                ++next;
-            }
-        t.halo = (int32_t)cells.size() - t.cells;
-        for (size_t i = 0; i < cells.size(); ++i) {
-            const int32_t k = cells[i];
-            local[k] = -1;
-            StageRow r = {k, {0, 0}, 0.5f * geom[k].inv_area, {}};
-            bool interior = true;
-            const int32_t any = *std::max_element(face_row[i].begin(), face_row[i].end());
-            for (int f = 0; f < 4; ++f) {
-                const int32_t row = face_row[i][f], j = geom[k].nbr[f];
-                const uint32_t e = row < 0 ? any | kFaceSkip
-                                           : row | (j < 0 ? kFaceBoundary : 0) |
-                                                 (j < 0 || k < j ? kFaceLower : 0);
-                interior &= j >= 0;
-                r.faces[f / 2] |= e << (16 * (f % 2));
-                r.nbr[f] = j;
-            }
-            r.faces[0] |= interior ? kFaceInterior : 0;
-            rows.push_back(r);
-        }
-        tiles.push_back(t);
-    }
+    StageLayout layout;
+    if (!layout_stage_tiles(m->geom_host.data(), nc, m->mf, order.empty() ? nullptr : order.data(),
+                            std::clamp<int64_t>(nc / m->num_cu, 16, kStageCells), layout))
+        return SNRT_OK;
+    const std::vector<StageTile>& tiles = layout.tiles;
+    const std::vector<StageRow>& rows = layout.rows;
     StageTiles d;
     const char* what = "snrt_mesh_set_face_midpoints: upload";
     snrt_status s = SNRT_OK;

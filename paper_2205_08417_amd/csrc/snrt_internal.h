@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "../../include/snrt.h"
+#include "sn_stage_tiles.h"
 
 struct snrt_quad;
 
@@ -19,17 +20,6 @@ constexpr int kWave = 64;              // CDNA wavefront width
 constexpr int kStepBlock = 256;        // 4 waves, one cell per wave
 constexpr int kCellsPerBlock = kStepBlock / kWave;
 constexpr int kNumXcd = 8;             // MI355X: 8 accelerator complex dies
-
-// Per-cell geometry record, one 64-byte line: neighbours, n_ij (outward normal x length),
-// 1/A_i and A_i.  An unused face slot points at the cell itself with a zero normal.
-struct alignas(64) CellGeom32 {
-    int32_t nbr[4];
-    float n[4][2];
-    float inv_area;
-    float area;
-    float pad[2];
-};
-static_assert(sizeof(CellGeom32) == 64, "one cache line per cell");
 
 struct alignas(32) CellGeom64 {
     int32_t nbr[4];
@@ -55,32 +45,7 @@ struct alignas(64) CellRecon64 {
 };
 static_assert(sizeof(CellRecon64) == 128, "two cache lines per cell");
 
-// Tiles of the second-order stage kernel (sn_step2_tile.hip): neighbouring cells, and the cells
-// outside the tile that share a face with one inside (its halo), so that a block can hold the
-// upwind value of every face of the tile in LDS, one row per face.
-constexpr int kStageFaces = 158;       // face rows of a block, 64 lanes x 2 x 4 bytes each
-constexpr int kStageCells = 96;        // cells of a tile at most
-struct StageTile {
-    int32_t rows;                      // first of its StageRows: its cells, then its halo
-    int32_t cells, halo;
-    int32_t pad;
-};
-// A cell of a tile or of its halo, in whole words for two scalar loads.
-struct alignas(32) StageRow {
-    int32_t cell;
-    uint32_t faces[2];                 // face(f): the LDS row of the face, and who writes it
-    float half_inv_area;
-    int32_t nbr[4];
-    __host__ __device__ uint32_t face(int f) const { return faces[f / 2] >> (16 * (f % 2)) & 0xffffu; }
-};
-constexpr uint32_t kFaceRow = 0x1ff;        // the LDS row (an unused slot's: a used face's)
-constexpr uint32_t kFaceInterior = 0x1000;  // on face 0: no face of the cell is a boundary's
-constexpr uint32_t kFaceLower = 0x2000;     // the lower of the face's two cells, or the only one
-constexpr uint32_t kFaceBoundary = 0x4000;  // this side writes the ghost value as well
-constexpr uint32_t kFaceSkip = 0x8000;      // not a face of the tile, or an unused slot
-struct alignas(64) StageGeom {
-    float n[4][2], r[4][2];            // CellGeom32::n, CellRecon32::r_own
-};
+// The tiles of a mesh on the device.
 struct StageTiles {
     StageTile* tile = nullptr;         // [count]
     StageRow* rows = nullptr;
