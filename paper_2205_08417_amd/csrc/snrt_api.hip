@@ -36,13 +36,6 @@ uint64_t hilbert_index(uint32_t x, uint32_t y) {
     return d;
 }
 
-void drop_stage_tiles(snrt_mesh* m) {
-    dev_free(m->tiles.tile);
-    dev_free(m->tiles.rows);
-    dev_free(m->tiles.geom);
-    m->tiles = StageTiles();
-}
-
 bool finite_centroids(const double* centroid, int64_t nc) {
     for (int64_t i = 0; i < 2 * nc; ++i)
         if (!is_finite(centroid[i])) return false;
@@ -168,7 +161,9 @@ void snrt_mesh_destroy(snrt_mesh* m) {
     dev_free(m->geom64);
     dev_free(m->d_to_user);
     dev_free(m->d_partial);
-    drop_stage_tiles(m);
+    dev_free(m->tiles.tile);
+    dev_free(m->tiles.rows);
+    dev_free(m->tiles.geom);
     dev_free(m->recon32);
     dev_free(m->recon64);
     delete m;
@@ -299,9 +294,19 @@ snrt_status snrt_mesh_create(snrt_mesh** out, int64_t nc, int32_t mf, const int3
 
 namespace {
 
+// The reconstruction vectors into the tiles' records.
+snrt_status fill_stage_geom(const snrt_mesh& m, const StageTiles& t) {
+    hipError_t e = launch_stage_geom(m, t.rows, t.geom, t.nrows, nullptr);
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+    return e == hipSuccess ? SNRT_OK : hip_fail(e, "snrt_mesh_set_face_midpoints: stage tiles");
+}
+
 // The tiles of the second-order stage kernel: cells along a Hilbert curve, whatever their numbering.
+// They depend on the mesh alone and are made once, when the first midpoints are set; later midpoints
+// only change their records in place, so that a captured step stays valid.
 snrt_status make_stage_tiles(snrt_mesh* m) {
     const int64_t nc = m->nc;
+    if (m->tiles.count) return fill_stage_geom(*m, m->tiles);
     if (nc == 0 || !finite_centroids(m->centroid_user.data(), nc)) return SNRT_OK;
     std::vector<int32_t> order;                         // cells along the curve
     if (!m->on_curve) {
@@ -331,17 +336,10 @@ snrt_status make_stage_tiles(snrt_mesh* m) {
         dev_free(d.geom);
         return s;
     }
-    hipError_t e = launch_stage_geom(*m, d.rows, d.geom, (int64_t)rows.size(), nullptr);
-    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
-    if (e != hipSuccess) {
-        dev_free(d.tile);
-        dev_free(d.rows);
-        dev_free(d.geom);
-        return hip_fail(e, what);
-    }
     d.count = (int32_t)tiles.size();
+    d.nrows = (int64_t)rows.size();
     m->tiles = d;
-    return SNRT_OK;
+    return fill_stage_geom(*m, d);
 }
 
 }  // namespace
@@ -407,7 +405,6 @@ snrt_status snrt_mesh_set_face_midpoints(snrt_mesh* m, const double* face_mid) {
     if ((s = upload(m->recon32, r32.data(), nc, "snrt_mesh_set_face_midpoints: upload")) != SNRT_OK ||
         (s = upload(m->recon64, r64.data(), nc, "snrt_mesh_set_face_midpoints: upload")) != SNRT_OK)
         return s;
-    drop_stage_tiles(m);
     return make_stage_tiles(m);
 }
 

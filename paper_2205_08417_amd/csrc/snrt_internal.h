@@ -51,6 +51,7 @@ struct StageTiles {
     StageRow* rows = nullptr;
     StageGeom* geom = nullptr;         // of the same row
     int32_t count = 0;                 // 0: no tiles, the two-kernel stage
+    int64_t nrows = 0;
 };
 
 // Right operand X [K][N] of a scattering product C = A X on the device, in every precision

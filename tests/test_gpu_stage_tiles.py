@@ -57,3 +57,39 @@ def test_a_neighbour_in_two_slots_of_one_cell(side):
     S = Solver(P, reorder=False)
     assert rel_l2(_heun(S), _oracle(P)) <= TOL
     S.close()
+
+
+@pytest.mark.parametrize("mesh", ["triangles", "quads"])
+def test_a_captured_step_sees_midpoints_that_are_set_later(mesh):
+    """The step's graph is replayed after new face midpoints, with eager work between: the mesh's
+    records change in place, and every replay is the eager result."""
+    from paper_2205_08417_amd import snrt
+    from paper_2205_08417_amd.solver import Solver
+    m = I.quad_grid_mesh(23, 19) if mesh == "quads" else I.jittered_delaunay_mesh(21, 0.0, 1.0, seed=293)
+    P = small_problem(m, 8, 8, seed=294, inflow=True)
+    S = Solver(P)
+    x = S.initial_state()
+    out, other = torch.empty_like(x), torch.empty_like(x)
+    args = S.args()
+    S.step2(x, out, args)
+    torch.cuda.synchronize()
+    assert rel_l2(S.to_user(out).cpu().numpy(), _oracle(P)) <= TOL
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        S.step2(x, out, args)
+    rng = np.random.default_rng(295)
+    for rep in range(3):
+        # the face values of another point of every face
+        moved = dataclasses.replace(m, face_mid=m.face_mid + 0.02 * rng.uniform(-1, 1, m.face_mid.shape)
+                                    * np.abs(m.face_normal[..., ::-1]))
+        snrt.snrt_mesh_set_face_midpoints(S.mesh, moved.face_mid)
+        hold = [torch.full((1 << 14,), 1e30, device="cuda") for _ in range(8)]   # takes freed memory
+        S.step2(x, other, args)
+        out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, other), f"replay {rep}"
+        assert rel_l2(S.to_user(out).cpu().numpy(), _oracle(dataclasses.replace(P, mesh=moved))) <= TOL
+        del hold
+    S.close()
