@@ -220,9 +220,13 @@ typedef struct {
  * once per process, selects the product-then-step form; both give the same bits).
  * Kernels that are functions of Omega_q . Omega_p on a product rule (one weight per polar node, up
  * to 16 equally spaced azimuths or an even count up to 32, up to 16 polar nodes or an even count
- * up to 32; checked on the entries when the handle is made) run in every precision mode as FP32
+ * up to 32; checked on the entries when the handle is made) run in every precision mode as FP64
  * products of the azimuthal modes where that is faster, in one launch for triangles and
- * quadrilaterals; their product's error is that of FP32 rounding. */
+ * quadrilaterals.  The product is rounded to FP32 once, and every element of it is off by FP32
+ * rounding of that element for states of one sign: kernels with an entry below 2^-25 of the
+ * operator's norm (zeros, where a kernel ends at an angle) keep the general products.  Moment-form
+ * handles, whose general product goes through the moments, have the error of FP64 relative to the
+ * row's norm. */
 snrt_status snrt_step(const snrt_mesh* mesh, const snrt_quad* quad, const snrt_scatter* scatter,
                       const snrt_step_args* args, const float* psi_in, float* psi_out,
                       void* ws, size_t ws_bytes, void* stream);

@@ -5,16 +5,20 @@
 // azimuths only: S[k,l] = sum_{k',l'} a_{kk'}(l - l') psi[k',l'], a even in the difference.  A
 // real Fourier transform over the azimuths makes that one polar matrix per mode m,
 // D_m[k][k'] = sum_d a_{kk'}(d) cos(2 pi f_m d / na), instead of one nq x nq matrix:
-//     X = F psi,   Y_m = D_m X_m,   S = F^T Y,
+//     X = F psi,   Y_m = D_m X_m,   S = F Y   (F symmetric),
 // 3 * 2 nq * 16 operations per cell after the two foldings below instead of 2 nq * nq (nq =
-// 1024: 1/21).  What is left fits beside the transport update's memory traffic, so all of it
-// runs in FP32 on the matrix cores (v_mfma_f32_16x16x4_f32): no operand split, and an error
-// below that of the three-product BF16 split (product of a two-decade state: 1.3e-7).
+// 1024: 1/21).  The transforms mix signs, so that their error is relative to a row's norm, not to
+// its elements: in FP32 an element of S that a peaked kernel makes small (Henyey-Greenstein 0.95 on
+// 512 ordinates, one of them lit) was off by 6e-4 of itself and could be negative.  The modes are
+// therefore FP64 (v_mfma_f64_16x16x4_f64), S is rounded to FP32 once, and every element is as good
+// as with a product of nq positive terms (1.2e-7 at most in those cases).  The IMEX step of a 16-bit
+// handle keeps FP32 modes: its general solve goes through eigenvectors of mixed sign as well, in
+// less than FP32.
 // Measured against the general products' one-launch steps (BF16x3): 100 352 cells x 1024 ordinates
-// 0.235 against 0.658 ms (a copy of the state: 0.131), FP32 handles 1.8 ms; 299 538 x 512 with its
-// dose 0.348 against 0.690 ms; the transposed step on 74 498 x 512 0.13 against 0.237 ms.  What
-// bounds it now: the vector update (0.10 ms of issue at 1024 ordinates), the matrix instructions
-// (0.065 ms) and the row traffic overlap only across the waves between two barriers.
+// 0.305 against 0.653 ms (a copy of the state: 0.131; FP32 modes 0.232), FP32 handles 1.8 ms; 299 538
+// x 512 with its dose 0.434 against 0.690 ms (FP32 modes 0.348).  What bounds it: the vector update
+// (0.10 ms of issue at 1024 ordinates), the matrix instructions (0.13 ms: FP64 has half the FP32
+// rate) and the row traffic overlap only across the waves between two barriers.
 //
 // Foldings, so that every contraction is at most 16 long (shorter ones are padded with zeros in
 // the operands, empty azimuthal slots hold zeros):
@@ -30,17 +34,14 @@
 // (0.35 against 0.24 ms per step at 100 352 x 1024), so rows change order through the wave's own
 // corner of LDS.  The waves of eight cells form a block and exchange through LDS:
 //   1. azimuthal fold (lane-local), X[k][m] = sum_l x[k][l] F[l][m] per class (4 MFMA), to LDS as
-//      [class][polar half][m][cell][k];
-//   2. a wave takes the modes 2j, 2j + 1 of a class: their 2 x 8 cells are the 16 columns of
-//      Y = D X (the cosine and sine of one frequency share D), polar fold around it, in place;
+//      [class][polar half][slot of m][cell][k];
+//   2. a wave takes two modes of one frequency of a class: their 2 x 8 cells are the 16 columns of
+//      Y = D X (they share D), polar fold around it, in place;
 //   3. S[l][k] = sum_m F[l][m] Y[k][m] per class, azimuthal unfold: S in the layout of the row.
-// The K order of an MFMA is free, so lane groups take k = 4 l4 + s at step s: its four values are
-// one 16-byte LDS access.
-//
-// LDS: a mode's plane is 8 cells x 64 bytes, planes 576 bytes apart, 16-byte granule g of
-// (m, cell) at g ^ swz(m, cell): 16 consecutive lanes of the 16-byte accesses of 1 and 2 and the
-// 4-byte reads of 3 fall on different banks.  Two buffers, tiles alternating: a wave that is a
-// tile ahead writes the buffer that nobody reads any more.
+// The K order of an MFMA and the order of its rows are free, so a lane group's four values are
+// adjacent in LDS (Modes<R>), and the symmetric basis makes stages 1 and 3 use the same registers.
+// One exchange buffer and a barrier before stage 1's stores: two FP64 buffers would not fit beside
+// the corners (1024 ordinates: 66 KB), or would halve the blocks of a CU (512: 33 KB).
 #pragma once
 
 #include <cstddef>
@@ -51,21 +52,69 @@ namespace snrt {
 namespace az {
 
 constexpr int kCells = 8;                    // cells of a block's tile, one wave each
-constexpr int kPlane = 144;                  // floats of a mode's plane (576 bytes)
-constexpr int kClass = 16 * kPlane;          // floats of a class
 
-__device__ __forceinline__ int swz(int m, int cell) {
-    return ((m >> 2) ^ (cell >> 2) ^ ((m & 1) << 1)) & 3;
-}
+// The precision R of the modes: FP64, or FP32 in the IMEX step of the 16-bit precisions.
+// Accumulator rows of a lane group q (lane >> 4), as places 4 q .. 4 q + 3: the rows themselves in
+// FP32, rows q, 4 + q, 8 + q, 12 + q in FP64.  row() is its own inverse.
+// A cell's 16 polar places in a plane are 16-byte granules, granule g at g ^ turn(cell); planes are
+// one granule longer than their eight cells: 8 cells at one g, and 8 planes, cover the banks once.
+template <typename R>
+struct Modes;
+template <>
+struct Modes<double> {
+    typedef double V4 __attribute__((ext_vector_type(4)));
+    typedef double V2 __attribute__((ext_vector_type(2)));
+    static constexpr int PLANE = 130;
+    __device__ static int row(int place) { return 4 * (place & 3) + (place >> 2); }
+    __device__ static V4 mfma(double a, double b, const V4& c) {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    }
+    // offset of a polar place of a cell, and places 4 q .. 4 q + 3
+    __device__ static int at(int place, int cell) { return (((place >> 1) ^ cell) << 1) + (place & 1); }
+    __device__ __forceinline__ static V4 load(const double* p, int q, int cell) {
+        const V2 a = *reinterpret_cast<const V2*>(p + at(4 * q, cell));
+        const V2 b = *reinterpret_cast<const V2*>(p + at(4 * q + 2, cell));
+        return V4{a[0], a[1], b[0], b[1]};
+    }
+    __device__ __forceinline__ static void store(double* p, int q, int cell, const V4& v) {
+        *reinterpret_cast<V2*>(p + at(4 * q, cell)) = V2{v[0], v[1]};
+        *reinterpret_cast<V2*>(p + at(4 * q + 2, cell)) = V2{v[2], v[3]};
+    }
+};
+template <>
+struct Modes<float> {
+    typedef f32x4 V4;
+    static constexpr int PLANE = 132;
+    __device__ static int row(int place) { return place; }
+    __device__ static V4 mfma(float a, float b, const V4& c) {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    }
+    __device__ static int at(int place, int cell) {
+        return (((place >> 2) ^ ((cell ^ (cell >> 2)) & 3)) << 2) + (place & 3);
+    }
+    __device__ __forceinline__ static V4 load(const float* p, int q, int cell) {
+        return *reinterpret_cast<const V4*>(p + at(4 * q, cell));
+    }
+    __device__ __forceinline__ static void store(float* p, int q, int cell, const V4& v) {
+        *reinterpret_cast<V4*>(p + at(4 * q, cell)) = v;
+    }
+};
+template <typename R>
+using V4 = typename Modes<R>::V4;
+template <typename R>
+constexpr int kPlane = Modes<R>::PLANE;      // elements of a mode's plane
+template <typename R>
+constexpr int kClass = 16 * kPlane<R>;       // and of a class
 
-__device__ __forceinline__ f32x4 mfma4(const f32x4& a, const f32x4& b, f32x4 acc) {
+template <typename R>
+__device__ __forceinline__ V4<R> mfma4(const V4<R>& a, const V4<R>& b, V4<R> acc) {
 #pragma unroll
-    for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s], b[s], acc, 0, 0, 0);
+    for (int s = 0; s < 4; ++s) acc = Modes<R>::mfma(a[s], b[s], acc);
     return acc;
 }
 
 // How a row is cut: AZ azimuthal classes, MU polar halves, WPC waves per cell, SEG segments per
-// wave, ITEMS mode pairs per wave in stage 2 (each with MU matrices).
+// wave, ITEMS pairs of mode slots per wave in stage 2 (each with MU matrices).
 // RV = 0: 16 AZ azimuths, rows in whole 16-byte pieces; else the azimuths do not fill their slots
 // and a lane owns RV (even) ordinates of a wave's piece of the row, 64 apart (as in the step
 // kernel's striped rows), the last RAGGED of which may lie past its end.
@@ -77,8 +126,13 @@ struct Shape {
     static constexpr int WAVES = kCells * WPC;
     static constexpr int THREADS = WAVES * kWave;
     static constexpr int ITEMS = AZ * 8 / WAVES;
-    static constexpr int LDS = AZ * MU * kClass;     // floats of one buffer
+    template <typename R>
+    static constexpr int LDS = AZ * MU * kClass<R>;  // elements of the exchange
     static constexpr int RAGGED = 2;
+    // eight values of every row in a lane (six do not fit either): the registers are full
+    static constexpr bool FULL = SEG == 2 && (RV == 0 || RV >= 6);
+    // waves per SIMD that the step's registers are bounded to
+    static constexpr int STEP_WAVES = SEG == 1 && RV == 2 ? 6 : 4;
     // class of segment i; whether a lane has ordinate v of segment i at all
     static constexpr int az(int i) { return i % AZ; }
     static constexpr bool has(int i, int v) { return RV == 0 || 4 * i + v < RV; }
@@ -96,7 +150,8 @@ struct Lane {
     bool valid, exists_[RAG ? P::RAGGED : P::SEG];
     uint32_t off[RAG ? 1 + P::RAGGED : P::SEG];
     int mem[N], mat[P::SEG];
-    __device__ __forceinline__ Lane(const AzOperand& op) {
+    template <typename R>
+    __device__ __forceinline__ Lane(const AzModes<R>& op) {
         wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         lane = threadIdx.x & (kWave - 1);
         kk = lane & 15;
@@ -257,60 +312,65 @@ __device__ __forceinline__ void to_memory_order(f32x4 (&x)[P::SEG], const Lane<P
 }
 
 // Azimuthal fold of a wave's segments and its inverse: the same sums.
-template <typename P>
-__device__ __forceinline__ void fold(f32x4 (&x)[P::SEG]) {
+template <typename P, typename V>
+__device__ __forceinline__ void fold(V (&x)[P::SEG]) {
     if constexpr (P::AZ == 2) {
 #pragma unroll
         for (int i = 0; i < P::SEG; i += 2) {
-            const f32x4 a = x[i], b = x[i + 1];
+            const V a = x[i], b = x[i + 1];
             x[i] = a + b;
             x[i + 1] = a - b;
         }
     }
 }
 
-// The azimuthal transforms of stages 1 and 3, in registers or (the kernels whose rows leave no
-// room for them) in LDS, from where each use reads them again: 16 registers that the transposed
-// and the IMEX step would otherwise spill (IMEX, 100 352 x 1024: 0.379 -> 0.304 ms; the 74 498 x
-// 512 gradient 2.55 -> 2.31).
-template <typename P, bool IN_LDS>
+// The azimuthal transforms, the same numbers in stages 1 and 3 (the basis is symmetric), in
+// registers or, in the kernels whose rows leave no room for them, in LDS.
+template <typename P, typename R, bool IN_LDS>
 struct Fourier {
-    f32x4 f[IN_LDS ? 1 : 2 * P::AZ];
-    const f32x4* lds;
-    // space: 2 AZ kWave f32x4 of LDS (IN_LDS; a block barrier follows)
-    __device__ __forceinline__ Fourier(const AzOperand& op, const Lane<P>& ln, f32x4* space) {
-        const f32x4* src = reinterpret_cast<const f32x4*>(op.f1);     // f3 follows f1
+    V4<R> f[IN_LDS ? 1 : P::AZ];
+    const V4<R>* lds;
+    // space: AZ kWave V4 of LDS (IN_LDS; a block barrier follows)
+    __device__ __forceinline__ Fourier(const AzModes<R>& op, const Lane<P>& ln, V4<R>* space) {
+        const V4<R>* src = reinterpret_cast<const V4<R>*>(op.f);
         if constexpr (IN_LDS) {
-            for (int i = threadIdx.x; i < 2 * P::AZ * kWave; i += P::THREADS) space[i] = src[i];
+            for (int i = threadIdx.x; i < P::AZ * kWave; i += P::THREADS) space[i] = src[i];
             lds = space + ln.lane;
         } else {
 #pragma unroll
-            for (int a = 0; a < 2 * P::AZ; ++a) f[a] = src[a * kWave + ln.lane];
+            for (int a = 0; a < P::AZ; ++a) f[a] = src[a * kWave + ln.lane];
         }
     }
-    // stage 0 (to modes) or 1 (back), azimuthal class a
-    __device__ __forceinline__ f32x4 at(int stage, int a) const {
-        if constexpr (IN_LDS) return lds[(stage * P::AZ + a) * kWave];
-        else return f[stage * P::AZ + a];
+    __device__ __forceinline__ V4<R> at(int a) const {      // of azimuthal class a
+        if constexpr (IN_LDS) return lds[a * kWave];
+        else return f[a];
     }
 };
 
-// The polar matrices of a wave's mode pairs.
-template <typename P>
+// The polar matrices of a wave's pairs, and where their two modes lie in the exchange.
+template <typename P, typename R>
 struct Ops {
-    f32x4 d[P::ITEMS][P::MU];
-    __device__ __forceinline__ Ops(const float* __restrict__ mats, const Lane<P>& ln) {
+    V4<R> d[P::ITEMS][P::MU];
+    int at[P::ITEMS];
+    __device__ __forceinline__ Ops(const AzModes<R>& op, const R* __restrict__ mats,
+                                   const Lane<P>& ln) {
         load(d, mats, ln);
+#pragma unroll
+        for (int i = 0; i < P::ITEMS; ++i) {
+            const int az = az_of(ln, i);
+            const int slot = op.slots[(az * 8 + (ln.wave & 7)) * 2 + ((ln.lane >> 3) & 1)];
+            at[i] = az * P::MU * kClass<R> + slot * kPlane<R> + (ln.lane & 7) * 16;
+        }
     }
-    // mats: [class = mu * AZ + az][pair][which][lane] of float4
-    __device__ __forceinline__ static void load(f32x4 (&d)[P::ITEMS][P::MU],
-                                                const float* __restrict__ mats,
+    // mats: [class = mu * AZ + az][pair][which][lane] of V4
+    __device__ __forceinline__ static void load(V4<R> (&d)[P::ITEMS][P::MU],
+                                                const R* __restrict__ mats,
                                                 const Lane<P>& ln) {
 #pragma unroll
         for (int i = 0; i < P::ITEMS; ++i)
 #pragma unroll
             for (int mu = 0; mu < P::MU; ++mu)
-                d[i][mu] = reinterpret_cast<const f32x4*>(
+                d[i][mu] = reinterpret_cast<const V4<R>*>(
                     mats)[(((mu * P::AZ + az_of(ln, i)) * 8 + (ln.wave & 7)) * 2) * kWave + ln.lane];
     }
     __device__ __forceinline__ static int az_of(const Lane<P>& ln, int i) {
@@ -318,79 +378,90 @@ struct Ops {
     }
 };
 
-// Stage 1: the row segments x of this wave into LDS as modes.
-template <typename P, bool FL>
-__device__ __forceinline__ void to_modes(f32x4 (&x)[P::SEG], const Fourier<P, FL>& fr,
-                                         const Lane<P>& ln, float* __restrict__ lds) {
-    fold<P>(x);
-    float* at = lds + ln.kk * kPlane + ln.cell * 16 + ((ln.l4 ^ swz(ln.kk, ln.cell)) << 2);
+// Stage 1: the row segments x of this wave into LDS as modes, once the block has read the modes of
+// the tile before.
+template <typename P, typename R, bool FL>
+__device__ __forceinline__ void to_modes(const f32x4 (&x)[P::SEG], const Fourier<P, R, FL>& fr,
+                                         const Lane<P>& ln, R* __restrict__ lds) {
+    V4<R> u[P::SEG];
+#pragma unroll
+    for (int i = 0; i < P::SEG; ++i) u[i] = __builtin_convertvector(x[i], V4<R>);
+    fold<P>(u);
+#pragma unroll
+    for (int i = 0; i < P::SEG; ++i) u[i] = mfma4<R>(u[i], fr.at(P::az(i)), V4<R>{0, 0, 0, 0});
+    lds_barrier();
+    R* at = lds + ln.kk * kPlane<R> + ln.cell * 16;
 #pragma unroll
     for (int i = 0; i < P::SEG; ++i)
-        *reinterpret_cast<f32x4*>(at + (P::az(i) * P::MU + ln.mu0 + i / P::AZ) * kClass) =
-            mfma4(x[i], fr.at(0, P::az(i)), f32x4{0, 0, 0, 0});
+        Modes<R>::store(at + (P::az(i) * P::MU + ln.mu0 + i / P::AZ) * kClass<R>, ln.l4, ln.cell,
+                        u[i]);
 }
 
-// y = A x for a pair of modes.  The pair of modes 0 and na / 2 (j = 0 of class 0) has a matrix for
+// y = A x for a pair of modes.  The pair of modes 0 and half (pair 0 of class 0) has a matrix for
 // each: second (LDS) is the other one's, null elsewhere.
-__device__ __forceinline__ f32x4 apply_pair(const f32x4& d, const f32x4* second, const f32x4& x,
+template <typename R>
+__device__ __forceinline__ V4<R> apply_pair(const V4<R>& d, const V4<R>* second, const V4<R>& x,
                                             int lane) {
-    const f32x4 zero{0, 0, 0, 0};
-    if (!second) return mfma4(d, x, zero);
+    const V4<R> zero{0, 0, 0, 0};
+    if (!second) return mfma4<R>(d, x, zero);
     const bool hi = (lane & 8) != 0;
-    const f32x4 y = mfma4(d, hi ? zero : x, zero);
-    return mfma4(second[lane], hi ? x : zero, y);
+    const V4<R> y = mfma4<R>(d, hi ? zero : x, zero);
+    return mfma4<R>(second[lane], hi ? x : zero, y);
 }
 
 // Stage 2: f(item, polar class, column values) on this wave's mode pairs, in place.
-template <typename P, typename F>
-__device__ __forceinline__ void on_modes(const Lane<P>& ln, float* __restrict__ lds, F&& f) {
-    const int cell = ln.lane & 7, m = 2 * (ln.wave & 7) + ((ln.lane >> 3) & 1);
-    float* at = lds + m * kPlane + cell * 16 + ((ln.l4 ^ swz(m, cell)) << 2);
+template <typename P, typename R, typename F>
+__device__ __forceinline__ void on_modes(const Ops<P, R>& op, const Lane<P>& ln,
+                                         R* __restrict__ lds, F&& f) {
+    using M = Modes<R>;
+    const int cell = ln.lane & 7;
 #pragma unroll
     for (int i = 0; i < P::ITEMS; ++i) {
-        f32x4* s = reinterpret_cast<f32x4*>(at + Ops<P>::az_of(ln, i) * P::MU * kClass);
+        R* s = lds + op.at[i];
+        const V4<R> a = M::load(s, ln.l4, cell);
         if constexpr (P::MU == 1) {
-            *s = f(i, 0, *s);
+            M::store(s, ln.l4, cell, f(i, 0, a));
         } else {
-            f32x4* t = s + kClass / 4;
-            const f32x4 a = *s, b = *t;
-            const f32x4 u = f(i, 0, a + b), v = f(i, 1, a - b);
-            *s = u + v;
-            *t = u - v;
+            const V4<R> b = M::load(s + kClass<R>, ln.l4, cell);
+            const V4<R> u = f(i, 0, a + b), v = f(i, 1, a - b);
+            M::store(s, ln.l4, cell, u + v);
+            M::store(s + kClass<R>, ln.l4, cell, u - v);
         }
     }
 }
 
-// The second matrices of the pair of modes 0 and na / 2 into LDS, one per polar class, and where a
+// The second matrices of the pair of modes 0 and half into LDS, one per polar class, and where a
 // wave finds them (null if its item is another pair).  In LDS rather than read from memory at use:
 // loads return in order, so a wait on one in the loop would also wait for the rows in flight.
-template <typename P>
-__device__ __forceinline__ void load_second(const float* __restrict__ mats, f32x4* second) {
+template <typename P, typename R>
+__device__ __forceinline__ void load_second(const R* __restrict__ mats, V4<R>* second) {
     if (threadIdx.x < kWave * P::MU)
-        second[threadIdx.x] = reinterpret_cast<const f32x4*>(
+        second[threadIdx.x] = reinterpret_cast<const V4<R>*>(
             mats)[((threadIdx.x >> 6) * P::AZ * 8 * 2 + 1) * kWave + (threadIdx.x & (kWave - 1))];
 }
-template <typename P>
-__device__ __forceinline__ const f32x4* second_of(const f32x4* second, const Lane<P>& ln, int i,
-                                                  int mu) {
-    return (ln.wave & 7) == 0 && Ops<P>::az_of(ln, i) == 0 ? second + mu * kWave : nullptr;
+template <typename P, typename R, typename V>
+__device__ __forceinline__ const V* second_of(const V* second, const Lane<P>& ln, int i, int mu) {
+    return (ln.wave & 7) == 0 && Ops<P, R>::az_of(ln, i) == 0 ? second + mu * kWave : nullptr;
 }
 
-// Stage 3: the modes of this wave's segments back to azimuths.
-template <typename P, bool FL>
-__device__ __forceinline__ void from_modes(f32x4 (&s)[P::SEG], const Fourier<P, FL>& fr,
-                                           const Lane<P>& ln, const float* __restrict__ lds) {
-    const float* at = lds + ln.l4 * kPlane + ln.cell * 16 + (ln.kk & 3);
-    const int g = (ln.kk >> 2) ^ swz(ln.l4, ln.cell);        // mode 4 s + l4: granule g ^ s
+// Stage 3: the modes of this wave's segments back to azimuths, rounded to FP32.
+template <typename P, typename R, bool FL>
+__device__ __forceinline__ void from_modes(f32x4 (&x)[P::SEG], const Fourier<P, R, FL>& fr,
+                                           const Lane<P>& ln, const R* __restrict__ lds) {
+    const R* at = lds + ln.cell * 16 + Modes<R>::at(Modes<R>::row(ln.kk), ln.cell);
+    V4<R> s[P::SEG];
 #pragma unroll
     for (int i = 0; i < P::SEG; ++i) {
         const int cls = P::az(i) * P::MU + ln.mu0 + i / P::AZ;
-        f32x4 y;
+        V4<R> y;
 #pragma unroll
-        for (int st = 0; st < 4; ++st) y[st] = at[cls * kClass + st * 4 * kPlane + ((g ^ st) << 2)];
-        s[i] = mfma4(fr.at(1, P::az(i)), y, f32x4{0, 0, 0, 0});
+        for (int st = 0; st < 4; ++st)
+            y[st] = at[cls * kClass<R> + Modes<R>::row(4 * ln.l4 + st) * kPlane<R>];
+        s[i] = mfma4<R>(fr.at(P::az(i)), y, V4<R>{0, 0, 0, 0});
     }
     fold<P>(s);
+#pragma unroll
+    for (int i = 0; i < P::SEG; ++i) x[i] = __builtin_convertvector(s[i], f32x4);
 }
 
 // The tiles of a block: XCD x owns a contiguous range of tiles (cells in Hilbert order) and its
@@ -590,22 +661,39 @@ struct Cell {
     }
 };
 
+// A row with an infinity: the modes mix signs, so that its S comes out as NaN, where a product with
+// a kernel of positive entries is infinite.  S of such a row is the plain sum of the row (NaN if it
+// holds a NaN or both infinities).  x: S in memory order; some of a wave's first values are NaN then.
+template <typename P>
+__device__ __forceinline__ void keep_infinities(f32x4 (&x)[P::SEG], const AzModes<double>& op,
+                                                __amdgpu_buffer_rsrc_t r, uint32_t row, int lane) {
+    if (!op.positive || __builtin_amdgcn_ballot_w64(x[0][0] != x[0][0]) == 0) return;
+    double t = 0.0;
+    for (int q = lane; q < op.np * op.na; q += kWave)
+        t += (double)__builtin_bit_cast(
+            float, __builtin_amdgcn_raw_buffer_load_b32(r, 4u * (uint32_t)q, row, 0));
+    const float sum = (float)wave_sum64(t);
+#pragma unroll
+    for (int i = 0; i < P::SEG; ++i) x[i] = f32x4{sum, sum, sum, sum};
+}
+
 // ------------------------------------------------------------------------------ the product
 
 // S = Psi B (or Lambda B^T with the transposed matrices): [nc][nq] -> [nc][nq].
 template <typename P>
-__global__ __launch_bounds__(P::THREADS, 4) void k_az_product(AzOperand opd,
-                                                              const float* __restrict__ mats,
+__global__ __launch_bounds__(P::THREADS, 4) void k_az_product(AzModes<double> opd,
+                                                              const double* __restrict__ mats,
                                                               const float* __restrict__ in,
                                                               float* __restrict__ out, int64_t nc)
 {
-    __shared__ __attribute__((aligned(16))) float lds[2][P::LDS];
-    __shared__ f32x4 second[P::MU * kWave];
+    using R = double;
+    __shared__ __attribute__((aligned(16))) R lds[P::template LDS<R>];
+    __shared__ V4<R> second[P::MU * kWave];
     __shared__ f32x4 rows[P::WAVES][P::SEG * kWave];
     const Lane<P> ln(opd);
-    const Ops<P> op(mats, ln);
-    const Fourier<P, false> fr(opd, ln, nullptr);
-    load_second<P>(mats, second);
+    const Ops<P, R> op(opd, mats, ln);
+    const Fourier<P, R, false> fr(opd, ln, nullptr);
+    load_second<P, R>(mats, second);
     clear_corner<P>(ln, rows[ln.wave]);
     const uint32_t row_bytes = (uint32_t)(opd.np * opd.na) * 4u;
     const auto rin = make_rsrc(in, (uint32_t)nc * row_bytes);
@@ -620,19 +708,20 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_product(AzOperand opd,
             nx[i] = load_piece<P>(rin, ln, i, (uint32_t)c.c * row_bytes);
     };
     fetch(tl.t);
-    for (int b = 0; tl.t < tl.end; tl.t += tl.stride, b ^= 1) {
+    for (; tl.t < tl.end; tl.t += tl.stride) {
         const Cell c(tl.t, ln.cell, nc);
         f32x4 x[P::SEG];
         to_matrix_order<P>(x, nx, ln, rows[ln.wave]);
         fetch(tl.t + tl.stride);
-        to_modes<P>(x, fr, ln, lds[b]);
+        to_modes(x, fr, ln, lds);
         lds_barrier();
-        on_modes<P>(ln, lds[b], [&](int i, int mu, const f32x4& v) {
-            return apply_pair(op.d[i][mu], second_of<P>(second, ln, i, mu), v, ln.lane);
+        on_modes(op, ln, lds, [&](int i, int mu, const V4<R>& v) {
+            return apply_pair<R>(op.d[i][mu], second_of<P, R>(second, ln, i, mu), v, ln.lane);
         });
         lds_barrier();
-        from_modes<P>(x, fr, ln, lds[b]);
+        from_modes(x, fr, ln, lds);
         to_memory_order<P>(x, ln, rows[ln.wave]);
+        keep_infinities<P>(x, opd, rin, (uint32_t)c.c * row_bytes, ln.lane);
 #pragma unroll
         for (int i = 0; i < P::SEG; ++i)
             if (c.real) store_piece<P>(rout, ln, i, (uint32_t)c.c * row_bytes, x[i]);
@@ -649,19 +738,21 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_product(AzOperand opd,
 // is in the exchange has priority over one that updates, whose vector work fills the gaps
 // (100 352 x 1024: 0.250 -> 0.231 ms; 299 538 x 512: 0.368 -> 0.350).
 template <typename P, int MF, bool RHO, bool DOSE>
-__global__ __launch_bounds__(P::THREADS, 4) void k_az_step(AzOperand opd, StepEpi se, double coeff,
+__global__ __launch_bounds__(P::THREADS, P::STEP_WAVES) void k_az_step(AzModes<double> opd, StepEpi se, double coeff,
                                                            double* __restrict__ dose)
 {
     constexpr int SEG = P::SEG;
-    __shared__ __attribute__((aligned(16))) float lds[2][P::LDS];
-    __shared__ double dsum[2][DOSE && P::WPC == 2 ? kCells : 1];
-    __shared__ f32x4 second[P::MU * kWave];
+    using R = double;
+    __shared__ __attribute__((aligned(16))) R lds[P::template LDS<R>];
+    __shared__ V4<R> ftab[P::FULL ? P::AZ * kWave : 1];
+    __shared__ double dsum[DOSE && P::WPC == 2 ? kCells : 1];
+    __shared__ V4<R> second[P::MU * kWave];
     __shared__ __attribute__((aligned(16))) float dirs[2 * kTable<P>];
     __shared__ f32x4 rows[P::WAVES][SEG * kWave];
     const Lane<P> ln(opd);
-    const Ops<P> op(opd.fwd, ln);
-    const Fourier<P, false> fr(opd, ln, nullptr);
-    load_second<P>(opd.fwd, second);
+    const Ops<P, R> op(opd, opd.fwd, ln);
+    const Fourier<P, R, P::FULL> fr(opd, ln, ftab);
+    load_second<P, R>(opd.fwd, second);
     load_dirs<P>(se.tab, se.nq, dirs);
     clear_corner<P>(ln, rows[ln.wave]);
     const FwdCtx<float> cx = make_ctx(se.a, se.psi_in, se.psi_out, se.nc, se.nq, se.nbf);
@@ -693,29 +784,29 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_step(AzOperand opd, StepEp
             up[i][f] = load_face<P>(CellWords::word(rec, f), cell_of(tl.t).c, ln, i, cx);
     float recn = record(tl.t + tl.stride);
     __syncthreads();                       // second, dirs
-    for (int b = 0;; b ^= 1) {
+    for (;;) {
         const Cell c = cell_of(tl.t), cn = cell_of(tl.t + tl.stride);
-        float* buf = lds[b];
         f32x4 x[SEG];
         __builtin_amdgcn_s_setprio(2);
         to_matrix_order<P>(x, p, ln, rows[ln.wave]);
-        to_modes<P>(x, fr, ln, buf);
+        to_modes(x, fr, ln, lds);
         const float matn = words.template material<MF>(recn, cn.c, ln.lane);
         own(pn, tl.t + tl.stride);
         const float recn2 = record(tl.t + 2 * tl.stride);
         lds_barrier();
-        on_modes<P>(ln, buf, [&](int i, int mu, const f32x4& v) {
-            return apply_pair(op.d[i][mu], second_of<P>(second, ln, i, mu), v, ln.lane);
+        on_modes(op, ln, lds, [&](int i, int mu, const V4<R>& v) {
+            return apply_pair<R>(op.d[i][mu], second_of<P, R>(second, ln, i, mu), v, ln.lane);
         });
         double sd = 0.0;
         if constexpr (DOSE) {
             sd = weighted<P>(p, P::RV ? wtab : wd, ln);
             sd = wave_sum64(sd);
-            if (P::WPC == 2 && ln.mu0 == 1 && ln.lane == 0) dsum[b][ln.cell] = sd;
+            if (P::WPC == 2 && ln.mu0 == 1 && ln.lane == 0) dsum[ln.cell] = sd;
         }
         lds_barrier();
-        from_modes<P>(x, fr, ln, buf);
+        from_modes(x, fr, ln, lds);
         to_memory_order<P>(x, ln, rows[ln.wave]);
+        keep_infinities<P>(x, opd, cx.psi, (uint32_t)c.c * cx.row_bytes, ln.lane);
         __builtin_amdgcn_s_setprio(0);
         CellData<MF> cd;
         cd.template form<RHO>(rec, mat, se.a, cx);
@@ -723,7 +814,7 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_step(AzOperand opd, StepEp
             const uint64_t d0 = ((uint64_t)(uint32_t)CellWords::word(mat, 9) << 32) |
                                 (uint32_t)CellWords::word(mat, 8);
             if (ln.mu0 == 0 && ln.lane == 0 && c.real) {
-                if (P::WPC == 2) sd += dsum[b][ln.cell];
+                if (P::WPC == 2) sd += dsum[ln.cell];
                 dose[c.c] = __builtin_bit_cast(double, d0) +
                             coeff * (RHO ? (double)cd.irho : 1.0) * sd;
             }
@@ -831,22 +922,23 @@ struct AdjWords {
 };
 
 template <typename P, int MF, typename GT, bool DA>
-__global__ __launch_bounds__(P::THREADS, 4) void k_az_adjoint(AzOperand opd, AzAdjoint e,
+__global__ __launch_bounds__(P::THREADS, 4) void k_az_adjoint(AzModes<double> opd, AzAdjoint e,
                                                               GT* __restrict__ g_t,
                                                               GT* __restrict__ g_s,
                                                               GT* __restrict__ g_r)
 {
     constexpr int SEG = P::SEG;
-    __shared__ __attribute__((aligned(16))) float lds[2][P::LDS];
-    __shared__ f32x4 second[P::MU * kWave];
+    using R = double;
+    __shared__ __attribute__((aligned(16))) R lds[P::template LDS<R>];
+    __shared__ V4<R> second[P::MU * kWave];
     __shared__ __attribute__((aligned(16))) float dirs[2 * kTable<P>];
     __shared__ f32x4 rows[P::WAVES][SEG * kWave];
-    __shared__ float gsum[2][P::WPC == 2 ? P::WAVES : 1][4];
+    __shared__ float gsum[P::WPC == 2 ? P::WAVES : 1][4];
     const Lane<P> ln(opd);
-    __shared__ f32x4 ftab[2 * P::AZ * kWave];
-    const Ops<P> op(opd.adj, ln);
-    const Fourier<P, true> fr(opd, ln, ftab);
-    load_second<P>(opd.adj, second);
+    __shared__ V4<R> ftab[P::AZ * kWave];
+    const Ops<P, R> op(opd, opd.adj, ln);
+    const Fourier<P, R, true> fr(opd, ln, ftab);
+    load_second<P, R>(opd.adj, second);
     load_dirs<P>(e.tab, e.nq, dirs);
     clear_corner<P>(ln, rows[ln.wave]);
     const StepArgs32& a = e.a;
@@ -888,9 +980,9 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_adjoint(AzOperand opd, AzA
         if (g_s) g_s[c] = AdjWords<GT>::gradient(mat, 1) + (GT)(a.dt * a.alpha_s * ps);
         if (g_r) g_r[c] = AdjWords<GT>::gradient(mat, 2) + (GT)(a.dt * irho * irho * pr);
     };
-    auto shared_gradients = [&](float mat, const Cell& c, int b) {
+    auto shared_gradients = [&](float mat, const Cell& c) {
         if (ln.mu0 == 0 && c.real) {
-            const float *u = gsum[b][ln.cell], *v = gsum[b][P::WPC == 2 ? ln.cell + 8 : 0];
+            const float *u = gsum[ln.cell], *v = gsum[P::WPC == 2 ? ln.cell + 8 : 0];
             const float irho = a.inv_rho ? CellWords::value(mat, 2) : 1.0f;
             const float pt = u[0] + v[0], ps = u[1] + v[1], pr = u[2] + v[2];
             if (ln.lane == 0) add_gradients(mat, c.c, pt, ps, pr, irho);
@@ -904,25 +996,24 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_adjoint(AzOperand opd, AzA
     Cell cp = cell_of(tl.t);
     bool first = true;
     __syncthreads();                       // second, dirs
-    int b = 0;
-    for (;; b ^= 1) {
+    for (;;) {
         const Cell c = cell_of(tl.t), cn = cell_of(tl.t + tl.stride);
-        float* buf = lds[b];
         f32x4 x[SEG];
         __builtin_amdgcn_s_setprio(2);
         to_matrix_order<P>(x, l, ln, rows[ln.wave]);
-        to_modes<P>(x, fr, ln, buf);
+        to_modes(x, fr, ln, lds);
         const float matn = words.template load<MF>(recn, cn.c, ln.lane);
         own(lnx, tl.t + tl.stride);
         const float recn2 = record(tl.t + 2 * tl.stride);
         lds_barrier();
-        if (P::WPC == 2 && !first) shared_gradients(matp, cp, b ^ 1);
-        on_modes<P>(ln, buf, [&](int i, int mu, const f32x4& v) {
-            return apply_pair(op.d[i][mu], second_of<P>(second, ln, i, mu), v, ln.lane);
+        if (P::WPC == 2 && !first) shared_gradients(matp, cp);
+        on_modes(op, ln, lds, [&](int i, int mu, const V4<R>& v) {
+            return apply_pair<R>(op.d[i][mu], second_of<P, R>(second, ln, i, mu), v, ln.lane);
         });
         lds_barrier();
-        from_modes<P>(x, fr, ln, buf);
+        from_modes(x, fr, ln, lds);
         to_memory_order<P>(x, ln, rows[ln.wave]);
+        keep_infinities<P>(x, opd, rlam, (uint32_t)c.c * row_bytes, ln.lane);
         __builtin_amdgcn_s_setprio(0);
         using W = CellWords;
         const float ia = W::value(rec, 12), irho = a.inv_rho ? W::value(mat, 2) : 1.0f;
@@ -987,9 +1078,9 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_adjoint(AzOperand opd, AzA
         pr = wave_sum_dpp(pr);
         if constexpr (P::WPC == 2) {
             if (ln.lane == 0) {
-                gsum[b][ln.wave][0] = pt;
-                gsum[b][ln.wave][1] = ps;
-                gsum[b][ln.wave][2] = pr;
+                gsum[ln.wave][0] = pt;
+                gsum[ln.wave][1] = ps;
+                gsum[ln.wave][2] = pr;
             }
         } else if (ln.lane == 0 && c.real) {
             add_gradients(mat, c.c, pt, ps, pr, irho);
@@ -1007,46 +1098,58 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_adjoint(AzOperand opd, AzA
     }
     if constexpr (P::WPC == 2) {
         lds_barrier();
-        shared_gradients(matp, cp, b);
+        shared_gradients(matp, cp);
     }
 }
 
 // ----------------------------------------------------------------------------- the IMEX step
+
+// b / (a - b lam); in FP64 from the hardware's estimate of the reciprocal and a Newton step (2e-15
+// measured).
+__device__ __forceinline__ float ratio(float b, float a, float lam) { return b / (a - b * lam); }
+__device__ __forceinline__ double ratio(double b, double a, double lam) {
+    const double d = __builtin_fma(-b, lam, a), r = __builtin_amdgcn_rcp(d);
+    return b * __builtin_fma(__builtin_fma(-d, r, 1.0), r, r);
+}
 
 // The IMEX step with a dense kernel or its moment projection (Sec. 4.2) in one pass: per cell
 // (a I - b A) psi' = r with a = 1 + dt alpha_t sigma_t, b = dt alpha_s sigma_s, A = K W.  The modes
 // decouple, D_m = V diag(lam) V^-1 per mode, so psi' = (r + V D V^-1 r) / a with
 // D = diag(b lam / (a - b lam)).  r is the collision-free step, formed from the wave's rows and
 // kept in registers; in stage 2 the two polar products follow each other without LDS (an MFMA's
-// result rows 4 l4 + s are the next one's K order), the per-cell diagonal between them.  The next
-// tile's rows are fetched as soon as r is formed and fly during the exchange.  100 352 x 1024:
-// 0.304 ms, against 1.47 ms with two nq x nq products (BF16x3) and 0.52 ms with two products
-// through 96 padded moments, each after a collision-free step of its own.
-template <typename P, int MF, bool RHO>
-__global__ __launch_bounds__(P::THREADS, 4) void k_az_imex(AzOperand opd, StepEpi se)
+// result rows are the next one's K order), the per-cell diagonal between them.  The next
+// tile's rows are fetched as soon as r is formed and fly during the exchange.  R: FP64 for FP32
+// handles, FP32 for the 16-bit ones.  Element-wise errors of a stiff step (g = 0.95, 512 ordinates,
+// one of them lit): FP64 modes 1.1e-6 (the step's FP32 roundings), the general solve of an FP32
+// handle 2.1e-4, FP32 modes 3.3e-4, the general solve of a BF16x3 handle 9.7e-3.  100 352 x 1024:
+// 0.321 ms in FP32 and 0.49 in FP64, against 1.43 ms with two nq x nq products (BF16x3) and 0.53 ms
+// with two products through 96 padded moments, each after a collision-free step of its own.
+template <typename P, typename R, int MF, bool RHO>
+__global__ __launch_bounds__(P::THREADS, 4) void k_az_imex(AzModes<R> opd, StepEpi se)
 {
     constexpr int SEG = P::SEG;
-    __shared__ __attribute__((aligned(16))) float lds[2][P::LDS];
-    __shared__ f32x4 second[2][P::MU * kWave];
+    __shared__ __attribute__((aligned(16))) R lds[P::template LDS<R>];
+    __shared__ V4<R> second[2][P::MU * kWave];
     __shared__ __attribute__((aligned(16))) float dirs[2 * kTable<P>];
     __shared__ f32x4 rows[P::WAVES][SEG * kWave];
     const Lane<P> ln(opd);
-    __shared__ f32x4 ftab[2 * P::AZ * kWave];
-    const Ops<P> op(opd.e1, ln);
-    const Fourier<P, true> fr(opd, ln, ftab);
-    f32x4 e2[P::ITEMS][P::MU], lam[P::ITEMS][P::MU];
-    Ops<P>::load(e2, opd.e2, ln);
+    __shared__ V4<R> ftab[P::AZ * kWave];
+    const Ops<P, R> op(opd, opd.e1, ln);
+    const Fourier<P, R, true> fr(opd, ln, ftab);
+    V4<R> e2[P::ITEMS][P::MU];
+    Ops<P, R>::load(e2, opd.e2, ln);
+    __shared__ V4<R> lam[P::AZ * P::MU * 8 * 2 * 4];
+    const V4<R>* lam_at[P::ITEMS];
+    for (int i = threadIdx.x; i < P::AZ * P::MU * 8 * 2 * 4; i += P::THREADS)
+        lam[i] = reinterpret_cast<const V4<R>*>(opd.lam)[i];
 #pragma unroll
-    for (int i = 0; i < P::ITEMS; ++i)
-#pragma unroll
-        for (int mu = 0; mu < P::MU; ++mu) {
-            const int az = Ops<P>::az_of(ln, i), pair = ln.wave & 7;
-            const int which = pair == 0 && az == 0 ? (ln.lane >> 3) & 1 : 0;
-            lam[i][mu] = reinterpret_cast<const f32x4*>(
-                opd.lam)[(((mu * P::AZ + az) * 8 + pair) * 2 + which) * 4 + ln.l4];
-        }
-    load_second<P>(opd.e1, second[0]);
-    load_second<P>(opd.e2, second[1]);
+    for (int i = 0; i < P::ITEMS; ++i) {
+        const int az = Ops<P, R>::az_of(ln, i), pair = ln.wave & 7;
+        const int which = pair == 0 && az == 0 ? (ln.lane >> 3) & 1 : 0;
+        lam_at[i] = lam + ((az * 8 + pair) * 2 + which) * 4 + ln.l4;
+    }
+    load_second<P, R>(opd.e1, second[0]);
+    load_second<P, R>(opd.e2, second[1]);
     load_dirs<P>(se.tab, se.nq, dirs);
     clear_corner<P>(ln, rows[ln.wave]);
     const StepArgs32& a = se.a;
@@ -1076,9 +1179,8 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_imex(AzOperand opd, StepEp
     fetch(rec, cell_of(tl.t).c);
     float recn = record(tl.t + tl.stride);
     __syncthreads();                       // second, dirs
-    for (int b = 0;; b ^= 1) {
+    for (;;) {
         const Cell c = cell_of(tl.t), cn = cell_of(tl.t + tl.stride);
-        float* buf = lds[b];
         CellData<MF> cd;
         cd.template form<RHO>(rec, mat, a, cx);
         f32x4 r[SEG], x[SEG];
@@ -1106,17 +1208,18 @@ __global__ __launch_bounds__(P::THREADS, 4) void k_az_imex(AzOperand opd, StepEp
         const float recn2 = record(tl.t + 2 * tl.stride);
         __builtin_amdgcn_s_setprio(2);
         to_matrix_order<P>(x, r, ln, rows[ln.wave]);
-        to_modes<P>(x, fr, ln, buf);
+        to_modes(x, fr, ln, lds);
         lds_barrier();
-        const float ca = 1.0f + a.dt * a.alpha_t * st, cb = a.dt * a.alpha_s * ss;
-        on_modes<P>(ln, buf, [&](int i, int mu, const f32x4& v) {
-            f32x4 z = apply_pair(op.d[i][mu], second_of<P>(second[0], ln, i, mu), v, ln.lane);
+        const R ca = R(1) + (R)a.dt * a.alpha_t * st, cb = (R)a.dt * a.alpha_s * ss;
+        on_modes(op, ln, lds, [&](int i, int mu, const V4<R>& v) {
+            V4<R> z = apply_pair<R>(op.d[i][mu], second_of<P, R>(second[0], ln, i, mu), v, ln.lane);
+            const V4<R> l = lam_at[i][mu * P::AZ * 8 * 2 * 4];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) z[k] *= cb / (ca - cb * lam[i][mu][k]);
-            return apply_pair(e2[i][mu], second_of<P>(second[1], ln, i, mu), z, ln.lane);
+            for (int k = 0; k < 4; ++k) z[k] *= ratio(cb, ca, l[k]);
+            return apply_pair<R>(e2[i][mu], second_of<P, R>(second[1], ln, i, mu), z, ln.lane);
         });
         lds_barrier();
-        from_modes<P>(x, fr, ln, buf);
+        from_modes(x, fr, ln, lds);
         to_memory_order<P>(x, ln, rows[ln.wave]);
         __builtin_amdgcn_s_setprio(0);
         const float y = cd.cabs / (1.0f + cd.cabs);
@@ -1157,8 +1260,8 @@ int az_resident(K kernel, int threads) {
 }
 
 // f(shape) for the class shape of an operand.
-template <typename F>
-hipError_t by_shape(const AzOperand& op, F&& f) {
+template <typename R, typename F>
+hipError_t by_shape(const AzModes<R>& op, F&& f) {
     const bool two = op.na > 16, fold = op.np > 16;
     if (op.na == (two ? 32 : 16)) {
         if (two) return fold ? f(Shape<2, 2>{}) : f(Shape<2, 1>{});

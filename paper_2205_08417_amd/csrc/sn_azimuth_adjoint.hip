@@ -5,7 +5,7 @@ namespace snrt {
 namespace {
 
 template <typename GT, bool DA>
-hipError_t launch(const snrt_mesh& m, const snrt_quad& q, const AzOperand& op, const StepArgs32& a,
+hipError_t launch(const snrt_mesh& m, const snrt_quad& q, const AzModes<double>& op, const StepArgs32& a,
                   const float* psi_n, const float* lam_np1, float* lam_n, GT* g_t, GT* g_s,
                   GT* g_r, const DoseAdj& da, hipStream_t st) {
     if (m.nc == 0) return hipSuccess;
@@ -25,7 +25,7 @@ hipError_t launch(const snrt_mesh& m, const snrt_quad& q, const AzOperand& op, c
 
 }  // namespace
 
-hipError_t launch_az_adjoint(const snrt_mesh& m, const snrt_quad& q, const AzOperand& op,
+hipError_t launch_az_adjoint(const snrt_mesh& m, const snrt_quad& q, const AzModes<double>& op,
                              const StepArgs32& a, const float* psi_n, const float* lam_np1,
                              float* lam_n, float* g_t, float* g_s, float* g_r, const DoseAdj& da,
                              hipStream_t st) {
@@ -33,7 +33,7 @@ hipError_t launch_az_adjoint(const snrt_mesh& m, const snrt_quad& q, const AzOpe
     return launch<float, false>(m, q, op, a, psi_n, lam_np1, lam_n, g_t, g_s, g_r, da, st);
 }
 
-hipError_t launch_az_adjoint(const snrt_mesh& m, const snrt_quad& q, const AzOperand& op,
+hipError_t launch_az_adjoint(const snrt_mesh& m, const snrt_quad& q, const AzModes<double>& op,
                              const StepArgs32& a, const float* psi_n, const float* lam_np1,
                              float* lam_n, double* g_t, double* g_s, double* g_r,
                              const DoseAdj& da, hipStream_t st) {

@@ -3,7 +3,7 @@
 
 namespace snrt {
 
-hipError_t launch_az_product(const snrt_mesh& m, const AzOperand& op, const float* mats,
+hipError_t launch_az_product(const snrt_mesh& m, const AzModes<double>& op, const double* mats,
                              const float* in, float* out, hipStream_t st) {
     if (m.nc == 0) return hipSuccess;
     return az::by_shape(op, [&](auto shape) {
@@ -15,7 +15,7 @@ hipError_t launch_az_product(const snrt_mesh& m, const AzOperand& op, const floa
     });
 }
 
-hipError_t launch_az_step(const snrt_mesh& m, const AzOperand& op, const StepEpi& se, double coeff,
+hipError_t launch_az_step(const snrt_mesh& m, const AzModes<double>& op, const StepEpi& se, double coeff,
                           double* dose, hipStream_t st) {
     if (m.nc == 0) return hipSuccess;
     return az::by_shape(op, [&](auto shape) {

@@ -491,8 +491,7 @@ void snrt_scatter_destroy(snrt_scatter* sc) {
     dev_free(sc->B.msig64);
     dev_free(sc->B.lam32);
     dev_free(sc->B.lam64);
-    dev_free(sc->B.az.base);
-    dev_free(sc->B.az.imp_base);
+    for (void* p : sc->B.az_mem) dev_free(p);
     delete sc;
 }
 
@@ -912,24 +911,56 @@ int32_t* ws_rexp(const DenseB& B, float* after_S, int64_t M) {
     return reinterpret_cast<int32_t*>(after_S + (B.chain == 2 ? (size_t)M * B.mid : 0));
 }
 
-// Whether the FP32 state's scattering product runs through the azimuthal modes, where the handle
-// has them.  Their kernels work on 16 or 32 azimuthal times 16 or 32 polar slots, padded, so the
-// line is how much of the slots the ordinates fill.  us per step, modes against general products:
-//   3 042 cells (short launches decide): every shape and precision measured, from 4 x 5 (8.0 :
-//     11.0 FP32) over 4 x 32 (8.2 : 24.7 FP32, 12.1 BF16x1) to 32 x 32 (13.7 : 258 FP32, 54 BF16x1);
-//   51 842 cells, FP32: 4 x 5 (8 % filled) 28.1 : 23.7, 6 x 8 (19 %) 28.4 : 32.3 but its product
-//     alone 18.6 : 15.4, 5 x 20 (20 %) 44.6 : 67.1, 8 x 8 (25 %) 28.8 : 35.8, 10 x 10 30.2 : 66.8;
-//     a width the matrix-core FP32 product takes, 4 x 32 (25 %) 49.3 : 44.5;
-//   51 842 cells, BF16x3: 8 x 20 (31 %) 50.4 : 44.2, 6 x 32 (38 %) 50.6 : 51.4, 8 x 32 (50 %) 53.3 :
-//     48.5, 8 x 16 (50 %) 33.0 : 33.9, 16 x 20 (63 %) 60.6 : 111.6, 12 x 16 (75 %) 34.1 : 94.8
-//     (BF16x1: 16 x 20 83.5, 12 x 16 83.9, 16 x 16 34.4 : 37.4).
+// Whether the FP32 state's scattering product and steps run through the azimuthal modes, where the
+// handle has them.  Their kernels work on 16 or 32 azimuthal times 16 or 32 polar slots, padded, and
+// cost the slots; the general products cost nq^2 (FP32) or a part of that under the rows' traffic
+// (16-bit), with 128 columns at least, and more launches.  So the lines are nq^2 / slots, or the share
+// of the slots that is filled.  us per step, modes : general product, dense kernels (moment forms
+// have the same lines; transposed steps lie within 10 % of them):
+//   3 042 cells, every shape and precision measured: 4 x 5 FP32 7.2 : 9.5, 4 x 8 BF16x1 6.9 : 9.7,
+//     4 x 32 BF16x1 8.6 : 11.0, 20 x 24 16.3 : 28.0
+//   FP32          7 938 cells         16 200              29 768              51 842
+//     6 x 8  ( 9)  9.3 : 13.5       14.0 : 15.6       23.1 : 20.5       34.5 : 29.6
+//     8 x 8  (16)  9.3 : 15.2       14.1 : 17.6       23.2 : 23.2       34.7 : 32.0
+//     5 x 20 (20) 13.6 : 23.5       22.6 : 29.8       37.4 : 42.4       60.4 : 61.7  (198 450: 215 : 190)
+//     8 x 10 (25)  9.6 : 18.9       14.5 : 23.1       23.8 : 34.0       36.1 : 48.3
+//     4 x 32 (32) 13.8 : 25.6       23.9 : 28.3       39.1 : 33.1       65.1 : 42.4  (nq a multiple of
+//     8 x 16 (64)  9.7 : 25.8       15.7 : 28.3       24.3 : 33.2       38.2 : 42.0   128: matrix cores)
+//   BF16x3
+//     8 x 8  (25 %)  9.3 : 12.1     14.0 : 13.9       23.1 : 16.6       34.5 : 20.6
+//     8 x 20 (31 %) 15.2 : 24.9     24.5 : 28.3       39.0 : 33.7       64.5 : 41.5  (FP16x3 56.3)
+//     20 x 24 (47 %) 27.4 : 48.1    48.6 : 57.5       85.5 : 79.3        145 : 137   (FP16x3 166)
+//     10 x 16 (63 %)  9.8 : 24.8    15.6 : 28.2       24.6 : 33.4       39.3 : 42.2
+//   BF16x1 (BF16x2 between)
+//     8 x 20 (31 %) 15.1 : 18.8     24.6 : 22.0       39.1 : 27.7       64.6 : 35.6
+//     8 x 16 (50 %)  9.7 : 12.5     15.6 : 15.4       24.4 : 20.0       38.3 : 29.0
+//     10 x 16 (63 %) 9.8 : 18.8     15.9 : 21.9       24.7 : 27.6       39.2 : 35.5
+//     12 x 16 (75 %) 9.8 : 20.1     15.8 : 23.7       25.5 : 29.4       40.8 : 40.7  (198 450: 133 : 143)
+//     16 x 16       10.0 : 31.8     16.2 : 31.8       26.2 : 33.0       42.1 : 35.7  (one launch)
 bool azimuth_product(const snrt_mesh& m, const DenseB& B) {
     if (B.az.na == 0 || (size_t)m.nc * B.nq * sizeof(float) >= (size_t(1) << 32)) return false;
-    if (m.nc <= 16384) return true;
+    if (m.nc <= 4096) return true;
+    const int size = m.nc <= 8192 ? 0 : m.nc <= 16384 ? 1 : m.nc <= 32768 ? 2 : 3;
+    const int32_t nq = B.nq, slots = (B.az.na > 16 ? 32 : 16) * (B.az.np > 16 ? 32 : 16);
+    if (B.precision == SNRT_FP32) {
+        static constexpr int line[4] = {8, 18, 18, 24};
+        return nq * nq >= slots * (nq % 128 == 0 && size >= 2 ? 48 : line[size]);
+    }
+    const bool few = B.precision == SNRT_BF16X1 || B.precision == SNRT_BF16X2;
+    static constexpr int share[3][4] = {{25, 31, 51, 51}, {25, 31, 45, 45}, {31, 50, 61, 71}};
+    if (few && size == 3 && nq == 256 && slots == 256) return false;
+    return 100 * nq >= slots * share[few ? 2 : B.precision == SNRT_FP16X3 ? 1 : 0][size];
+}
+
+// The same for the IMEX step, which replaces two products and a collision-free step; only FP32
+// handles (whose modes are FP64) with sparsely filled slots on large meshes are better off without:
+// 198 450 cells 4 x 8 181 : 168 us, 6 x 8 182 : 212; 4 x 32 at 51 842 cells 98.9 : 94.8, at 29 768 59 :
+// 87; the moment form with 5 x 20 at 100 352 cells 155 : 144 (as a dense kernel 155 : 220).
+bool azimuth_imex(const snrt_mesh& m, const DenseB& B) {
+    if (!B.az.e1) return B.az32.e1 != nullptr;
     const int32_t slots = (B.az.na > 16 ? 32 : 16) * (B.az.np > 16 ? 32 : 16);
-    if (B.precision == SNRT_FP32)
-        return 5 * B.nq >= slots && (B.nq % 128 != 0 || 4 * B.nq > slots);
-    return 2 * B.nq > slots;
+    if (m.nc > 32768 && B.nq % 128 == 0 && 4 * B.nq <= slots) return false;
+    return m.nc <= 65536 || (B.chain == 2 ? 5 : 8) * B.nq > slots;
 }
 
 // S = Psi B (forward) or G = Lambda B^T (adjoint) into the workspace, FP32 state
@@ -1416,8 +1447,10 @@ hipError_t imex_modes(const snrt_mesh* m, const snrt_quad* q, const DenseB& B,
         StepArgs32 free_flight = a32;
         free_flight.alpha_t = 0.0f;
         free_flight.alpha_s = 0.0f;
-        if (B.az.e1)   // the whole step in one launch through the azimuthal modes
-            return launch_az_imex(*m, B.az, step_epi(*m, *q, a32, psi_in, psi_out), st);
+        if (azimuth_imex(*m, B)) {   // the whole step in one launch through the azimuthal modes
+            const StepEpi se = step_epi(*m, *q, a32, psi_in, psi_out);
+            return B.az.e1 ? launch_az_imex(*m, B.az, se, st) : launch_az_imex(*m, B.az32, se, st);
+        }
         e = launch_free_step32(*m, *q, free_flight, psi_in, psi_out, st);
         // the per-cell diagonal and the final combine ride on the two products' epilogues
         // where the matrix-core kernels run them (S then stays unused), else separate passes

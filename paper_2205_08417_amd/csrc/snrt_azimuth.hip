@@ -2,6 +2,7 @@
 // an operator on a product rule and packs the transforms and polar matrices in lane order.
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <vector>
 
 #include "snrt_internal.h"
@@ -16,6 +17,13 @@ constexpr double kPi = 3.14159265358979323846;
 // its polar pair: far above the FP64 rounding of a kernel evaluated from Omega_q . Omega_p, far
 // below the FP32 rounding of the operands.
 constexpr double kInvariant = 1e-11;
+
+// The modes' error is that of FP64 relative to the operator's norm (largest row or column sum), and
+// has to stay below FP32 rounding in every element of S, which for psi >= 0 is at least the smallest
+// entry times the sum of psi: entries below this share of the norm, zeros above all (a kernel that
+// ends at an angle), leave the operator with the general products, whose error is relative to the
+// element.  A Henyey-Greenstein kernel's are above 1e-6 up to g = 0.95 on 32 x 32 ordinates.
+constexpr double kSmallest = 0x1p-25;
 
 // Product-rule shape: na consecutive ordinates share each polar node, with one weight.  The
 // kernels take up to 16 azimuths or an even count up to 32 (folded), and up to 16 polar nodes or an
@@ -38,31 +46,50 @@ bool product_shape(const snrt_quad& q, int& np, int& na) {
 
 int classes(int na) { return na > 16 ? 2 : 1; }
 
-// Frequency and phase of mode slot m (0..15) of azimuthal class c (two classes: the even and the
-// odd frequencies): pairs (2j, 2j + 1) are the cosine and sine of one frequency, except modes 0
-// and na / 2 of class 0, which share its first pair.  f < 0: no mode in the slot.
-struct Mode {
-    int f;
-    bool sine;
-};
-Mode mode_of(int na, int c, int m) {
-    const int j = m / 2, s = m & 1, AZ = classes(na);
-    const int f = AZ == 1 ? j : 2 * j + c;
-    if (f == 0) {
-        if (!s) return {0, false};
-        return {na % 2 == 0 && (AZ == 1 || na / 2 % 2 == 0) ? na / 2 : -1, false};
-    }
-    if (2 * f < na) return {f, s == 1};
-    // the odd class holds na / 2 where that is odd, as an ordinary pair without a sine
-    return {2 * f == na && AZ == 2 && c == 1 && !s ? f : -1, false};
+// The modes of azimuthal class c are those of half = na / classes azimuths, m = 0 .. half - 1, in a
+// symmetric real basis: class 0 (the sums x_l + x_{l+half}, or the azimuths themselves) has
+// cas(2 pi l m / half), cas = cos + sin, of frequency m; class 1 (the differences) has
+// cas(pi (2 l + 1)(2 m + 1) / (2 half)) of frequency m + 1/2, both in periods per half azimuths.
+// Two modes of one frequency (m and half - m, or half - 1 - m) share a polar matrix.
+int frequency(int na, int c, int m) { return classes(na) == 1 ? m : 2 * m + c; }   // per na azimuths
+double basis(int na, int c, int l, int m) {
+    const int half = na / classes(na);
+    if (l >= half || m >= half) return 0.0;
+    const double x = c == 0 ? 2.0 * kPi * (double)((l * m) % half) / half
+                            : kPi * (double)(((2 * l + 1) * (2 * m + 1)) % (4 * half)) / (2.0 * half);
+    return (std::cos(x) + std::sin(x)) / std::sqrt((double)na);
 }
 
-// Element l of the orthonormal real Fourier basis over na azimuths.
-double basis(int na, const Mode& md, int l) {
-    if (md.f < 0) return 0.0;
-    const double x = 2.0 * kPi * (double)((md.f * l) % na) / na;
-    if (md.f == 0 || 2 * md.f == na) return std::cos(x) / std::sqrt((double)na);
-    return std::sqrt(2.0 / na) * (md.sine ? std::sin(x) : std::cos(x));
+// The accumulator row at a place, as the kernels' Modes<R>::row(); mode m lies in slot row(m).
+template <typename R>
+int row(int place) { return sizeof(R) == 8 ? 4 * (place & 3) + (place >> 2) : place; }
+
+// The eight pairs of modes of class c that a wave takes together (modes from half on are empty
+// slots).  Pair 0 of class 0: mode 0 and, where half is even, half / 2, each alone in its frequency.
+std::vector<int> mode_pairs(int na, int c) {
+    const int half = na / classes(na);
+    std::vector<int> p, empty;
+    for (int m = 15; m >= half; --m) empty.push_back(m);
+    auto add = [&](int m, int partner) {
+        if (partner < 0) {
+            partner = empty.back();
+            empty.pop_back();
+        }
+        p.push_back(m);
+        p.push_back(partner);
+    };
+    if (c == 0) add(0, half % 2 == 0 ? half / 2 : -1);
+    for (int m = c == 0 ? 1 : 0; m < half; ++m) {
+        const int other = c == 0 ? half - m : half - 1 - m;
+        if (m < other) add(m, other);
+        else if (m == other && c == 1) add(m, -1);
+    }
+    while (!empty.empty()) {
+        const int m = empty.back();
+        empty.pop_back();
+        add(m, -1);
+    }
+    return p;
 }
 
 // The polar matrices M[class][pair][which] (h x h in a 16 x 16 frame, row-major) of the
@@ -71,75 +98,113 @@ std::vector<double> polar_matrices(const std::vector<double>& a, int np, int na,
     const int AZ = classes(na), MU = np > 16 ? 2 : 1, NC = AZ * MU, h = np / MU;
     std::vector<double> M((size_t)NC * 16 * 256, 0.0);
     std::vector<double> c(na);
-    for (int f = 0; f <= na / 2; ++f) {
-        for (int d = 0; d < na; ++d) c[d] = std::cos(2.0 * kPi * (double)((f * d) % na) / na);
-        auto hat = [&](int k, int k2) {
-            double s = 0.0;
-            for (int d = 0; d < na; ++d) s += c[d] * a[((size_t)k * np + k2) * na + d];
-            return s;
-        };
-        for (int cls = 0; cls < NC; ++cls)
-            for (int j = 0; j < 8; ++j)
-                for (int s = 0; s < 2; ++s) {
-                    if (mode_of(na, cls % AZ, 2 * j + s).f != f) continue;
-                    double* D = &M[((size_t)(cls * 8 + j) * 2 + s) * 256];
-                    for (int i = 0; i < h; ++i)
-                        for (int i2 = 0; i2 < h; ++i2) {
-                            double v = hat(i, i2);
-                            if (MU == 2) {
-                                const double w = hat(i, np - 1 - i2);
-                                v = cls < AZ ? v + w : v - w;
-                                if (half) v *= 0.5;
-                            }
-                            D[i * 16 + i2] = v;
+    for (int az = 0; az < AZ; ++az) {
+        const std::vector<int> pairs = mode_pairs(na, az);
+        for (int js = 0; js < 16; ++js) {
+            if (pairs[js] >= na / AZ) continue;
+            const int f = frequency(na, az, pairs[js]);
+            for (int d = 0; d < na; ++d) c[d] = std::cos(2.0 * kPi * (double)((f * d) % na) / na);
+            auto hat = [&](int k, int k2) {
+                double s = 0.0;
+                for (int d = 0; d < na; ++d) s += c[d] * a[((size_t)k * np + k2) * na + d];
+                return s;
+            };
+            for (int mu = 0; mu < MU; ++mu) {
+                double* D = &M[((size_t)(mu * AZ + az) * 16 + js) * 256];
+                for (int i = 0; i < h; ++i)
+                    for (int i2 = 0; i2 < h; ++i2) {
+                        double v = hat(i, i2);
+                        if (MU == 2) {
+                            const double w = hat(i, np - 1 - i2);
+                            v = mu == 0 ? v + w : v - w;
+                            if (half) v *= 0.5;
                         }
-                }
+                        D[i * 16 + i2] = v;
+                    }
+            }
+        }
     }
     return M;
 }
 
 // M [n][16][16] in the A-operand order of the kernels: lane (row = lane & 15), step s takes
-// column 4 (lane >> 4) + s.
-void pack(const double* M, size_t n, bool transpose, float* out) {
+// column row(4 (lane >> 4) + s).
+template <typename R>
+void pack(const double* M, size_t n, bool transpose, std::vector<R>& out) {
     for (size_t b = 0; b < n; ++b)
         for (int lane = 0; lane < 64; ++lane)
             for (int s = 0; s < 4; ++s) {
-                const int r = lane & 15, c = 4 * (lane >> 4) + s;
-                out[(b * 64 + lane) * 4 + s] =
-                    (float)M[b * 256 + (transpose ? c * 16 + r : r * 16 + c)];
+                const int r = lane & 15, c = row<R>(4 * (lane >> 4) + s);
+                out.push_back((R)M[b * 256 + (transpose ? c * 16 + r : r * 16 + c)]);
             }
 }
 
-snrt_status upload_operand(DenseB& B, int np, int na, std::vector<double> a) {
-    const int AZ = classes(na), MU = np > 16 ? 2 : 1, NC = AZ * MU, half = na / AZ;
-    const std::vector<double> M = polar_matrices(a, np, na, true);
-    const size_t nf = (size_t)AZ * 256, nm = (size_t)NC * 16 * 256;
-    std::vector<float> host(2 * nf + 2 * nm);
-    for (int c = 0; c < AZ; ++c)
+// The transforms in that order, and the pairs' slots behind them.
+constexpr size_t kTransform = 256;                     // elements of a class's transform
+template <typename R>
+void pack_transforms(int na, std::vector<R>& out) {
+    std::vector<int32_t> slots;
+    for (int c = 0; c < classes(na); ++c) {
         for (int lane = 0; lane < 64; ++lane)
-            for (int s = 0; s < 4; ++s) {
-                const int lo = lane & 15, hi = lane >> 4;
-                const size_t at = (size_t)(c * 64 + lane) * 4 + s;
-                if (4 * hi + s < half) host[at] = (float)basis(na, mode_of(na, c, lo), 4 * hi + s);
-                if (lo < half) host[nf + at] = (float)basis(na, mode_of(na, c, 4 * s + hi), lo);
-            }
-    pack(M.data(), (size_t)NC * 16, false, &host[2 * nf]);
-    pack(M.data(), (size_t)NC * 16, true, &host[2 * nf + nm]);
-    AzOperand op;
-    snrt_status s = dev_alloc(&op.base, host.size(), "azimuthal modes");
-    if (s == SNRT_OK) s = upload(op.base, host.data(), host.size(), "azimuthal modes: upload");
-    if (s != SNRT_OK) {
-        dev_free(op.base);
-        return s;
+            for (int s = 0; s < 4; ++s)
+                out.push_back((R)basis(na, c, 4 * (lane >> 4) + s, row<R>(lane & 15)));
+        for (int m : mode_pairs(na, c)) slots.push_back(row<R>(m));
     }
+    const size_t at = out.size();
+    out.resize(at + slots.size() * sizeof(int32_t) / sizeof(R));
+    std::memcpy(&out[at], slots.data(), slots.size() * sizeof(int32_t));
+}
+
+template <typename R>
+snrt_status upload_modes(DenseB& B, const std::vector<R>& host, const R** base) {
+    R* p = nullptr;
+    const snrt_status s = dev_alloc(&p, host.size(), "azimuthal modes");
+    if (s != SNRT_OK) return s;
+    B.az_mem.push_back(p);
+    *base = p;
+    return upload(p, host.data(), host.size(), "azimuthal modes: upload");
+}
+
+snrt_status upload_operand(DenseB& B, int np, int na, std::vector<double> a) {
+    const int AZ = classes(na), NC = AZ * (np > 16 ? 2 : 1);
+    const std::vector<double> M = polar_matrices(a, np, na, true);
+    std::vector<double> host;
+    pack(M.data(), (size_t)NC * 16, false, host);
+    pack(M.data(), (size_t)NC * 16, true, host);
+    pack_transforms(na, host);
+    const double* base = nullptr;
+    const snrt_status s = upload_modes(B, host, &base);
+    if (s != SNRT_OK) return s;
+    AzModes<double>& op = B.az;
     op.np = np;
     op.na = na;
-    op.f1 = op.base;
-    op.f3 = op.base + nf;
-    op.fwd = op.base + 2 * nf;
-    op.adj = op.base + 2 * nf + nm;
-    B.az = op;
+    op.fwd = base;
+    op.adj = base + M.size();
+    op.f = base + 2 * M.size();
+    op.slots = reinterpret_cast<const int32_t*>(op.f + AZ * kTransform);
     B.az_a = std::move(a);
+    return SNRT_OK;
+}
+
+// The IMEX operands in precision R; E1, E2 [n][16][16], L [n][16].
+template <typename R>
+snrt_status upload_implicit(DenseB& B, AzModes<R>& op, const std::vector<double>& E1,
+                            const std::vector<double>& E2, const std::vector<double>& L) {
+    std::vector<R> host;
+    pack(E1.data(), L.size() / 16, false, host);
+    pack(E2.data(), L.size() / 16, false, host);
+    for (size_t i = 0; i < L.size(); ++i) host.push_back((R)L[i / 16 * 16 + row<R>(i % 16)]);
+    pack_transforms(B.az.na, host);
+    const R* base = nullptr;
+    const snrt_status s = upload_modes(B, host, &base);
+    if (s != SNRT_OK) return s;
+    op.np = B.az.np;
+    op.na = B.az.na;
+    op.e1 = base;
+    op.e2 = base + E1.size();
+    op.lam = base + 2 * E1.size();
+    op.f = op.lam + L.size();
+    op.slots = reinterpret_cast<const int32_t*>(op.f + classes(B.az.na) * kTransform);
     return SNRT_OK;
 }
 
@@ -191,6 +256,22 @@ snrt_status make_azimuth_dense(DenseB& B, const snrt_quad& q, const std::vector<
                     if (!(std::fabs(m[d] - r[d]) <= kInvariant * top)) return SNRT_OK;
             }
     }
+    double least = INFINITY, norm = 0.0;
+    bool positive = true;
+    for (int k = 0; k < np; ++k) {
+        double row = 0.0, column = 0.0;
+        for (int k2 = 0; k2 < np; ++k2)
+            for (int d = 0; d < na; ++d) {
+                const double v = a[((size_t)k * np + k2) * na + d];
+                row += std::fabs(v);
+                column += std::fabs(a[((size_t)k2 * np + k) * na + d]);
+                least = std::min(least, std::fabs(v));
+                positive &= v > 0.0;
+            }
+        norm = std::max({norm, row, column});
+    }
+    if (!(least >= kSmallest * norm)) return SNRT_OK;
+    B.az.positive = positive;
     // diag(r) A symmetric, r a function of the polar node: from the forward entries a_{0k}(0)
     std::vector<double> r(np, 1.0);
     for (int k = 1; k < np && !r.empty(); ++k) {
@@ -248,9 +329,8 @@ snrt_status make_azimuth_moments(DenseB& B, const snrt_quad& q, const double* si
 }
 
 snrt_status make_azimuth_implicit(DenseB& B) {
-    AzOperand& op = B.az;
-    if (op.na == 0 || op.imp_base || B.az_r.empty()) return SNRT_OK;
-    const int np = op.np, na = op.na, AZ = classes(na), MU = np > 16 ? 2 : 1, h = np / MU;
+    if (B.az.na == 0 || B.az.e1 || B.az32.e1 || B.az_r.empty()) return SNRT_OK;
+    const int np = B.az.np, na = B.az.na, AZ = classes(na), MU = np > 16 ? 2 : 1, h = np / MU;
     // A is symmetric after the scaling r of the polar nodes; under the polar fold r has to be
     // the same on both halves
     std::vector<double> sr(h);
@@ -284,23 +364,10 @@ snrt_status make_azimuth_implicit(DenseB& B) {
             }
         }
     }
-    const size_t nm = nb * 256;
-    std::vector<float> host(2 * nm + L.size());
-    pack(E1.data(), nb, false, host.data());
-    pack(E2.data(), nb, false, &host[nm]);
-    for (size_t i = 0; i < L.size(); ++i) host[2 * nm + i] = (float)L[i];
-    float* base = nullptr;
-    snrt_status s = dev_alloc(&base, host.size(), "azimuthal modes (implicit)");
-    if (s == SNRT_OK) s = upload(base, host.data(), host.size(), "azimuthal modes: upload");
-    if (s != SNRT_OK) {
-        dev_free(base);
-        return s;
-    }
-    op.imp_base = base;
-    op.e1 = base;
-    op.e2 = base + nm;
-    op.lam = base + 2 * nm;
-    return SNRT_OK;
+    // the general solve of a 16-bit handle is further off than FP32 modes in every element, that of
+    // an FP32 handle is not where the kernel is peaked
+    return B.precision == SNRT_FP32 ? upload_implicit(B, B.az, E1, E2, L)
+                                    : upload_implicit(B, B.az32, E1, E2, L);
 }
 
 }  // namespace snrt

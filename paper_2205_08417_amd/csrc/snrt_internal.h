@@ -69,18 +69,20 @@ struct GemmOperand {
     float* t32 = nullptr;     // FP32 in the MFMA kernel's tiled order (FP32 mode, if shaped)
 };
 
-// The scattering operator in azimuthal modes (sn_azimuth.h), for operators that couple two
-// ordinates of a product rule through their polar nodes and azimuth difference only; na == 0:
-// not available.  Device arrays in the kernels' lane order (one allocation, base): the
-// azimuthal transforms f1, f3 [na / 16][64][4]; the polar matrices fwd and adj (transposed)
-// [class][mode pair][first, second][64][4]; for the IMEX solve the modes' eigenvectors e1 =
-// V^-1 and e2 = V diag(lam) in the same order and lam [class][mode pair][first, second][16].
-struct AzOperand {
+// The scattering operator in azimuthal modes of precision R (sn_azimuth.h), for operators that
+// couple two ordinates of a product rule through their polar nodes and azimuth difference only; na
+// == 0: not available.  Device arrays in the kernels' lane order: the azimuthal transforms f
+// [azimuthal class][64][4]; the polar matrices fwd and adj (transposed) [class][mode pair][first,
+// second][64][4]; for the IMEX solve the modes' eigenvectors e1 = V^-1 and e2 = V diag(lam) in the
+// same order and lam [class][mode pair][first, second][16]; the pairs' mode slots [azimuthal
+// class][8][2].
+template <typename R>
+struct AzModes {
     int32_t np = 0, na = 0;
-    const float *f1 = nullptr, *f3 = nullptr, *fwd = nullptr, *adj = nullptr;
-    const float *e1 = nullptr, *e2 = nullptr, *lam = nullptr;
-    float* base = nullptr;
-    float* imp_base = nullptr;
+    bool positive = false;                 // every entry of the operator
+    const R *f = nullptr, *fwd = nullptr, *adj = nullptr;
+    const R *e1 = nullptr, *e2 = nullptr, *lam = nullptr;
+    const int32_t* slots = nullptr;
 };
 
 // The scattering product as a chain of right operands, forward (S = Psi X0 [X1]) and adjoint
@@ -110,10 +112,13 @@ struct DenseB {
     float* lam32 = nullptr;
     double* lam64 = nullptr;
     double imp_resid = 0.0;
-    // the same operator in azimuthal modes, where it has that structure, and its coefficients
-    // a_{kk'}(d) = A[(k, l + d)][(k', l)] (host, [np][np][na]) with the polar scaling r [np] that
-    // makes diag(r) A symmetric (empty if none)
-    AzOperand az;
+    // the same operator in azimuthal modes, where it has that structure (the 16-bit precisions'
+    // IMEX operands in FP32: az32), and its coefficients a_{kk'}(d) = A[(k, l + d)][(k', l)]
+    // (host, [np][np][na]) with the polar scaling r [np] that makes diag(r) A symmetric (empty if
+    // none)
+    AzModes<double> az;
+    AzModes<float> az32;
+    std::vector<void*> az_mem;             // their device memory
     std::vector<double> az_a, az_r;
 };
 
@@ -451,18 +456,20 @@ hipError_t launch_adjoint_fold64(int64_t nc, int32_t npieces, const StepArgs32& 
 // The products and steps of sn_azimuth.h on an operand with na != 0; states below 4 GiB.
 // launch_az_step: the explicit step, with dose != NULL also dose[c] += coeff (1/rho) sum w psi
 // of its input.
-hipError_t launch_az_product(const snrt_mesh& m, const AzOperand& op, const float* mats,
+hipError_t launch_az_product(const snrt_mesh& m, const AzModes<double>& op, const double* mats,
                              const float* in, float* out, hipStream_t st);
-hipError_t launch_az_step(const snrt_mesh& m, const AzOperand& op, const StepEpi& se, double coeff,
+hipError_t launch_az_step(const snrt_mesh& m, const AzModes<double>& op, const StepEpi& se, double coeff,
                           double* dose, hipStream_t st);
 // the IMEX step on an operand with e1 != NULL (dense kernel or moment form)
-hipError_t launch_az_imex(const snrt_mesh& m, const AzOperand& op, const StepEpi& se,
+hipError_t launch_az_imex(const snrt_mesh& m, const AzModes<double>& op, const StepEpi& se,
                           hipStream_t st);
-hipError_t launch_az_adjoint(const snrt_mesh& m, const snrt_quad& q, const AzOperand& op,
+hipError_t launch_az_imex(const snrt_mesh& m, const AzModes<float>& op, const StepEpi& se,
+                          hipStream_t st);
+hipError_t launch_az_adjoint(const snrt_mesh& m, const snrt_quad& q, const AzModes<double>& op,
                              const StepArgs32& a, const float* psi_n, const float* lam_np1,
                              float* lam_n, float* g_t, float* g_s, float* g_r, const DoseAdj& da,
                              hipStream_t st);
-hipError_t launch_az_adjoint(const snrt_mesh& m, const snrt_quad& q, const AzOperand& op,
+hipError_t launch_az_adjoint(const snrt_mesh& m, const snrt_quad& q, const AzModes<double>& op,
                              const StepArgs32& a, const float* psi_n, const float* lam_np1,
                              float* lam_n, double* g_t, double* g_s, double* g_r,
                              const DoseAdj& da, hipStream_t st);
