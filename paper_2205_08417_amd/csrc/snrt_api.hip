@@ -462,6 +462,8 @@ snrt_status snrt_quad_create(snrt_quad** out, int32_t nq, const double* omega, c
     }
     qd->nq = nq;
     qd->w_host.assign(w, w + nq);
+    qd->equal_fours = nq % 4 == 0;
+    for (int32_t q = 0; q < nq; ++q) qd->equal_fours = qd->equal_fours && w[q] == w[q & ~3];
     qd->omega_host.assign(omega, omega + (size_t)nq * 3);
     snrt_status s = SNRT_OK;
     if ((s = dev_alloc(&qd->tab32, t32.size(), "ordinates")) != SNRT_OK ||
@@ -952,7 +954,13 @@ bool azimuth_product(const snrt_mesh& m, const DenseB& B) {
     return 100 * nq >= slots * share[few ? 2 : B.precision == SNRT_FP16X3 ? 1 : 0][size];
 }
 
-// The same for the IMEX step, which replaces two products and a collision-free step; only FP32
+// Whether the mode kernels' dose takes the step's weights right: rows in whole 16-byte pieces have one
+// weight per piece.  The handle's own rule is like that, but a step may come with another one.
+bool azimuth_dose(const snrt_quad& q, const DenseB& B) {
+    return q.equal_fours || (B.az.na != 16 && B.az.na != 32);
+}
+
+// azimuth_product() for the IMEX step, which replaces two products and a collision-free step; only FP32
 // handles (whose modes are FP64) with sparsely filled slots on large meshes are better off without:
 // 198 450 cells 4 x 8 181 : 168 us, 6 x 8 182 : 212; 4 x 32 at 51 842 cells 98.9 : 94.8, at 29 768 59 :
 // 87; the moment form with 5 x 20 at 100 352 cells 155 : 144 (as a dense kernel 155 : 220).
@@ -1112,8 +1120,11 @@ snrt_status step_adjoint32_t(const char* fn, const snrt_mesh* m, const snrt_quad
     // up to 64 ordinates the transposed-step kernel holds a row in one register per lane, and the
     // gradients' row sums keep its order, whether or not the dose term rides along
     if (sc->dense && tune().step_fused && q->nq > kWave && azimuth_product(*m, sc->B)) {
-        const hipError_t e = launch_az_adjoint(*m, *q, sc->B.az, to32(a), psi_n, lam_np1, lam_n,
-                                               g_t, g_s, g_r, da, st);
+        const bool fused = !da.g_dose || azimuth_dose(*q, sc->B);
+        hipError_t e = launch_az_adjoint(*m, *q, sc->B.az, to32(a), psi_n, lam_np1, lam_n, g_t, g_s,
+                                         g_r, fused ? da : DoseAdj(), st);
+        if (e == hipSuccess && !fused)
+            e = launch_dose_adjoint(*m, *q, a->inv_rho, da.coeff, da.g_dose, lam_n, st);
         return e == hipSuccess ? SNRT_OK
                                : hip_fail(e, (std::string(fn) + ": fused transposed step").c_str());
     }
@@ -1211,9 +1222,11 @@ snrt_status snrt_step_dose(const snrt_mesh* m, const snrt_quad* q, const snrt_sc
         float* Sbuf = static_cast<float*>(ws);
         float* after = Sbuf + (size_t)m->nc * q->nq;
         if (tune().step_fused && azimuth_product(*m, sc->B)) {
-            const hipError_t e =
-                launch_az_step(*m, sc->B.az, step_epi(*m, *q, to32(a), psi_in, psi_out), coeff,
-                               dose, st);
+            const bool fused = azimuth_dose(*q, sc->B);
+            hipError_t e = launch_az_step(*m, sc->B.az, step_epi(*m, *q, to32(a), psi_in, psi_out),
+                                          coeff, fused ? dose : nullptr, st);
+            if (e == hipSuccess && !fused)
+                e = launch_dose(*m, *q, psi_in, a->inv_rho, coeff, dose, st);
             return e == hipSuccess ? SNRT_OK : hip_fail(e, "snrt_step_dose: fused dense step");
         }
         if (step_fusable(*m, *q, sc->B)) {

@@ -173,6 +173,7 @@ struct snrt_quad {
     double* tab64 = nullptr;
     std::vector<double> w_host;
     std::vector<double> omega_host;        // [nq*3] unit directions (x, y, z)
+    bool equal_fours = false;              // ordinates 4 i .. 4 i + 3 have one weight
 };
 
 // P_N system of degree N (Sec. 3.1 P_N closure, Sec. 4.3): the flux Jacobians, |A_x|,

@@ -141,3 +141,36 @@ def test_imex_step_per_element(npol, naz, kind):
     bound = (4 * 3 + 6 + 1.0 + P.dt * P.sigma_t.max()) * EPS
     print(f"imex {npol}x{naz} {kind}: {err:.2e} of {bound:.2e}")
     assert got.min() > 0.0 and err <= bound
+
+
+@pytest.mark.parametrize("npol,naz", [(16, 32), (12, 16), (10, 10)])
+def test_dose_with_the_weights_of_another_rule_than_the_kernels(npol, naz):
+    """A step whose ordinate set has other weights than the one its kernel was made with: dose and
+    reverse dose take the step's (FP64 sums of FP32 states: 1e-12; the reverse one is stored in
+    FP32)."""
+    from paper_2205_08417_amd import snrt
+    from paper_2205_08417_amd.solver import differentiable_rollout
+    omega, w = I.product_quadrature(npol, naz)
+    K = I.henyey_greenstein_kernel(omega, w, 0.8)
+    P, S = _solver(omega, w, K, lambda nc: _rows("two", omega, nc, 306), "fp32")
+    w2 = w * (1.0 + 0.3 * np.cos(np.arange(w.size)))
+    own, S.quad = S.quad, snrt.snrt_quad_create(omega, w2)
+    x = S.initial_state()
+    outs = [torch.empty_like(x) for _ in range(2)]
+    dose = torch.full((S.nc,), 0.25, dtype=torch.float64, device="cuda")
+    S.step(x, outs[0])
+    snrt.snrt_step_dose(S.mesh, S.quad, S.scatter, S.args(), x, outs[1], 0.37, dose, S.ws, S.ws_bytes)
+    assert torch.equal(outs[0], outs[1])
+    want = 0.25 + 0.37 * (P.psi0 @ w2)
+    assert float(np.abs(dose.cpu().numpy() / want - 1.0).max()) <= 1e-12
+    psi = x.clone().requires_grad_()
+    rho = torch.ones(S.nc, device="cuda", requires_grad=True)
+    _, D = differentiable_rollout(S, psi, 1, S.mats32["sigma_t"], S.mats32["sigma_s"], rho,
+                                  ckpt_every=1, dose_coeff=[0.37])
+    g = torch.linspace(0.5, 1.5, S.nc, dtype=torch.float64, device="cuda")
+    torch.autograd.backward([D], [g])
+    want = 0.37 * g.cpu().numpy()[:, None] * w2[None, :]
+    assert float(np.abs(psi.grad.cpu().numpy() / want - 1.0).max()) <= 2 * EPS
+    snrt.snrt_quad_destroy(S.quad)
+    S.quad = own
+    S.close()
