@@ -95,9 +95,9 @@ hipError_t launch_pn_t(const snrt_mesh& m, const snrt_pn& p, const typename Args
     if (m.nc == 0) return hipSuccess;
     if constexpr (sizeof(T) == 4) {
         if (p.degree == pn::kFusedHighDegree) return launch_pn_fused_high32(m, p, a, u, out, st);
-        // 198 450 cells, degrees 10 / 11 / 12: 103 / 122 / 141 us (31 / 37 / 43 to copy the state), the
-        // chunked kernel below 1 526 / 2 023 / 3 448; 3 042 cells: 17 / 18 / 20 against 731 / 975 / 1 410
-        if (pn::has_mfma_kernel(p.degree) && tune().pn_mfma && p.wa16) {
+        // 198 450 cells, degrees 10 / 11 / 12: 108 / 126 / 153 us (31 / 37 / 43 to copy the state), the
+        // chunked kernel below 1 526 / 2 023 / 3 448; 3 042 cells: 16 / 19 / 21 against 731 / 975 / 1 410
+        if (pn::has_mfma_kernel(p.degree) && tune().pn_mfma && p.wa) {
             if (p.degree == 10) return launch_pn_mfma32_10(m, p, a, u, out, st);
             if (p.degree == 11) return launch_pn_mfma32_11(m, p, a, u, out, st);
             return launch_pn_mfma32_12(m, p, a, u, out, st);

@@ -11,7 +11,7 @@ hipError_t launch_pn_fused_high32(const snrt_mesh& m, const snrt_pn& p, const St
                                   const float* u, float* out, hipStream_t st) {
     constexpr int N = pn::kFusedHighDegree;
     if (p.degree != N) return hipErrorInvalidValue;
-    if (tune().pn_mfma && p.wa16)
+    if (tune().pn_mfma && p.wa)
         return m.mf == 3 ? launch_mfma_t<N, 3>(m, p, a, u, out, st)
                          : launch_mfma_t<N, 4>(m, p, a, u, out, st);
     return m.mf == 3 ? launch_fused_t<N, 3, float>(m, p, a, p.w32, p.sig32, u, out, st)

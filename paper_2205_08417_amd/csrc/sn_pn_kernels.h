@@ -443,7 +443,9 @@ hipError_t launch_fused_t(const snrt_mesh& m, const snrt_pn& p, const typename A
 // with three products (hi hi, hi lo, lo hi) as the scattering product does: each cell's
 // staged values are scaled by 2^e_c (their largest magnitude into [2^13, 2^14)), the
 // coefficients by a per-class 2^e_W prepared on the host, and the accumulators scaled back
-// exactly.  The accumulators hold rows = outputs, columns = cells; one v_permlane32_swap per
+// exactly.  Degrees 10 to 12 run the block in FP32 instead (v_mfma_f32_32x32x2_f32, no scaling,
+// the padding columns skipped): the pairs hold 22 bits of the largest operand of a class, and the
+// chunked kernel that this step replaces there held 24 of each (pn_f32_blocks).  The accumulators hold rows = outputs, columns = cells; one v_permlane32_swap per
 // register pair turns the two halves into lane-per-cell rows that are added to the vector
 // accumulators.
 typedef _Float16 f16x8_pn __attribute__((ext_vector_type(8)));
@@ -473,9 +475,18 @@ __device__ __forceinline__ uint32_t u32_of(float f) { return __builtin_bit_cast(
 // Degrees whose matrix-core step adds u_m last, from a second read of the own values, instead of
 // with the collision term: the flux is then summed at its own magnitude, and the error against 64
 // bits stays below that of the chunked kernel that the step replaces (one step, 198 450 cells:
-// 2.8e-8 against 3.8e-8; with u_m in the sum 6.2e-8), for 7 to 8 us of 141 at degree 12.
+// 2.8e-8 against 3.8e-8; with u_m in the sum 6.2e-8), for 7 to 8 us at degree 12.
 template <int N>
 constexpr bool pn_late_u() { return N < pn::kFusedHighDegree; }
+
+// FP32 class blocks.  A lane group takes P, the other Q, of the same input, so a product adds one
+// input; 198 450 cells, degrees 10 / 11 / 12 in FP16 pairs 107 / 127 / 142 us, in FP32 108 / 126 / 153,
+// and a single coefficient is off by 2.2e-7 at most instead of 6.7e-7 / 1.2e-6 / 4.7e-6.
+template <int N>
+constexpr bool pn_f32_blocks() { return N < pn::kFusedHighDegree; }
+// What the class blocks' coefficients are kept in: FP32 [class][input / 4][lane][4] or FP16 pairs.
+template <int N>
+using PnCoef = std::conditional_t<pn_f32_blocks<N>(), float, uint16_t>;
 
 // The class block of class position Q (pn::ClassOrder<N, PZ>::order[Q]) from the staged rows
 // stage (this wavefront's 64 rows), added to acc.  mx: the largest staged magnitude of the
@@ -484,12 +495,49 @@ constexpr bool pn_late_u() { return N < pn::kFusedHighDegree; }
 template <int N, int PZ, int Q>
 __device__ __forceinline__ void pn_class_block(float (&acc)[pn::nmom(N)], float& mx,
                                                const float* stage,
-                                               const uint16_t* __restrict__ wa,
+                                               const PnCoef<N>* __restrict__ wa,
                                                const int32_t* __restrict__ wae, int lane) {
     using CO = pn::ClassOrder<N, PZ>;
     constexpr int lc = CO::order[Q];
     constexpr int n = CO::size[lc];
     static_assert(n <= 32, "one 32-row block per class");
+    if constexpr (pn_f32_blocks<N>()) {
+        f32x16_pn C[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) C[h][r] = 0.0f;
+        const float* a = wa + (size_t)(PZ * 4 + lc) * 8 * kWave * 4 + lane * 4;
+        const float* row = stage + (lane & 31) * kPnStageRow + 32 * (lane >> 5);
+        for_each_index(
+            [&](auto sc) {
+                constexpr int s = 4 * decltype(sc)::value;
+                const f32x4 w = *reinterpret_cast<const f32x4*>(a + s * kWave);
+                const f32x4 v0 = *reinterpret_cast<const f32x4*>(row + s);
+                const f32x4 v1 = *reinterpret_cast<const f32x4*>(row + 32 * kPnStageRow + s);
+                for_each_index(
+                    [&](auto ic) {
+                        constexpr int i = decltype(ic)::value;
+                        C[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[i], v0[i], C[0], 0, 0, 0);
+                        C[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[i], v1[i], C[1], 0, 0, 0);
+                    },
+                    std::make_integer_sequence<int, (n - s < 4 ? n - s : 4)>{});
+            },
+            std::make_integer_sequence<int, (n + 3) / 4>{});
+        for_each_index(
+            [&](auto rc) {
+                constexpr int r = decltype(rc)::value;
+                constexpr int i0 = (r / 4) * 8 + (r % 4), i1 = i0 + 4;
+                if constexpr (i0 < n) {
+                    const auto sw = __builtin_amdgcn_permlane32_swap(u32_of(C[0][r]), u32_of(C[1][r]),
+                                                                     false, false);
+                    constexpr int k0 = CO::at(lc, i0), k1 = i1 < n ? CO::at(lc, i1) : 0;
+                    acc[k0] += f32_of(sw[0]);
+                    if constexpr (i1 < n) acc[k1] += f32_of(sw[1]);
+                }
+            },
+            std::make_integer_sequence<int, 16>{});
+    } else {
     int E = 0;
     (void)__builtin_frexpf(mx, &E);
     const int e = (mx > 0.0f && mx < INFINITY) ? 14 - E : 0;
@@ -542,6 +590,7 @@ __device__ __forceinline__ void pn_class_block(float (&acc)[pn::nmom(N)], float&
             }
         },
         std::make_integer_sequence<int, 16>{});
+    }
 }
 
 // The moment loop of one z-parity subsystem in class order, with the load pipeline of
@@ -555,7 +604,7 @@ __device__ __forceinline__ void pn_mfma_moments(float (&acc)[pn::nmom(N)],
                                                 uint32_t own, float irho_c, float mdt, float c1,
                                                 float c2, const float* __restrict__ Ws,
                                                 const float* __restrict__ sig, float* stage,
-                                                const uint16_t* __restrict__ wa,
+                                                const PnCoef<N>* __restrict__ wa,
                                                 const int32_t* __restrict__ wae, int lane) {
     using T = float;
     using CO = pn::ClassOrder<N, PZ>;
@@ -636,7 +685,7 @@ __device__ __forceinline__ void pn_mfma_moments(float (&acc)[pn::nmom(N)],
             constexpr int t = CO::local[m];
             srow[t] = P;
             srow[32 + t] = Q;
-            mx = fmaxf(mx, fmaxf(fabsf(P), fabsf(Q)));
+            if constexpr (!pn_f32_blocks<N>()) mx = fmaxf(mx, fmaxf(fabsf(P), fabsf(Q)));
             __builtin_amdgcn_sched_barrier(0);
             // after the last input of class position q: its class block
             constexpr int q = (i < CO::size[CO::order[0]]) ? 0
@@ -650,7 +699,7 @@ __device__ __forceinline__ void pn_mfma_moments(float (&acc)[pn::nmom(N)],
                 pn_class_block<N, PZ, q>(acc, mx, stage, wa, wae, lane);
                 // a smaller next class leaves this class's values in its padding columns:
                 // clear them (the class blocks read all 32 columns of P and of Q)
-                if constexpr (q < 3) {
+                if constexpr (q < 3 && !pn_f32_blocks<N>()) {
                     constexpr int nn = CO::size[CO::order[q + 1]], nc = CO::size[CO::order[q]];
 #pragma unroll
                     for (int z = nn; z < nc; ++z) {
@@ -670,7 +719,7 @@ __device__ __forceinline__ void pn_mfma_tile(const CellGeom32* __restrict__ geom
                                              const float* __restrict__ sig, const StepArgs32& a,
                                              const float* __restrict__ u, float* __restrict__ out,
                                              uint32_t state_bytes, uint32_t inflow_bytes,
-                                             float* stage, const uint16_t* __restrict__ wa,
+                                             float* stage, const PnCoef<N>* __restrict__ wa,
                                              const int32_t* __restrict__ wae, int lane) {
     using T = float;
     using CO = pn::ClassOrder<N, PZ>;
@@ -729,7 +778,7 @@ __global__ __launch_bounds__(256, 2) void k_pn_mfma(const CellGeom32* __restrict
                                                     const float* __restrict__ u,
                                                     float* __restrict__ out, uint32_t state_bytes,
                                                     uint32_t inflow_bytes,
-                                                    const uint16_t* __restrict__ wa,
+                                                    const PnCoef<N>* __restrict__ wa,
                                                     const int32_t* __restrict__ wae) {
     __shared__ __attribute__((aligned(16))) float stage_all[4 * kPnStageWave];
     const int64_t blk = xcd_remap(blockIdx.x, gridDim.x);
@@ -762,7 +811,8 @@ hipError_t launch_mfma_t(const snrt_mesh& m, const snrt_pn& p, const StepArgs32&
         a.inflow ? (uint32_t)(m.nbf * (int64_t)p.nm * (int64_t)sizeof(float)) : 0u;
     hipLaunchKernelGGL((k_pn_mfma<N, MF>), dim3(blocks), dim3(256), 0, st, m.geom32,
                        (int32_t)m.nc, ntiles, p.wsp32, p.sig32, a, u, out,
-                       state_bytes<float>(m, p.nm), inflow_bytes, p.wa16, p.wae);
+                       state_bytes<float>(m, p.nm), inflow_bytes,
+                       static_cast<const PnCoef<N>*>(p.wa), p.wae);
     return hipGetLastError();
 }
 

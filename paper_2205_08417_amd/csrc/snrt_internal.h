@@ -194,10 +194,10 @@ struct snrt_pn {
     float* sig32 = nullptr;
     double* sig64 = nullptr;
     // the matrix-core step (pn::has_mfma_kernel): the A_x, A_y coefficients
-    // (pn::SparseOps order), the class blocks' FP16 hi/lo operands [z parity][class][K step]
-    // [hi, lo][lane][8] and their exponents [z parity][class]
+    // (pn::SparseOps order), the class blocks' operands (pn_class_block: FP32, or FP16 hi/lo at
+    // degree 13) and the exponents of the latter [z parity][class]
     float* wsp32 = nullptr;
-    uint16_t* wa16 = nullptr;
+    void* wa = nullptr;
     int32_t* wae = nullptr;
 };
 

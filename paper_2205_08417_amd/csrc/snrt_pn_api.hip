@@ -176,12 +176,14 @@ snrt_status build_operators(int N, std::vector<double>& ax, std::vector<double>&
 
 // The matrix-core step's tables of degree NH: sparse A_x / A_y coefficients, then per
 // (z parity, class) the 32 x 64 class block W[i][k] (k < 32: |A_x| on input k of the
-// class, k >= 32: |A_y| on input k - 32; halved, zero past the class), scaled by 2^e_W
+// class, k >= 32: |A_y| on input k - 32; halved, zero past the class).  Degree 13: scaled by 2^e_W
 // (largest magnitude into [2^13, 2^14)) and split into FP16 hi + lo, in the lane order of
 // the 32x32x16 products' left operand (lane l: row l % 32, k = 16 s + 8 (l / 32) + [0, 8)).
+// Below: FP32 in that of the 32x32x2 products (row l % 32, k = 32 (l / 32) + s), four s together.
 struct MfmaTables {
     std::vector<float> wsp;
-    std::vector<uint16_t> wa16;
+    std::vector<float> wa32;         // degrees below 13
+    std::vector<uint16_t> wa16;      // degree 13
     std::vector<int32_t> wae;
 };
 template <int NH>
@@ -199,7 +201,8 @@ MfmaTables mfma_tables(const snrt_pn& p) {
         const int si = SO::sidx[idx++];
         if (si >= 0) wsp[si] = (float)(0.5 * (*mats[kind])[(size_t)k * nm + m]);
     });
-    wa16.assign((size_t)2 * 4 * 4 * 2 * 64 * 8, 0);
+    if constexpr (NH < pn::kFusedHighDegree) t.wa32.assign((size_t)2 * 4 * 8 * 64 * 4, 0.0f);
+    else wa16.assign((size_t)2 * 4 * 4 * 2 * 64 * 8, 0);
     wae.assign(8, 0);
     for (int pz = 0; pz < 2; ++pz)
         for (int lc = 0; lc < 4; ++lc) {
@@ -216,6 +219,13 @@ MfmaTables mfma_tables(const snrt_pn& p) {
                     W[i * 64 + 32 + t] = (float)(0.5 * p.ay_abs[ki]);
                     wmax = std::max({wmax, std::fabs(W[i * 64 + t]), std::fabs(W[i * 64 + 32 + t])});
                 }
+            if constexpr (NH < pn::kFusedHighDegree) {
+                for (int s = 0; s < 32; ++s)
+                    for (int lane = 0; lane < 64; ++lane)
+                        t.wa32[(((size_t)(pz * 4 + lc) * 8 + s / 4) * 64 + lane) * 4 + s % 4] =
+                            W[(lane % 32) * 64 + 32 * (lane / 32) + s];
+                continue;
+            }
             int E = 0;
             (void)std::frexp(wmax, &E);
             const int ew = wmax > 0.0f ? 14 - E : 0;
@@ -279,7 +289,7 @@ void snrt_pn_destroy(snrt_pn* p) {
     dev_free(p->sig32);
     dev_free(p->sig64);
     dev_free(p->wsp32);
-    dev_free(p->wa16);
+    dev_free(p->wa);
     dev_free(p->wae);
     delete p;
 }
@@ -338,10 +348,16 @@ snrt_status snrt_pn_create(snrt_pn** out, int32_t degree, const double* sigma_l)
         default: break;
     }
     std::vector<float>& wsp = mt.wsp;
-    std::vector<uint16_t>& wa16 = mt.wa16;
     std::vector<int32_t>& wae = mt.wae;
     static_assert(pn::has_mfma_kernel(10) && !pn::has_mfma_kernel(9) && pn::kFusedHighDegree == 13,
                   "the degrees above");
+    auto upload_blocks = [&](const auto& w) {
+        if (w.empty()) return SNRT_OK;
+        typename std::decay_t<decltype(w)>::value_type* d = nullptr;
+        const snrt_status e = dev_alloc(&d, w.size(), "P_N class blocks");
+        p->wa = d;
+        return e == SNRT_OK ? upload(d, w.data(), w.size(), "snrt_pn_create: upload") : e;
+    };
     const std::vector<double> t32d = table(pn::has_fused_kernel<float>(N));
     const std::vector<double> tab = table(pn::has_fused_kernel<double>(N));
     std::vector<float> tab32(t32d.begin(), t32d.end());
@@ -361,8 +377,7 @@ snrt_status snrt_pn_create(snrt_pn** out, int32_t degree, const double* sigma_l)
         (s = upload(p->sig64, p->sig.data(), (size_t)nm, "snrt_pn_create: upload")) != SNRT_OK ||
         (s = dev_alloc(&p->wsp32, wsp.size(), "P_N sparse coefficients")) != SNRT_OK ||
         (s = upload(p->wsp32, wsp.data(), wsp.size(), "snrt_pn_create: upload")) != SNRT_OK ||
-        (s = dev_alloc(&p->wa16, wa16.size(), "P_N class blocks")) != SNRT_OK ||
-        (s = upload(p->wa16, wa16.data(), wa16.size(), "snrt_pn_create: upload")) != SNRT_OK ||
+        (s = upload_blocks(mt.wa32)) != SNRT_OK || (s = upload_blocks(mt.wa16)) != SNRT_OK ||
         (s = dev_alloc(&p->wae, wae.size(), "P_N class exponents")) != SNRT_OK ||
         (s = upload(p->wae, wae.data(), wae.size(), "snrt_pn_create: upload")) != SNRT_OK) {
         snrt_pn_destroy(p);
