@@ -5,7 +5,12 @@
 
 #include <algorithm>
 #include <cstdint>
+#include <cstdlib>
+#include <memory>
+#include <new>
 #include <vector>
+
+#include "host_ranges.h"
 
 namespace snrt {
 
@@ -44,80 +49,79 @@ struct alignas(64) StageGeom {
     float n[4][2], r[4][2];            // CellGeom32::n, CellRecon32::r_own
 };
 
-struct StageLayout {
+struct StagePart {
     std::vector<StageTile> tiles;
     std::vector<StageRow> rows;
 };
+// The kernel reaches a row's StageGeom at a 32-bit byte offset.
+constexpr int64_t kStageRows = (int64_t(1) << 32) / (int64_t)sizeof(StageGeom);
 
-// Cells along order (null: as they are numbered), at most cap to a tile, as long as the faces fit
-// a block's rows.  A face has one row and its two sides decide from their own normals which of them
-// writes it: that takes normals that are exact negatives in FP32 and one face at most between two
-// cells, in the slots of either.  false: the mesh is not like that, and has no tiles.
-inline bool layout_stage_tiles(const CellGeom32* geom, int64_t nc, int mf, const int32_t* order,
-                               int64_t cap, StageLayout& out)
+// The tiles of the cells order[first .. end) (order null: as they are numbered), at most cap cells to
+// a tile, as long as the faces fit a block's rows.  A face has one row and its two sides decide from
+// their own normals which of them writes it: that takes normals that are exact negatives in FP32 and
+// one face at most between two cells, in the slots of either.  false: these cells are not like that.
+inline bool layout_tiles_of(const CellGeom32* geom, int64_t nc, int mf, const int32_t* order,
+                            int64_t cap, int64_t first, int64_t last, StagePart& out)
 {
-    out.tiles.clear();
-    out.rows.clear();
     const auto back = [&](int32_t j, int32_t k) {      // the slot of cell k in cell j
         int g = 0;
         while (g < mf && geom[j].nbr[g] != k) ++g;
         return g;
     };
-    for (int32_t k = 0; k < nc; ++k)
-        for (int f = 0; f < mf; ++f) {
-            const int32_t j = geom[k].nbr[f];
-            if (j < 0 || j == k) continue;             // a boundary, an unused slot
-            for (int g = 0; g < f; ++g)
-                if (geom[k].nbr[g] == j) return false;
-            const float *n = geom[k].n[f], *nj = geom[j].n[back(j, k)];
-            if (n[0] != -nj[0] || n[1] != -nj[1]) return false;
-        }
-    out.rows.reserve(nc + nc / 2);
-    struct Faces {
-        int32_t row[4];
+    out.tiles.reserve((last - first) / 64 + 1);
+    out.rows.reserve((last - first) * 3 / 2);
+    struct Free {
+        void operator()(int32_t* p) const { std::free(p); }
     };
-    std::vector<int32_t> local(nc, -1), cells;         // a cell's place among the tile's rows
-    std::vector<Faces> face_row;                       // of those rows
-    for (int64_t first = 0, end; first < nc; first = end) {
-        cells.clear();
-        int32_t faces = 0;
-        for (end = first; end < nc && end - first < cap; ++end) {
-            const int32_t k = order ? order[end] : (int32_t)end;
+    // a cell's place among the tile's rows, from 1 (calloc: only the part's pages are touched)
+    std::unique_ptr<int32_t, Free> places(static_cast<int32_t*>(std::calloc(nc, sizeof(int32_t))));
+    if (!places) throw std::bad_alloc();
+    int32_t* const place = places.get();
+    int32_t cells[kStageCells + kStageFaces], face_row[kStageCells + kStageFaces][4];
+    const auto enter = [&](int32_t k, int32_t n) {
+        cells[n] = k;
+        for (int32_t& r : face_row[n]) r = -1;
+        place[k] = n + 1;
+    };
+    while (first < last) {
+        int32_t n = 0, faces = 0;
+        for (; first < last && n < cap; ++first) {
+            const int32_t k = order ? order[first] : (int32_t)first;
             int32_t add = 0;
             for (int f = 0; f < mf; ++f) {
                 const int32_t j = geom[k].nbr[f];
-                add += j != k && (j < 0 || local[j] < 0);
+                if (j == k) continue;                  // an unused slot
+                add += j < 0 || !place[j];
+                if (j < 0) continue;
+                for (int g = 0; g < f; ++g)
+                    if (geom[k].nbr[g] == j) return false;
+                const float *a = geom[k].n[f], *b = geom[j].n[back(j, k)];
+                if (a[0] != -b[0] || a[1] != -b[1]) return false;
             }
-            if (end > first && faces + add > kStageFaces) break;
-            faces += add;
-            local[k] = (int32_t)cells.size();
-            cells.push_back(k);
+            if (n > 0 && faces + add > kStageFaces) break;
+            enter(k, n);
+            for (int f = 0; f < mf; ++f) {
+                const int32_t j = geom[k].nbr[f];
+                if (j == k) continue;
+                face_row[n][f] = j >= 0 && place[j] ? face_row[place[j] - 1][back(j, k)] : faces++;
+            }
+            ++n;
         }
-        StageTile t = {(int32_t)out.rows.size(), (int32_t)cells.size(), 0, 0};
-        face_row.assign(cells.size(), {{-1, -1, -1, -1}});
-        int32_t next = 0;
+        StageTile t = {(int32_t)out.rows.size(), n, 0, 0};
         for (int32_t i = 0; i < t.cells; ++i)
             for (int f = 0; f < mf; ++f) {
                 const int32_t k = cells[i], j = geom[k].nbr[f];
-                if (j == k || face_row[i].row[f] >= 0) continue;
-                face_row[i].row[f] = next;
-                if (j >= 0) {
-                    if (local[j] < 0) {
-                        local[j] = (int32_t)cells.size();
-                        cells.push_back(j);
-                        face_row.push_back({{-1, -1, -1, -1}});
-                    }
-                    face_row[local[j]].row[back(j, k)] = next;
-                }
-                ++next;
+                if (j < 0 || j == k) continue;
+                if (!place[j]) enter(j, n++);
+                if (place[j] > t.cells) face_row[place[j] - 1][back(j, k)] = face_row[i][f];
             }
-        t.halo = (int32_t)cells.size() - t.cells;
-        for (size_t i = 0; i < cells.size(); ++i) {
+        t.halo = n - t.cells;
+        for (int32_t i = 0; i < n; ++i) {
             const int32_t k = cells[i];
-            local[k] = -1;
+            place[k] = 0;
             StageRow r = {k, {0, 0}, 0.5f * geom[k].inv_area, {}};
             bool interior = true;
-            const int32_t* rows = face_row[i].row;
+            const int32_t* rows = face_row[i];
             const int32_t any = *std::max_element(rows, rows + 4);
             for (int f = 0; f < 4; ++f) {
                 const int32_t row = rows[f], j = geom[k].nbr[f];
@@ -132,6 +136,34 @@ inline bool layout_stage_tiles(const CellGeom32* geom, int64_t nc, int mf, const
             out.rows.push_back(r);
         }
         out.tiles.push_back(t);
+    }
+    return true;
+}
+
+// The tiles of a mesh, laid out and kept part by part (host_ranges), their rows numbered through.
+// false: the mesh has none, because of its faces or because the rows exceed most.
+struct StageLayout {
+    StagePart part[kHostParts];
+    int64_t ntiles = 0, nrows = 0;
+};
+inline bool layout_stage_tiles(const CellGeom32* geom, int64_t nc, int mf, const int32_t* order,
+                               int64_t cap, StageLayout& out, int64_t most = kStageRows)
+{
+    bool ok[kHostParts];
+    std::fill(ok, ok + kHostParts, true);
+    host_ranges(nc, [&](int p, int64_t first, int64_t last) {
+        ok[p] = layout_tiles_of(geom, nc, mf, order, cap, first, last, out.part[p]);
+    });
+    out.ntiles = out.nrows = 0;
+    for (const StagePart& l : out.part) {
+        out.ntiles += (int64_t)l.tiles.size();
+        out.nrows += (int64_t)l.rows.size();
+    }
+    if (out.nrows > most || !std::all_of(ok, ok + kHostParts, [](bool b) { return b; })) return false;
+    int32_t before = 0;
+    for (StagePart& l : out.part) {
+        for (StageTile& t : l.tiles) t.rows += before;
+        before += (int32_t)l.rows.size();
     }
     return true;
 }

@@ -5,6 +5,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <memory>
 #include <numeric>
 #include <string>
 #include <type_traits>
@@ -161,9 +162,7 @@ void snrt_mesh_destroy(snrt_mesh* m) {
     dev_free(m->geom64);
     dev_free(m->d_to_user);
     dev_free(m->d_partial);
-    dev_free(m->tiles.tile);
-    dev_free(m->tiles.rows);
-    dev_free(m->tiles.geom);
+    dev_free(m->tiles.base);
     dev_free(m->recon32);
     dev_free(m->recon64);
     delete m;
@@ -303,43 +302,59 @@ snrt_status fill_stage_geom(const snrt_mesh& m, const StageTiles& t) {
 
 // The tiles of the second-order stage kernel: cells along a Hilbert curve, whatever their numbering.
 // They depend on the mesh alone and are made once, when the first midpoints are set; later midpoints
-// only change their records in place, so that a captured step stays valid.
-snrt_status make_stage_tiles(snrt_mesh* m) {
-    const int64_t nc = m->nc;
-    if (m->tiles.count) return fill_stage_geom(*m, m->tiles);
-    if (nc == 0 || !finite_centroids(m->centroid_user.data(), nc)) return SNRT_OK;
+// only change their records in place, so that a captured step stays valid.  Without memory for them
+// the mesh has none and its steps take the two kernels.  All users of the midpoints pay for the
+// tiles, so they are laid out on several threads and go up in one copy, and so are the midpoints:
+// snrt_mesh_set_face_midpoints of 198 450 cells 21 -> 5.8 ms, of 51 842 3.9 -> 1.7 (9.7 and 1.6
+// without tiles, on one thread).
+StageTiles make_stage_tiles(const snrt_mesh& m) {
+    const int64_t nc = m.nc;
+    StageTiles d;
+    if (nc == 0 || (!m.on_curve && !finite_centroids(m.centroid_user.data(), nc))) return d;
     std::vector<int32_t> order;                         // cells along the curve
-    if (!m->on_curve) {
+    if (!m.on_curve) {
         order.resize(nc);
         std::vector<int64_t> curve(nc), to_int(nc);
         std::iota(curve.begin(), curve.end(), 0);
-        hilbert_sort(curve, m->centroid_user.data());
-        for (int64_t k = 0; k < nc; ++k) to_int[m->to_user[k]] = k;
+        hilbert_sort(curve, m.centroid_user.data());
+        for (int64_t k = 0; k < nc; ++k) to_int[m.to_user[k]] = k;
         for (int64_t i = 0; i < nc; ++i) order[i] = (int32_t)to_int[curve[i]];
     }
     StageLayout layout;
-    if (!layout_stage_tiles(m->geom_host.data(), nc, m->mf, order.empty() ? nullptr : order.data(),
-                            std::clamp<int64_t>(nc / m->num_cu, 16, kStageCells), layout))
-        return SNRT_OK;
-    const std::vector<StageTile>& tiles = layout.tiles;
-    const std::vector<StageRow>& rows = layout.rows;
-    StageTiles d;
-    const char* what = "snrt_mesh_set_face_midpoints: upload";
-    snrt_status s = SNRT_OK;
-    if ((s = dev_alloc(&d.tile, (int64_t)tiles.size(), "stage tiles")) != SNRT_OK ||
-        (s = dev_alloc(&d.rows, (int64_t)rows.size(), "stage tiles")) != SNRT_OK ||
-        (s = dev_alloc(&d.geom, (int64_t)rows.size(), "stage tiles")) != SNRT_OK ||
-        (s = upload(d.tile, tiles.data(), (int64_t)tiles.size(), what)) != SNRT_OK ||
-        (s = upload(d.rows, rows.data(), (int64_t)rows.size(), what)) != SNRT_OK) {
-        dev_free(d.tile);
-        dev_free(d.rows);
-        dev_free(d.geom);
-        return s;
+    if (!layout_stage_tiles(m.geom_host.data(), nc, m.mf, order.empty() ? nullptr : order.data(),
+                            std::clamp<int64_t>(nc / m.num_cu, 16, kStageCells), layout))
+        return d;
+    // the records of the rows and the tiles go up in one copy, behind those of the device's own making
+    const size_t made = layout.nrows * sizeof(StageGeom), rows = layout.nrows * sizeof(StageRow);
+    const size_t copied = rows + layout.ntiles * sizeof(StageTile);
+    const std::unique_ptr<char[]> host(new char[copied]);
+    host_ranges(nc, [&](int part, int64_t, int64_t last) {
+        StageRow* r = reinterpret_cast<StageRow*>(host.get());
+        StageTile* t = reinterpret_cast<StageTile*>(host.get() + rows);
+        for (int p = 0; p < kHostParts; ++p) {          // the parts after this thread's last
+            const StagePart& l = layout.part[p];
+            const bool mine = p == part || (last == nc && p > part);
+            if (mine) std::copy(l.rows.begin(), l.rows.end(), r);
+            if (mine) std::copy(l.tiles.begin(), l.tiles.end(), t);
+            r += l.rows.size();
+            t += l.tiles.size();
+        }
+    });
+    if (hipMalloc(&d.base, made + copied) != hipSuccess) {
+        (void)hipGetLastError();
+        return StageTiles();
     }
-    d.count = (int32_t)tiles.size();
-    d.nrows = (int64_t)rows.size();
-    m->tiles = d;
-    return fill_stage_geom(*m, d);
+    d.geom = static_cast<StageGeom*>(d.base);
+    d.rows = reinterpret_cast<StageRow*>(d.geom + layout.nrows);
+    d.tile = reinterpret_cast<StageTile*>(d.rows + layout.nrows);
+    if (upload(reinterpret_cast<char*>(d.rows), host.get(), copied,
+               "snrt_mesh_set_face_midpoints: upload") != SNRT_OK) {
+        dev_free(d.base);
+        return StageTiles();
+    }
+    d.count = (int32_t)layout.ntiles;
+    d.nrows = layout.nrows;
+    return d;
 }
 
 }  // namespace
@@ -357,40 +372,44 @@ snrt_status snrt_mesh_set_face_midpoints(snrt_mesh* m, const double* face_mid) {
     SNRT_TRY(check_device(m->device, "snrt_mesh_set_face_midpoints"));
     const std::vector<int32_t>& nbr = m->face_nbr_user;
     const std::vector<double>& cen = m->centroid_user;
-    std::vector<CellRecon32> r32(nc);
-    std::vector<CellRecon64> r64(nc);
-    for (int64_t k = 0; k < nc; ++k) {
-        const int64_t i = m->to_user[k];
-        CellRecon64& b = r64[k];
-        CellRecon32& a = r32[k];
-        std::memset(&a, 0, sizeof(a));
-        std::memset(&b, 0, sizeof(b));
-        for (int f = 0; f < mf; ++f) {
-            const int32_t j = nbr[i * mf + f];
-            if (j == kUnusedFace) continue;
-            const double* mid = face_mid + (i * mf + f) * 2;
-            SNRT_REQUIRE(is_finite(mid[0]) && is_finite(mid[1]), SNRT_E_ARG,
-                         "snrt_mesh_set_face_midpoints: non-finite midpoint at cell " +
-                             std::to_string(i));
-            b.r_own[f][0] = mid[0] - cen[2 * i];
-            b.r_own[f][1] = mid[1] - cen[2 * i + 1];
-            if (j >= 0) {
-                int g = 0;
-                while (g < mf && nbr[(int64_t)j * mf + g] != (int32_t)i) ++g;
-                // adjacency was checked symmetric at creation, so the back slot exists
-                const double* mj = face_mid + ((int64_t)j * mf + g) * 2;
-                SNRT_REQUIRE(is_finite(mj[0]) && is_finite(mj[1]), SNRT_E_ARG,
-                             "snrt_mesh_set_face_midpoints: non-finite midpoint at cell " +
-                                 std::to_string(j));
-                b.r_far[f][0] = mj[0] - cen[2 * (int64_t)j];
-                b.r_far[f][1] = mj[1] - cen[2 * (int64_t)j + 1];
-            }
-            for (int d = 0; d < 2; ++d) {
-                a.r_own[f][d] = (float)b.r_own[f][d];
-                a.r_far[f][d] = (float)b.r_far[f][d];
+    const std::unique_ptr<CellRecon32[]> r32(new CellRecon32[nc]);
+    const std::unique_ptr<CellRecon64[]> r64(new CellRecon64[nc]);
+    int64_t bad[kHostParts];                            // a cell with a non-finite midpoint
+    std::fill(bad, bad + kHostParts, -1);
+    host_ranges(nc, [&](int part, int64_t first, int64_t last) {
+        for (int64_t k = first; k < last && bad[part] < 0; ++k) {
+            const int64_t i = m->to_user[k];
+            CellRecon64& b = r64[k];
+            CellRecon32& a = r32[k];
+            std::memset(&a, 0, sizeof(a));
+            std::memset(&b, 0, sizeof(b));
+            for (int f = 0; f < mf && bad[part] < 0; ++f) {
+                const int32_t j = nbr[i * mf + f];
+                if (j == kUnusedFace) continue;
+                const double* mid = face_mid + (i * mf + f) * 2;
+                if (!is_finite(mid[0]) || !is_finite(mid[1])) bad[part] = i;
+                b.r_own[f][0] = mid[0] - cen[2 * i];
+                b.r_own[f][1] = mid[1] - cen[2 * i + 1];
+                if (j >= 0) {
+                    int g = 0;
+                    while (g < mf && nbr[(int64_t)j * mf + g] != (int32_t)i) ++g;
+                    // adjacency was checked symmetric at creation, so the back slot exists
+                    const double* mj = face_mid + ((int64_t)j * mf + g) * 2;
+                    if (bad[part] < 0 && (!is_finite(mj[0]) || !is_finite(mj[1]))) bad[part] = j;
+                    b.r_far[f][0] = mj[0] - cen[2 * (int64_t)j];
+                    b.r_far[f][1] = mj[1] - cen[2 * (int64_t)j + 1];
+                }
+                for (int d = 0; d < 2; ++d) {
+                    a.r_own[f][d] = (float)b.r_own[f][d];
+                    a.r_far[f][d] = (float)b.r_far[f][d];
+                }
             }
         }
-    }
+    });
+    for (const int64_t cell : bad)
+        SNRT_REQUIRE(cell < 0, SNRT_E_ARG,
+                     "snrt_mesh_set_face_midpoints: non-finite midpoint at cell " +
+                         std::to_string(cell));
     if (!m->recon32) {
         snrt_status s = SNRT_OK;
         if ((s = dev_alloc(&m->recon32, std::max<int64_t>(nc, 1), "reconstruction vectors")) != SNRT_OK)
@@ -402,10 +421,18 @@ snrt_status snrt_mesh_set_face_midpoints(snrt_mesh* m, const double* face_mid) {
         }
     }
     snrt_status s = SNRT_OK;
-    if ((s = upload(m->recon32, r32.data(), nc, "snrt_mesh_set_face_midpoints: upload")) != SNRT_OK ||
-        (s = upload(m->recon64, r64.data(), nc, "snrt_mesh_set_face_midpoints: upload")) != SNRT_OK)
+    if ((s = upload(m->recon32, r32.get(), nc, "snrt_mesh_set_face_midpoints: upload")) != SNRT_OK ||
+        (s = upload(m->recon64, r64.get(), nc, "snrt_mesh_set_face_midpoints: upload")) != SNRT_OK)
         return s;
-    return make_stage_tiles(m);
+    if (!m->geom_host.empty()) {
+        try {
+            m->tiles = make_stage_tiles(*m);
+        } catch (const std::bad_alloc&) {
+        }
+        g_last_error.clear();
+        std::vector<CellGeom32>().swap(m->geom_host);
+    }
+    return m->tiles.count ? fill_stage_geom(*m, m->tiles) : SNRT_OK;
 }
 
 snrt_status snrt_mesh_permutation(const snrt_mesh* m, int64_t* internal_to_user) {

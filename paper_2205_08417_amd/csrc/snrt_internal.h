@@ -47,9 +47,10 @@ static_assert(sizeof(CellRecon64) == 128, "two cache lines per cell");
 
 // The tiles of a mesh on the device.
 struct StageTiles {
-    StageTile* tile = nullptr;         // [count]
-    StageRow* rows = nullptr;
+    void* base = nullptr;              // one allocation
     StageGeom* geom = nullptr;         // of the same row
+    StageRow* rows = nullptr;
+    StageTile* tile = nullptr;         // [count]
     int32_t count = 0;                 // 0: no tiles, the two-kernel stage
     int64_t nrows = 0;
 };
@@ -158,7 +159,7 @@ struct snrt_mesh {
     // host copies kept for the second-order set-up (user order)
     std::vector<int32_t> face_nbr_user;    // [nc*mf]
     std::vector<double> centroid_user;     // [nc*2], empty if none was given
-    std::vector<snrt::CellGeom32> geom_host;   // geom32
+    std::vector<snrt::CellGeom32> geom_host;   // geom32, until the tiles are made
     bool on_curve = false;                 // the internal order is the Hilbert curve's
     snrt::CellRecon32* recon32 = nullptr;  // second-order reconstruction vectors (internal
     snrt::CellRecon64* recon64 = nullptr;  // order); NULL until face midpoints are set

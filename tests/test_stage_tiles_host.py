@@ -15,14 +15,25 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 SHIM = r"""
 #include "sn_stage_tiles.h"
 using namespace snrt;
-static StageLayout layout;
-extern "C" int make(const void* geom, long nc, int mf, const int* order, long cap) {
-    return layout_stage_tiles(static_cast<const CellGeom32*>(geom), nc, mf, order, cap, layout);
+static std::vector<StageTile> all_tiles;
+static std::vector<StageRow> all_rows;
+extern "C" int make(const void* geom, long nc, int mf, const int* order, long cap, long most) {
+    StageLayout l;
+    if (!layout_stage_tiles(static_cast<const CellGeom32*>(geom), nc, mf, order, cap, l,
+                            most < 0 ? kStageRows : most))
+        return 0;
+    all_tiles.clear();
+    all_rows.clear();
+    for (const StagePart& p : l.part) {
+        all_tiles.insert(all_tiles.end(), p.tiles.begin(), p.tiles.end());
+        all_rows.insert(all_rows.end(), p.rows.begin(), p.rows.end());
+    }
+    return (long)all_tiles.size() == l.ntiles && (long)all_rows.size() == l.nrows;
 }
-extern "C" long ntiles() { return (long)layout.tiles.size(); }
-extern "C" long nrows() { return (long)layout.rows.size(); }
-extern "C" const void* tiles() { return layout.tiles.data(); }
-extern "C" const void* rows() { return layout.rows.data(); }
+extern "C" long ntiles() { return (long)all_tiles.size(); }
+extern "C" long nrows() { return (long)all_rows.size(); }
+extern "C" const void* tiles() { return all_tiles.data(); }
+extern "C" const void* rows() { return all_rows.data(); }
 """
 ROW, INTERIOR, LOWER, BOUNDARY, SKIP = 0x1ff, 0x1000, 0x2000, 0x4000, 0x8000
 FACES = 158
@@ -37,7 +48,7 @@ def shim(tmp_path_factory):
                     str(src), "-o", str(so)], check=True)
     lib = ctypes.CDLL(str(so))
     lib.make.argtypes = [ctypes.c_void_p, ctypes.c_long, ctypes.c_int, ctypes.c_void_p,
-                         ctypes.c_long]
+                         ctypes.c_long, ctypes.c_long]
     for f in (lib.ntiles, lib.nrows):
         f.restype = ctypes.c_long
     for f in (lib.tiles, lib.rows):
@@ -59,9 +70,9 @@ def _records(mesh):
     return g
 
 
-def _layout(shim, g, mf, order=None, cap=96):
+def _layout(shim, g, mf, order=None, cap=96, most=-1):
     o = None if order is None else np.ascontiguousarray(order, dtype=np.int32)
-    if not shim.make(g.ctypes.data, len(g), mf, None if o is None else o.ctypes.data, cap):
+    if not shim.make(g.ctypes.data, len(g), mf, None if o is None else o.ctypes.data, cap, most):
         return None
     tiles = np.ctypeslib.as_array((ctypes.c_int32 * (4 * shim.ntiles())).from_address(
         shim.tiles())).reshape(-1, 4).copy()
@@ -111,6 +122,8 @@ MESHES = {
     "tri_1922": lambda: I.jittered_delaunay_mesh(32, 0.0, 1.0, seed=282),
     "quad_143": lambda: I.quad_grid_mesh(13, 11),
     "padded_512": lambda: I.pad_faces(I.jittered_delaunay_mesh(17, 0.0, 1.0, seed=283), 4),
+    "tri_9800": lambda: I.jittered_delaunay_mesh(71, 0.0, 1.0, seed=286),      # two threads
+    "quad_36481": lambda: I.quad_grid_mesh(191, 191),                          # eight
 }
 
 
@@ -146,3 +159,12 @@ def test_normals_that_do_not_cancel_leave_no_tiles(shim):
     k = int(np.flatnonzero((g["nbr"][:, :3] >= 0).all(1))[5])
     g["n"][k, 1, 0] *= np.float32(1.0 + 2.0 ** -22)
     assert _layout(shim, g, 3) is None
+
+
+def test_rows_beyond_the_kernels_offsets_leave_no_tiles(shim):
+    m = MESHES["tri_9800"]()
+    g = _records(m)
+    n = len(_layout(shim, g, 3)[1])
+    assert n < 2 ** 26      # records of 64 bytes at 32-bit offsets
+    assert _layout(shim, g, 3, most=n) is not None
+    assert _layout(shim, g, 3, most=n - 1) is None
