@@ -433,8 +433,7 @@ hipError_t launch_flux2_t(const snrt_mesh& m, const snrt_quad& q,
             if (persistent) {
                 static const int occ = resident_blocks(k_flux2p<V, E, MF, R, D, F, T>);
                 const StepShape sp = step_shape(m, m.nc << shift, shift ? kCellsPerBlock : 1, occ,
-                                                tune().flux2_blocks_per_cu *
-                                                    (small_rows<T>(q.nq) ? 3 : 1));
+                                                sweep_width<T>(q.nq, tune().flux2_blocks_per_cu, 2, 6));
                 hipLaunchKernelGGL((k_flux2p<V, E, MF, R, D, F, T>), dim3(sp.blocks),
                                    dim3(kStepBlock), 0, st, geom, recon, m.nc, q.nq, tab, a, psi,
                                    G, S, psi_n, out, sp.cells_per_xcd, (uint32_t)m.nbf,

@@ -1036,18 +1036,19 @@ struct StepShape {
 };
 
 // Rows of at most 512 bytes put little load on a CU's memory path, and a sweep over them waits for
-// latency: the widths that suit 1 KB rows are then multiplied (79 202 / 178 802 cells x 64 FP32
-// ordinates, step at 3 and 6 blocks per CU: 17.1 / 45.6 and 14.4 / 33.5 us, 100 ordinates 20.1 /
-// 41.8 and 18.1 / 36.6; the second-order update at 2 and 6: its whole step 122 / 253 and 100 / 206
-// us; 182 and 256 ordinates are as fast at 3, respectively 2).
+// latency: they take more blocks per CU, unless the caller sets a width (SNRT_STEP_TUNE).  us per
+// step at 3 and 6 blocks per CU, 64 ordinates FP32 (FP64): 16 200 cells 6.7 and 6.8 (6.6 and 6.7),
+// 29 768 8.3 and 7.6 (9.3 and 8.2), 51 842 11.7 and 10.4 (19.4 and 14.6), 198 450 53 and 38 (67 and
+// 48); below 16 200 cells all are resident either way.  The same at 16 to 128 ordinates, with IMEX and
+// dose, and for the second-order update at 2 and 6 (FP64, 51 842 cells: its whole step 128 and 98);
+// 128 ordinates at 29 768 cells lose 5 %.  182 and 256 ordinates are as fast at 3, respectively 2.
 template <typename T>
-bool small_rows(int32_t nq) {
-    return nq * (int)sizeof(T) <= 512;
+int sweep_width(int32_t nq, int set, int usual, int small) {
+    return set > 0 ? set : nq * (int)sizeof(T) <= 512 ? small : usual;
 }
 
 inline StepShape step_shape(const snrt_mesh& m, int64_t items, int cpw,
-                            int resident_blocks_per_cu, int blocks_per_cu = 0) {
-    int bpc = blocks_per_cu > 0 ? blocks_per_cu : tune().step_blocks_per_cu;
+                            int resident_blocks_per_cu, int bpc) {
     if (resident_blocks_per_cu > 0 && bpc > resident_blocks_per_cu) bpc = resident_blocks_per_cu;
     int64_t want = (items + (int64_t)kCellsPerBlock - 1) / (int64_t)kCellsPerBlock;
     int64_t cap = (int64_t)m.num_cu * bpc;
@@ -1075,7 +1076,7 @@ hipError_t launch_fwd(const typename GeomOf<T>::type* geom, const snrt_mesh& m, 
                       T* psi_out, const T* S, int shift, hipStream_t st,
                       const double* wq = nullptr, double* dpart = nullptr)
 {
-    const int bpc = tune().step_blocks_per_cu * (small_rows<T>(nq) ? 2 : 1);
+    const int bpc = sweep_width<T>(nq, tune().step_blocks_per_cu, 3, 6);
     if (dpart) {
         if constexpr (!IMEX) {
             static const int occ = resident_blocks(k_step_dose<V, E, MF, RHO, DENSE, T>);

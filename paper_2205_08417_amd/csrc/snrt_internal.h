@@ -217,8 +217,8 @@ namespace snrt {
 // epilogues (separate passes instead), SNRT_PN_MFMA=0 the matrix-core class blocks of the
 // P_N steps of degrees 10 to 13, SNRT_AZIMUTH=0 the azimuthal-mode scattering (all read once per process).
 struct Tune {
-    int step_blocks_per_cu = 3;
-    int flux2_blocks_per_cu = 2;   // its larger per-cell footprint favours a narrower sweep
+    int step_blocks_per_cu = 0;    // 0: sweep_width's
+    int flux2_blocks_per_cu = 0;
     int adjoint_blocks_per_cu = 7; // the adjoint's smaller workloads favour a wide grid
     bool gemm_stagger = true;      // staggered split/product phases in the BF16 product
     bool gemm_epilogue = true;     // IMEX per-cell steps in the products' epilogues
