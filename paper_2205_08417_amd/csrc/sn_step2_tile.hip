@@ -328,19 +328,36 @@ hipError_t launch_stage_geom(const snrt_mesh& m, const StageRow* rows, StageGeom
     return hipGetLastError();
 }
 
-// Where the two kernels' gradients outgrow the caches (states from 40 MB: 36 450 x 256 110 -> 106
-// us, 21 000 x 640 382 -> 181, 198 450 x 256 732 -> 441), where there are enough cells for whole
-// tiles (36 450 x 64 51 -> 46, 80 000 x 100 148 -> 106), and where the launches are what costs
-// (2 048 x 64 20 -> 13, 648 x 480 23 -> 20).  Between these the gradients stay in the caches and
-// the halo's slopes and the few blocks cost more: 5 000 x 256 24 -> 34, 21 632 x 64 33 -> 43.
-bool stage2_tiled(const snrt_mesh& m, const snrt_quad& q) {
+// Where the two kernels' gradients outgrow the caches, where there are enough cells for whole tiles,
+// and where the launches are what costs.  Between these the gradients stay in the caches and the
+// halo's slopes and the few blocks cost more.  Quadrilaterals have more faces to a tile, and
+// Venkatakrishnan's limiter a quotient for each (Barth-Jespersen two per cell).  us per Heun step,
+// tiles : two kernels, Barth-Jespersen on triangles | quadrilaterals, Venkatakrishnan on the same:
+//     4 000 x   64   14 : 16  |   15 : 16       15 : 18  |   17 : 17
+//     4 000 x  128   16 : 17  |   18 : 18       19 : 18  |   24 : 20
+//     2 000 x  512   26 : 20  |   29 : 22       30 : 23  |   39 : 27
+//     4 000 x  256   24 : 20  |   27 : 21       28 : 22  |   36 : 25
+//    16 000 x  256   62 : 51  |   72 : 55       75 : 59  |   95 : 67
+//    22 000 x  512  127 : 129 |  149 : 142     154 : 138 |  200 : 158     (45 MB)
+//    32 800 x   64   45 : 43  |   45 : 47       51 : 46  |   54 : 52
+//    32 800 x  100   56 : 65  |   55 : 74       72 : 67  |   78 : 79
+//    32 800 x  256   87 : 93  |  104 : 101     107 : 105 |  138 : 116
+//    32 800 x  512  164 : 203 |  199 : 228     202 : 216 |  265 : 243     (67 MB)
+//    50 000 x  256  128 : 129 |  148 : 142     162 : 147 |  199 : 166
+//    50 000 x  480  254 : 352 |  315 : 403     300 : 362 |  406 : 423     (96 MB)
+//   100 000 x   32  100 : 117 |  116 : 129     113 : 118 |  137 : 133
+//   100 000 x  256  220 : 358 |  270 : 393     279 : 372 |  380 : 423
+bool stage2_tiled(const snrt_mesh& m, const snrt_quad& q, const Limiter& lim) {
     const int64_t bytes = m.nc * (int64_t)q.nq * 4;
     // 32-bit offsets, as in the persistent kernels
     if (m.tiles.count == 0 || bytes >= (int64_t(1) << 32) ||
         m.nbf * (int64_t)q.nq * 4 >= (int64_t(1) << 32))
         return false;
-    return m.nc >= 32768 || bytes >= (int64_t(40) << 20) || (m.nc <= 4096 && q.nq <= 128) ||
-           (m.nc <= 2048 && q.nq <= 512);
+    const bool vk = lim.kind == SNRT_LIMITER_VENKATAKRISHNAN, quads = m.mf == 4;
+    if (m.nc <= 4096 && q.nq <= (vk || quads ? 64 : 128)) return true;
+    const int64_t mb = bytes >> 20;
+    if (vk) return mb >= (quads ? 90 : 64);
+    return mb >= 48 || m.nc >= 65536 || (m.nc >= 32768 && q.nq > 64);
 }
 
 hipError_t launch_stage2_32(const snrt_mesh& m, const snrt_quad& q, const StepArgs32& a,

@@ -1372,7 +1372,7 @@ snrt_status step2_common(const char* fn, const snrt_mesh* m, const snrt_quad* q,
     for (int stage = 0; stage < 2 && e == hipSuccess; ++stage) {
         if constexpr (sizeof(T) == 4) {
             const StepArgs32 a32 = to32(a);
-            if (stage2_tiled(*m, *q)) {
+            if (stage2_tiled(*m, *q, lim)) {
                 if (S) e = scatter_product32(*m, sc, in[stage], S, false, U, st);
                 if (e == hipSuccess)
                     e = launch_stage2_32(*m, *q, a32, lim, in[stage], S,

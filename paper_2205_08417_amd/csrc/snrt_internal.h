@@ -546,7 +546,7 @@ hipError_t launch_grad2_32(const snrt_mesh& m, const snrt_quad& q, const StepArg
 hipError_t launch_grad2_64(const snrt_mesh& m, const snrt_quad& q, const StepArgs64& a,
                            const Limiter& lim, const double* psi, double* G, hipStream_t st);
 // Both in one launch (sn_step2_tile.hip), for meshes with tiles; S NULL: isotropic scattering.
-bool stage2_tiled(const snrt_mesh& m, const snrt_quad& q);
+bool stage2_tiled(const snrt_mesh& m, const snrt_quad& q, const Limiter& lim);
 // StageTiles::geom of n rows from the mesh's records
 hipError_t launch_stage_geom(const snrt_mesh& m, const StageRow* rows, StageGeom* geom, int64_t n,
                              hipStream_t st);

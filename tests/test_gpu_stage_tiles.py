@@ -93,3 +93,52 @@ def test_a_captured_step_sees_midpoints_that_are_set_later(mesh):
         assert rel_l2(S.to_user(out).cpu().numpy(), _oracle(dataclasses.replace(P, mesh=moved))) <= TOL
         del hold
     S.close()
+
+
+# A block's chunks of 128 ordinates.  More than 3 072 tiles take all chunks in one block (240 ordinates:
+# a full chunk and one of 112); 1 200 tiles split them, 480 ordinates into two and two, 640 into two,
+# two and one, 500 ordinates of 600 tiles into one each.  The row sums of isotropic scattering are kept
+# between a block's chunks.
+@pytest.mark.parametrize("nx,npol,naz,dense", [(388, 12, 20, False), (224, 20, 24, False),
+                                               (224, 20, 24, True), (224, 20, 32, False),
+                                               (159, 20, 25, False)])
+def test_several_ordinate_chunks_in_a_block(nx, npol, naz, dense):
+    _large(I.jittered_delaunay_mesh(nx, 0.0, 1.0, seed=296), npol, naz, dense)
+
+
+@pytest.mark.parametrize("limiter", ["barth-jespersen", "venkatakrishnan"])
+def test_large_quadrilateral_meshes(limiter):
+    _large(I.quad_grid_mesh(223, 221), 16, 32, False, limiter=limiter)
+
+
+def _large(mesh, npol, naz, dense, **kw):
+    """Sampled cells of one step against the oracle on the part of the mesh that they depend on."""
+    from paper_2205_08417_amd.solver import Solver
+    omega, w = I.product_quadrature(npol, naz)
+    K = I.henyey_greenstein_kernel(omega, w, 0.7) if dense else None
+    P = small_problem(mesh, omega_w=(omega, w), K=K, seed=297, rho=True, source=True, inflow=True)
+    S = Solver(P)
+    got = _heun(S, **kw)
+    S.close()
+    rng = np.random.default_rng(298)
+    seeds = rng.choice(mesh.ncells, 60, replace=False)
+    ring = [set(seeds.tolist())]
+    for _ in range(4):                        # two stages of gradients and fluxes
+        n = mesh.face_nbr[sorted(ring[-1])]
+        ring.append(ring[-1] | set(n[n >= 0].tolist()))
+    part = np.array(sorted(ring[-1]))
+    to = np.full(mesh.ncells, -1)
+    to[part] = np.arange(part.size)
+    nbr = mesh.face_nbr[part]
+    cut = (nbr >= 0) & (to[np.maximum(nbr, 0)] < 0)
+    nbr = np.where(nbr >= 0, to[np.maximum(nbr, 0)], nbr)
+    nbr[cut] = -1                             # beyond the rings: any boundary does
+    sub = dataclasses.replace(mesh, cells=mesh.cells[part], face_nbr=nbr.astype(np.int32),
+                              face_normal=mesh.face_normal[part], area=mesh.area[part],
+                              centroid=mesh.centroid[part], face_mid=mesh.face_mid[part])
+    Q = dataclasses.replace(P, mesh=sub, sigma_t=P.sigma_t[part], sigma_s=P.sigma_s[part],
+                            rho=P.rho[part], source=P.source[part], psi0=P.psi0[part])
+    want = _oracle(Q, **kw)
+    err = rel_l2(got[seeds], want[to[seeds]])
+    print(f"{mesh.ncells} x {P.nq} {kw}: {err:.2e}")
+    assert err <= TOL
