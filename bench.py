@@ -152,11 +152,10 @@ def timed(fn, n, stream):
 
 def product_rate(S, psi, reps: int = 10, passes: int = 3, kernel: str = "k_gemm_bf16",
                  peak: float = None):
-    """Rate of the scattering product on state psi.  The kernels here are invariant under the
-    azimuth of their product rules and run through azimuthal modes (k_az_product: bound by
-    memory, one read and one write of the state).  With SNRT_AZIMUTH=0 the dense product runs:
-    executed TFLOP/s of the BF16 hi+lo product (three passes, against the BF16 MFMA peak) or the
-    FP32 one (one pass, FP32 MFMA peak)."""
+    """Rate of the scattering product on state psi.  ``passes`` 0: through azimuthal modes
+    (k_az_product: one read and one write of the state).  Else the executed TFLOP/s of a general
+    product: BF16 or FP16 split (two or three passes, against the BF16 MFMA peak) or FP32 (one pass,
+    FP32 MFMA peak)."""
     import torch
     from paper_2205_08417_amd import snrt
     peak = BF16_PEAK_TFLOPS if peak is None else peak
@@ -167,7 +166,7 @@ def product_rate(S, psi, reps: int = 10, passes: int = 3, kernel: str = "k_gemm_
     apply()
     torch.cuda.synchronize()
     ms = timed(apply, reps, stream)
-    if modes_on():
+    if passes == 0:
         gbs = 2.0 * psi.element_size() * S.nc * S.nq / (ms * 1e-3) / 1e9
         return {"kernel": "k_az_product", "ms": ms, "gbs": gbs, "hbm_frac": gbs / HBM_PEAK_GBS}
     tflops = passes * 2.0 * S.nc * S.nq * S.nq / (ms * 1e-3) / 1e12
@@ -180,13 +179,35 @@ def modes_on() -> bool:
     return os.environ.get("SNRT_AZIMUTH", "1") != "0"
 
 
-def step_form() -> str:
+MODES = ("FP64 azimuthal modes, S rounded to FP32 once (whatever the handle's precision: the kernel "
+         "depends on the angle only, on a product rule)")
+
+
+def arithmetic(general: str) -> str:
+    """What the scattering product of a kernel of the angle is computed in; ``general``: the
+    arithmetic of the general product of the handle's precision."""
+    return MODES if modes_on() else general
+
+
+def unstructured(P):
+    """The same problem with a kernel that is not a function of the angle: its entries times 1 + 1e-8
+    s_q s_p for random s, which the general products then run (nothing else changes above their
+    rounding)."""
+    import dataclasses
+    import numpy as np
+    s = np.random.default_rng(0).uniform(-1.0, 1.0, P.nq)
+    return dataclasses.replace(P, K=P.K * (1.0 + 1e-8 * s[:, None] * s[None, :]))
+
+
+def step_form(general: bool = False) -> str:
     """How the library runs an explicit dense step (SNRT_AZIMUTH, SNRT_STEP_FUSED, read once per
-    process)."""
-    if modes_on():
+    process); ``general``: of an operator without azimuthal modes."""
+    fused = os.environ.get("SNRT_STEP_FUSED", "1") != "0"
+    if modes_on() and not general:
         return ("one launch: k_az_step, the scattering product through azimuthal modes and the "
-                "update of the same cells (product rules, kernels of the angle)")
-    if os.environ.get("SNRT_STEP_FUSED", "1") == "0":
+                "update of the same cells" if fused else
+                "two launches: k_az_product into the workspace, then k_step")
+    if not fused:
         return "two launches: scattering product into the workspace, then k_step"
     return ("one launch: k_gemm_step, the scattering product whose tiles run the update of "
             "their cells and ordinates (triangles, nq % 256 == 0, BF16/FP16 products)")
@@ -194,25 +215,27 @@ def step_form() -> str:
 
 def transposed_step_form() -> str:
     """How the library runs a dense transposed step (the same switches as the forward)."""
+    fused = os.environ.get("SNRT_STEP_FUSED", "1") != "0"
+    if not fused:
+        return (f"two launches: transposed {'k_az_product' if modes_on() else 'product'} into the "
+                "workspace, then k_adjoint_p, and the dose functional's term in a pass of its own")
     if modes_on():
         return ("one launch: k_az_adjoint, the transposed product through azimuthal modes, the "
                 "update (with the dose functional's term) and the gradient sums")
-    if os.environ.get("SNRT_STEP_FUSED", "1") == "0":
-        return ("two launches: transposed product into the workspace, then k_adjoint_p with "
-                "the dose functional's term")
     return ("one launch: k_gemm_adjoint, the transposed product whose tiles run the adjoint "
             "update (with the dose functional's term) of their cells and ordinates, then "
             "k_adjoint_fold adding the per-piece gradient sums")
 
 
 def bench_dense(steps, warmup: int):
-    """Anisotropic HG line source (100 352 cells x 1024 ordinates) with the scattering product
-    in each mixed precision (BF16 hi+lo in three and two products, FP16 hi+lo in three) and
-    in FP32.  Each low-precision run is timed over the whole 200-step workload from the
+    """Anisotropic HG line source (100 352 cells x 1024 ordinates): the step as the library runs it
+    (through azimuthal modes), then with the general scattering product in each mixed precision (BF16
+    hi+lo in three and two products, FP16 hi+lo in three) and in FP32, on the same kernel without its
+    azimuthal structure.  Each run but FP32's is timed over the whole 200-step workload from the
     initial pulse (steps=None; warm-up steps run on a separate copy first): early states are
     mostly exact zeros, on which the matrix cores draw less power and clock higher, so a
-    window of early steps alone would flatter the rate.  The products' MFMA utilisation is
-    measured on the run's final state and on a dense random state; every precision's final
+    window of early steps alone would flatter the rate.  The products' rates are
+    measured on the run's final state and on a dense random state; every run's final
     state then takes one more step whose sampled cells are checked against the FP64 oracle."""
     import torch
     from oracle import oracle as o
@@ -221,11 +244,12 @@ def bench_dense(steps, warmup: int):
 
     P = I.build(DENSE_WORKLOAD)
     nsteps = P.nsteps if steps is None else steps
+    general = unstructured(P)
     op = o.OracleProblem.from_problem(P)
     stream = torch.cuda.current_stream()
 
-    def whole_run(precision, nrun, warm):
-        S = Solver(P, precision=precision)
+    def whole_run(precision, nrun, warm, Q=general):
+        S = Solver(Q, precision=precision)
         args = S.args()
         st = [S.initial_state(), None]
         st[1] = torch.empty_like(st[0])
@@ -246,37 +270,42 @@ def bench_dense(steps, warmup: int):
     out = {"workload": DENSE_WORKLOAD, "cells": P.ncells, "ordinates": P.nq,
            "scattering": "Henyey-Greenstein g=0.9, dense, column-normalised", "steps": nsteps,
            "unit": "cell-ordinate updates/s", "step_form": step_form()}
-    finals = {}
+    # the headline figures of the section: the step as the library runs it
+    S, final, ms = whole_run("bf16x3", nsteps, warmup, P)
+    passes = 0 if modes_on() else 3
+    vs = step_vs_oracle(S, final, oracle_rows)
+    out.update({"precision": arithmetic("BF16 hi+lo, three products, FP32 accumulate"),
+                "ms_per_step": ms, "value": P.ncells * P.nq / (ms * 1e-3),
+                "scatter_product": product_rate(S, final, passes=passes),
+                "scatter_product_dense_random_state":
+                    product_rate(S, torch.rand_like(final), passes=passes),
+                "vs_oracle": vs, "rel_l2_vs_oracle": vs["rel_l2"]})
+    reference = final.clone()
+    S.close()
+    out["general_kernel"] = "the same kernel, its entries times 1 + 1e-8 s_q s_p"
+    out["general_step_form"] = step_form(general=True)
     for precision, label in (("bf16x3", "BF16 hi+lo, three products"),
                              ("bf16x2", "BF16, operand hi+lo and state once: two products"),
                              ("fp16x3", "FP16 hi+lo with per-row power-of-2 scaling, three "
                                         "products")):
         S, final, ms = whole_run(precision, nsteps, warmup if precision == "bf16x3" else 3)
         passes = 2 if precision == "bf16x2" else 3
-        sec = {"precision": label, "ms_per_step": ms, "steps": nsteps,
-               "value": P.ncells * P.nq / (ms * 1e-3),
-               "scatter_product": product_rate(S, final, passes=passes,
-                                               kernel="k_gemm_f16" if precision == "fp16x3"
-                                               else "k_gemm_bf16"),
-               "scatter_product_dense_random_state":
-                   product_rate(S, torch.rand_like(final), passes=passes,
-                                kernel="k_gemm_f16" if precision == "fp16x3" else "k_gemm_bf16"),
-               "vs_oracle": step_vs_oracle(S, final, oracle_rows)}
-        finals[precision] = final.clone()
+        kernel = "k_gemm_f16" if precision == "fp16x3" else "k_gemm_bf16"
+        out[precision] = {
+            "precision": label, "ms_per_step": ms, "steps": nsteps,
+            "value": P.ncells * P.nq / (ms * 1e-3),
+            "scatter_product": product_rate(S, final, passes=passes, kernel=kernel),
+            "scatter_product_dense_random_state":
+                product_rate(S, torch.rand_like(final), passes=passes, kernel=kernel),
+            "vs_oracle": step_vs_oracle(S, final, oracle_rows),
+            "rel_l2_vs_headline_final_state":
+                float(torch.linalg.vector_norm((final - reference).double()) /
+                      torch.linalg.vector_norm(reference.double()))}
         S.close()
-        out[precision] = sec
-    for k in ("bf16x2", "fp16x3"):
-        out[k]["rel_l2_vs_bf16x3_final_state"] = float(
-            torch.linalg.vector_norm((finals[k] - finals["bf16x3"]).double()) /
-            torch.linalg.vector_norm(finals["bf16x3"].double()))
-    # the headline figures of the section: the three-product BF16 run
-    out.update({"precision": "bf16x3 (hi+lo split, FP32 accumulate)",
-                "value": out["bf16x3"]["value"], "ms_per_step": out["bf16x3"]["ms_per_step"],
-                "rel_l2_vs_oracle": out["bf16x3"]["vs_oracle"]["rel_l2"]})
     # the same step with the FP32 scattering product (on the matrix cores), 20 steps from the
     # initial state: the FP32 side of the FP32-vs-mixed comparison
     S32, final32, ms32 = whole_run("fp32", 20, 1)
-    out["fp32"] = {"ms_per_step": ms32, "steps": 20,
+    out["fp32"] = {"precision": "FP32", "ms_per_step": ms32, "steps": 20,
                    "scatter_product": product_rate(S32, final32, passes=1, kernel="k_gemm_f32",
                                                    peak=FP32_MFMA_PEAK_TFLOPS),
                    "vs_oracle": step_vs_oracle(S32, final32, oracle_rows)}
@@ -287,8 +316,8 @@ def bench_dense(steps, warmup: int):
 
 def bench_imex_dense(P, op, nsteps: int, warmup: int):
     """IMEX steps with the dense HG kernel (implicit collisions through the kernel's
-    eigendecomposition: collision-free step, product with V^-1, per-cell diagonal, product
-    with V diag(lam), combine), BF16 hi+lo, over the whole run from the initial pulse; the
+    eigendecomposition: collision-free step, V^-1, per-cell diagonal, V diag(lam), combine; one launch
+    through azimuthal modes), a BF16x3 handle, over the whole run from the initial pulse; the
     one-time host set-up is timed on its own."""
     import time
     import torch
@@ -316,10 +345,13 @@ def bench_imex_dense(P, op, nsteps: int, warmup: int):
     vs = step_vs_oracle(S, st[0], lambda start, c: o.step_imex(op, start, P.dt, cells=c), n=32,
                         step=lambda a_, b_: S.step_imex(a_, b_, args), what="one IMEX step")
     S.close()
-    return {"precision": "bf16x3", "steps": nsteps, "ms_per_step": ms,
+    return {"precision": "FP32 azimuthal modes" if modes_on() else
+                         "BF16 hi+lo, three products, FP32 accumulate",
+            "steps": nsteps, "ms_per_step": ms,
             "value": P.ncells * P.nq / (ms * 1e-3), "setup_s": setup_s,
             "note": "implicit HG collisions through one eigendecomposition of K W (host FP64, "
-                    "set-up), two nq x nq products per step",
+                    "set-up), " + ("per azimuthal mode in one launch (k_az_imex)" if modes_on() else
+                                   "two nq x nq products per step"),
             "vs_oracle": vs, "rel_l2_vs_oracle": vs["rel_l2"]}
 
 
@@ -364,11 +396,12 @@ def copy_ceiling(nbytes: int, reps: int = 20, passes: int = 3):
 
 def bench_csd(steps, warmup: int):
     """CSD dose workload: phantom of 388 x 388 points (299 538 cells), 16 x 32 = 512
-    ordinates, HG g=0.95 with the BF16 hi+lo product, densities in the streaming, the beam
+    ordinates, HG g=0.95, densities in the streaming, the beam
     inflow scaled by S(E_n) G_E(E_n) at every energy step and the FP64 dose accumulated
     before every step.  The whole 500-step energy run is timed (steps=None; warm-up steps
-    run on a separate copy first); the product's MFMA utilisation is measured on the final
-    state and on a dense random state."""
+    run on a separate copy first); the product's rate is measured on the final
+    state and on a dense random state.  The general mixed-precision products run the same energy steps
+    on the kernel without its azimuthal structure."""
     import torch
     from paper_2205_08417_amd import inputs as I
     from paper_2205_08417_amd import snrt
@@ -412,8 +445,9 @@ def bench_csd(steps, warmup: int):
 
     ms_separate = run(separate_step)
     ms_step = run(fused_step)
-    final = product_rate(S, state[0])
-    dense = product_rate(S, torch.rand_like(state[0]))
+    passes = 0 if modes_on() else 3
+    final = product_rate(S, state[0], passes=passes)
+    dense = product_rate(S, torch.rand_like(state[0]), passes=passes)
     dose_ref = dose.clone()
     from oracle import oracle as o
     op = o.OracleProblem.from_problem(P)
@@ -423,70 +457,56 @@ def bench_csd(steps, warmup: int):
                                                  cells=cells),
         step=lambda a_, b_: S.step(a_, b_, args[last]))
     S.close()
-    # the two-product mode over the same energy run: its dose against the three-product dose
-    S2 = Solver(P, precision="bf16x2")
-    args2 = [S2.args(inflow_scale=float(isc[n])) for n in range(nsteps)]
-    st2 = [S2.initial_state(), None]
-    st2[1] = torch.empty_like(st2[0])
-    dose2 = torch.zeros(S2.nc, dtype=torch.float64, device="cuda")
+    # the general products over the same energy run: their doses against the one above
+    general = unstructured(P)
 
-    def fused_step2():
-        n = counter[0]
-        snrt.snrt_step_dose(S2.mesh, S2.quad, S2.scatter, args2[n], st2[0], st2[1],
-                            float(coeff[n]), dose2, S2.ws, S2.ws_bytes)
-        st2.reverse()
-        counter[0] = n + 1
+    def general_run(precision):
+        S2 = Solver(general, precision=precision)
+        args2 = [S2.args(inflow_scale=float(isc[n])) for n in range(nsteps)]
+        st = [S2.initial_state(), None]
+        st[1] = torch.empty_like(st[0])
+        d = torch.zeros(S2.nc, dtype=torch.float64, device="cuda")
 
-    counter[0] = 0
-    for _ in range(min(warmup, 5, nsteps)):
-        fused_step2()
-    counter[0] = 0
-    st2[0] = S2.initial_state()
-    dose2.zero_()
-    torch.cuda.synchronize()
-    ms_x2 = timed(fused_step2, nsteps, stream)
-    dose_diff = float(torch.linalg.vector_norm(dose2 - dose_ref) /
-                      torch.linalg.vector_norm(dose_ref))
-    S2.close()
-    # the FP16 three-product mode over the same run
-    S3 = Solver(P, precision="fp16x3")
-    args3 = [S3.args(inflow_scale=float(isc[n])) for n in range(nsteps)]
-    st3 = [S3.initial_state(), torch.empty_like(state[0])]
-    dose3 = torch.zeros(S3.nc, dtype=torch.float64, device="cuda")
+        def one_step():
+            n = counter[0]
+            snrt.snrt_step_dose(S2.mesh, S2.quad, S2.scatter, args2[n], st[0], st[1],
+                                float(coeff[n]), d, S2.ws, S2.ws_bytes)
+            st.reverse()
+            counter[0] = n + 1
 
-    def fused_step3():
-        n = counter[0]
-        snrt.snrt_step_dose(S3.mesh, S3.quad, S3.scatter, args3[n], st3[0], st3[1],
-                            float(coeff[n]), dose3, S3.ws, S3.ws_bytes)
-        st3.reverse()
-        counter[0] = n + 1
+        counter[0] = 0
+        for _ in range(min(warmup, 5, nsteps)):
+            one_step()
+        counter[0] = 0
+        st[0] = S2.initial_state()
+        d.zero_()
+        torch.cuda.synchronize()
+        ms = timed(one_step, nsteps, stream)
+        S2.close()
+        return {"ms_per_step": ms, "step_form": step_form(general=True),
+                "dose_rel_l2_vs_headline": float(torch.linalg.vector_norm(d - dose_ref) /
+                                                 torch.linalg.vector_norm(dose_ref))}
 
-    counter[0] = 0
-    torch.cuda.synchronize()
-    ms_x3f16 = timed(fused_step3, nsteps, stream)
-    dose_diff16 = float(torch.linalg.vector_norm(dose3 - dose_ref) /
-                        torch.linalg.vector_norm(dose_ref))
-    S3.close()
     return {"workload": "csd_phantom_s512", "cells": P.ncells, "ordinates": P.nq,
             "scattering": "Henyey-Greenstein g=0.95, dense, column-normalised",
-            "precision": "bf16x3 (hi+lo split, FP32 accumulate)", "steps": nsteps,
+            "precision": arithmetic("BF16 hi+lo, three products, FP32 accumulate"), "steps": nsteps,
             "energy_MeV": [float(P.meta["energy"][0]), float(P.meta["energy"][nsteps - 1])],
             "value": P.ncells * P.nq / (ms_step * 1e-3), "unit": "cell-ordinate updates/s",
             "ms_per_step": ms_step,
             "note": "a step = snrt_step_dose: the scattering product, the flux/update and the "
-                    "dose of the step's input, then the fold of the dose partials",
+                    "dose of the step's input",
             "step_form": step_form(),
             "ms_per_step_separate_dose_pass": ms_separate,
             "scatter_product": final, "scatter_product_dense_random_state": dense,
             "vs_oracle": vs_oracle, "rel_l2_vs_oracle": vs_oracle["rel_l2"],
-            "bf16x2": {"ms_per_step": ms_x2, "dose_rel_l2_vs_bf16x3": dose_diff},
-            "fp16x3": {"ms_per_step": ms_x3f16, "dose_rel_l2_vs_bf16x3": dose_diff16}}
+            "general_kernel": "the same kernel, its entries times 1 + 1e-8 s_q s_p",
+            **{p: general_run(p) for p in ("bf16x3", "bf16x2", "fp16x3")}}
 
 
 def bench_dose_gradient(nsteps: int = 500, ckpt: int = 20):
     """Gradient of the target-minus-organ dose functional w.r.t. the per-cell density on
-    the full CSD phantom (299 538 cells x 512 ordinates, the first 500 energy steps, BF16 hi+lo
-    products, checkpoints every 20): the differentiable rollout's forward pass (steps with the
+    the full CSD phantom (299 538 cells x 512 ordinates, the first 500 energy steps, checkpoints
+    every 20): the differentiable rollout's forward pass (steps with the
     fused dose) against its backward pass (segment recompute, transposed steps with the
     transposed product and the dose's adjoint terms), each one library call."""
     import numpy as np
@@ -525,7 +545,8 @@ def bench_dose_gradient(nsteps: int = 500, ckpt: int = 20):
     fwd, bwd = one_pass()
     S.close()
     return {"workload": "csd_phantom_s512", "cells": P.ncells, "ordinates": P.nq, "steps": n,
-            "checkpoint_every": ckpt, "precision": "bf16x3",
+            "checkpoint_every": ckpt,
+            "precision": arithmetic("BF16 hi+lo, three products, FP32 accumulate"),
             "functional": "sum_T A D - sum_O A D, gradient w.r.t. per-cell density",
             "forward_ms": fwd, "backward_ms": bwd, "adjoint_forward_ratio": bwd / fwd,
             "step_form": step_form(), "transposed_step_form": transposed_step_form(),
@@ -536,11 +557,10 @@ def bench_dose_gradient(nsteps: int = 500, ckpt: int = 20):
 
 def bench_moments(steps, warmup: int, degree: int = 8):
     """Moment-projected scattering (eq. SNEqns2) on the HG line source (100 352 cells x
-    1024 ordinates), HG g=0.9 to degree 8 (81 moments, padded to 96 for the MFMA kernel),
-    BF16 hi+lo: the step rate over the whole 200-step run (steps=None) against the
+    1024 ordinates), HG g=0.9 to degree 8 (81 moments): the step rate over the whole 200-step run (steps=None) against the
     dense-kernel step of the same workload; then the same number of IMEX steps (implicit
-    moment-form collisions: collision-free step, two products with the per-cell diagonal
-    between them, combine)."""
+    moment-form collisions).  Both run through azimuthal modes; with SNRT_AZIMUTH=0 through two
+    products by way of the moments, padded to 96 for the MFMA kernel (BF16 hi+lo)."""
     import torch
     from paper_2205_08417_amd import inputs as I
     from paper_2205_08417_amd.solver import Solver
@@ -583,17 +603,22 @@ def bench_moments(steps, warmup: int, degree: int = 8):
                                     step=lambda a_, b_: S.step_imex(a_, b_, args),
                                     what="one IMEX step")
     nm = (degree + 1) ** 2
-    mid = ((nm + 31) // 32) * 32                         # the library's BF16 padding (K chunk)
-    mid_tile = ((mid + 127) // 128) * 128                # product 1's output tile width
-    executed = 3 * 2.0 * P.ncells * P.nq * (mid_tile + mid)   # two products, three BF16 passes
-    useful = 2 * 2.0 * P.ncells * P.nq * nm
+    products = {}
+    if not modes_on():
+        mid = ((nm + 31) // 32) * 32                     # the library's BF16 padding (K chunk)
+        tile = ((mid + 127) // 128) * 128                # product 1's output tile width
+        products = {"moment_dimension_padded": mid,      # two products, three BF16 passes
+                    "product_flops_executed": 3 * 2.0 * P.ncells * P.nq * (tile + mid),
+                    "product_flops_useful": 2 * 2.0 * P.ncells * P.nq * nm}
     S.close()
     return {"workload": DENSE_WORKLOAD, "cells": P.ncells, "ordinates": P.nq,
             "scattering": f"moment-projected O Sigma M, HG g=0.9, degree {degree} ({nm} moments)",
-            "precision": "bf16x3", "steps": steps, "ms_per_step": ms, "step_form": step_form(),
+            "precision": arithmetic("BF16 hi+lo, three products, FP32 accumulate"),
+            "imex_precision": "FP32 azimuthal modes" if modes_on() else
+                              "BF16 hi+lo, three products, FP32 accumulate",
+            "steps": steps, "ms_per_step": ms, "step_form": step_form(),
             "value": P.ncells * P.nq / (ms * 1e-3), "unit": "cell-ordinate updates/s",
-            "moment_dimension_padded": mid, "product_flops_executed": executed,
-            "product_flops_useful": useful, "imex_ms_per_step": ms_imex,
+            **products, "imex_ms_per_step": ms_imex,
             "vs_oracle": vs_oracle, "rel_l2_vs_oracle": vs_oracle["rel_l2"],
             "imex_vs_oracle": vs_oracle_imex}
 
