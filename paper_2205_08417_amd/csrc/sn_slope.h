@@ -44,7 +44,8 @@ __device__ __forceinline__ uint32_t ratio_place(float d)   // <= kRatioSpan in t
 
 // gx, gy *= Psi.  Barth-Jespersen: d1 depends on the sign of d_f alone, and a rounded quotient
 // falls with its divisor, so the smallest of d1 / d_f over the faces is that of the largest
-// d_f > 0 or of the smallest d_f < 0: two quotients instead of one per face, the same result.
+// d_f > 0 or of the smallest d_f < 0: two quotients instead of one per face.  (ratio_in_range
+// rounds otherwise than the divide near ties only: the limiter may differ by one bit there.)
 // The gradient kernel is bound by its instructions (a Heun step of two kernels per stage, 198 450
 // cells x 256 ordinates: 741 -> 726 us).
 template <int V, int MF, int LIM, typename T>

@@ -12,9 +12,10 @@
 // reconstructs both sides in both cells.  The rows of 158 faces take half of a CU's LDS (a G row
 // per cell and halo cell instead would hold as few cells and take more arithmetic), so that the
 // slopes of one block overlap the update of another.
-// What bounds it is the latency of the scalar loads that precede a cell's rows, and the arithmetic
-// (60 % of the time at 2.3 GHz): 16 waves a block 502 us per step, 12 waves 590, 8 waves 758; the
-// records of a cell in one place and loaded ahead 441.  The step took 732 through two kernels.
+// What bounds it is the arithmetic (105.7 million vector instructions per stage, at four cycles
+// 413 000 of each SIMD's 540 000) and the latency of the scalar loads that precede a cell's rows:
+// 16 waves a block 502 us per step, 12 waves 590, 8 waves 758; the records of a cell in one place
+// and loaded ahead 447.  The step took 730 through two kernels.
 #include "sn_slope.h"
 
 namespace snrt {
